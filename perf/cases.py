@@ -35,7 +35,8 @@ from paper_1807_03097_amd import workloads as W
 
 GAUSS = 5          # points per direction of the regular and of the singular rules
 JITTER = 2e-3      # standard deviation of the control points' displacement
-SOLVE_ITERS = 200  # iterations that work() counts for a solve
+SOLVE_ITERS = 800  # iterations that work() counts for a solve (the listed one takes 829)
+RESTART = 300      # Krylov basis of a solve
 
 _context = None
 
@@ -197,7 +198,7 @@ def run(st):
         op.close()
         return y
     if call == "solve":
-        return st["op"].solve(st["f"], tol=1e-6, restart=300, maxit=3000)[0]
+        return st["op"].solve(st["f"], tol=1e-6, restart=RESTART, maxit=3000)[0]
     if call == "rhs":
         return _rhs(st)
     return st["op"].potential(st["w"], st["points"])
@@ -235,7 +236,7 @@ def work(case):
         sing = float(info.singular_pairs) * 3300.0 * (46.0 + 4.0 * nl * nl)
         w = {"bytes": nb, "flops": nf + pairs * per + sing}
     elif call == "solve":
-        basis = SOLVE_ITERS * (SOLVE_ITERS + 1) / 2
+        basis = SOLVE_ITERS * RESTART / 2
         w = {"bytes": SOLVE_ITERS * nb + 32.0 * basis * n * r, "flops": SOLVE_ITERS * nf + 16.0 * basis * n * r}
     elif call == "rhs":
         w = {"bytes": 72.0 * el * g2 + 16.0 * n * r, "flops": r * el * g2 * (40.0 + 8.0 * 2 + 4.0 * nl)}
