@@ -347,6 +347,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)op->NC * Q * (9 * 8 + 11 * 16 * R);             // node data, moments, fields
     b += (size_t)op->T.far.size() * 4 * Q * 16 / 4 * R;          // coupling partials (chunks of partners)
     b += (size_t)op->nsing * 24 + (size_t)D.N * 80 * R;
+    b += std::max((size_t)E * nl * 16, std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols)));   // right-hand side element moments
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
     b += ((size_t)restart + 1 + 8) * D.N * 16 * R;               // Krylov basis and work vectors
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
@@ -775,6 +776,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // (the upward pass stops there) but the matrix-core coupling stages them
             IGE_HIP(hipMemsetAsync(op->d_src.p, 0, op->d_src.bytes(), s));
             op->d_loc.alloc((size_t)op->NC * 3 * v.Q);
+            op->d_rhs.alloc(ige::rhs_scratch_values(v, 1));
             op->d_ybuf.alloc((size_t)D.P * v.SL * v.SL * 2 * F.rowlen * F.rowlen);
             op->d_part.alloc(std::max<size_t>(1, op->work1.size()) * 4 * v.Q);
             // one FP64 column, one degree (<= 8) on every level: the coupling over unordered
@@ -915,7 +917,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_work1.bytes() + op->d_wrk_of_tgt1.bytes() + op->d_wrk_of_tgt.bytes();
         b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes() + op->d_part.bytes();
         b += op->d_swork.bytes() + op->d_spartner.bytes() + op->d_sred_ptr.bytes() + op->d_sred_idx.bytes() + op->d_spart.bytes();
-        b += op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
+        b += op->d_rhs.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
         b += op->d_cnr.bytes() + op->d_cnc.bytes() + op->d_cld.bytes() + op->d_cidx.bytes() + op->d_corder.bytes() + op->d_cred_idx.bytes();
         b += op->d_cocc_ptr.bytes() + op->d_cocc.bytes() + op->d_cnp_ptr.bytes() + op->d_cnp_leaf.bytes();
         b += op->d_cnp_code.bytes() + op->d_csym.bytes() + op->d_cvoff.bytes() + op->d_clst.bytes();
@@ -1312,6 +1314,46 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
     return rc == IGE_OK ? tried : rc;
 }
 
+}  // extern "C"
+
+namespace {
+// right-hand sides of r columns, up to kRhsCols per launch.  The scratch of the element
+// moments holds one column from the assembly on and grows to the columns of a launch (at most
+// 256 MiB, or one column), except while the caller captures the stream, where it serves as it is
+void rhs_columns(ige_op op, int r, int kind, const double *a, const double2 *pol, ige_c64 *f, int ptr_kind)
+{
+    set_device(op->ctx);
+    const int64_t N = op->D.N;
+    hipStream_t s = op->ctx->stream;
+    const size_t one = ige::rhs_scratch_values(op->view, 1);
+    const int fit = (int)std::max<size_t>(1, ((size_t)256 << 20) / (sizeof(double2) * one));
+    int nc = std::min({r, ige::kRhsCols, fit});
+    if (op->d_rhs.n < one * nc) {
+        hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+        IGE_HIP(hipStreamIsCapturing(s, &cap));
+        if (cap == hipStreamCaptureStatusNone) {
+            IGE_HIP(hipStreamSynchronize(s));   // a launch that uses the old scratch may be in flight
+            op->d_rhs.alloc(one * nc);
+        } else {
+            nc = (int)(op->d_rhs.n / one);
+        }
+    }
+    if (ptr_kind == IGE_HOST && op->d_by.n < (size_t)N * nc) op->d_by.alloc((size_t)N * nc);
+    for (int c = 0; c < r; c += nc) {
+        const int k = std::min(nc, r - c);
+        double2 *fc = reinterpret_cast<double2 *>(f) + (size_t)c * N;
+        double2 *dst = ptr_kind == IGE_HOST ? op->d_by.p : fc;
+        ige::launch_rhs(op, kind, k, a + 3 * c, pol ? pol + 3 * c : nullptr, dst);
+        if (ptr_kind == IGE_HOST) {
+            IGE_HIP(hipMemcpyAsync(fc, dst, sizeof(double2) * N * k, hipMemcpyDeviceToHost, s));
+            IGE_HIP(hipStreamSynchronize(s));
+        }
+    }
+}
+}  // namespace
+
+extern "C" {
+
 int ige_rhs_scalar(ige_op op, int r, int kind, const double *a, ige_c64 *f, int ptr_kind)
 {
     return guard([&] {
@@ -1320,21 +1362,8 @@ int ige_rhs_scalar(ige_op op, int r, int kind, const double *a, ige_c64 *f, int 
         IGE_REQUIRE(op->view.scalar, "the operator is not the scalar single layer");
         IGE_REQUIRE(kind == IGE_RHS_PLANE || kind == IGE_RHS_POINT, "kind must be IGE_RHS_PLANE or IGE_RHS_POINT");
         IGE_REQUIRE(ptr_kind == IGE_HOST || ptr_kind == IGE_DEVICE, "bad ptr_kind");
-        set_device(op->ctx);
-        const int64_t N = op->D.N;
-        hipStream_t s = op->ctx->stream;
-        if (ptr_kind == IGE_HOST) ensure_staging(op);
-        for (int c = 0; c < r; ++c) {
-            const double *ac = a + 3 * c;
-            IGE_REQUIRE(std::isfinite(ac[0]) && std::isfinite(ac[1]) && std::isfinite(ac[2]), "a must be finite");
-            double2 *fc = reinterpret_cast<double2 *>(f) + (size_t)c * N;
-            double2 *dst = (ptr_kind == IGE_HOST) ? op->d_y.p : fc;
-            ige::launch_rhs_scalar(op, kind, ac, dst);
-            if (ptr_kind == IGE_HOST) {
-                IGE_HIP(hipMemcpyAsync(fc, op->d_y.p, sizeof(double2) * N, hipMemcpyDeviceToHost, s));
-                IGE_HIP(hipStreamSynchronize(s));
-            }
-        }
+        for (int64_t i = 0; i < 3 * (int64_t)r; ++i) IGE_REQUIRE(std::isfinite(a[i]), "a must be finite");
+        rhs_columns(op, r, kind, a, nullptr, f, ptr_kind);
     });
 }
 
@@ -1345,23 +1374,8 @@ int ige_rhs_plane_wave(ige_op op, int r, const double *dir, const ige_c64 *pol, 
         IGE_REQUIRE(op->assembled, "operator was planned, not assembled");
         IGE_REQUIRE(!op->view.scalar, "the operator is the scalar single layer: use ige_rhs_scalar");
         IGE_REQUIRE(ptr_kind == IGE_HOST || ptr_kind == IGE_DEVICE, "bad ptr_kind");
-        set_device(op->ctx);
-        const int64_t N = op->D.N;
-        hipStream_t s = op->ctx->stream;
-        if (ptr_kind == IGE_HOST) ensure_staging(op);
-        for (int c = 0; c < r; ++c) {
-            const double *d = dir + 3 * c;
-            IGE_REQUIRE(std::isfinite(d[0]) && std::isfinite(d[1]) && std::isfinite(d[2]), "direction must be finite");
-            const ige_c64 *pc = pol + 3 * c;
-            double2 *fc = reinterpret_cast<double2 *>(f) + (size_t)c * N;
-            double2 *dst = (ptr_kind == IGE_HOST) ? op->d_y.p : fc;
-            ige::launch_rhs_plane(op, d, make_double2(pc[0].re, pc[0].im), make_double2(pc[1].re, pc[1].im),
-                                  make_double2(pc[2].re, pc[2].im), dst);
-            if (ptr_kind == IGE_HOST) {
-                IGE_HIP(hipMemcpyAsync(fc, op->d_y.p, sizeof(double2) * N, hipMemcpyDeviceToHost, s));
-                IGE_HIP(hipStreamSynchronize(s));
-            }
-        }
+        for (int64_t i = 0; i < 3 * (int64_t)r; ++i) IGE_REQUIRE(std::isfinite(dir[i]), "direction must be finite");
+        rhs_columns(op, r, IGE_RHS_PLANE, dir, reinterpret_cast<const double2 *>(pol), f, ptr_kind);
     });
 }
 

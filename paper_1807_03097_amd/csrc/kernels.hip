@@ -13,7 +13,6 @@
 //   L2P        test-side moments, fused with the scatter T^T
 //   near product near_blk + near_gather: product with the stored blocks and their
 //              transposes, then a fixed-order sum per unknown
-//   rhs        plane-wave right-hand side
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -29,22 +28,11 @@ namespace {
 
 constexpr int kWave = 64;
 typedef double dx4 __attribute__((ext_vector_type(4)));   // FP64 matrix-core accumulator
-__device__ __constant__ double kInv4Pi = 0.07957747154594767;   // 1/(4 pi)
 
 __device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ inline double2 cscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
 using dm::surf_elem;
-
-// Helmholtz kernel e^{i k r} / (4 pi r) (library sincos, correctly rounded sqrt):
-// used by the assembly kernels
-__device__ inline double2 helmholtz(double kappa, double r)
-{
-    double sn, cs;
-    sincos(kappa * r, &sn, &cs);
-    const double f = kInv4Pi / r;
-    return make_double2(cs * f, sn * f);
-}
 
 // Bernstein values and derivatives of degree deg <= kMaxP at x
 __device__ inline void bernstein(int deg, double x, double *B, double *D)
@@ -1722,77 +1710,6 @@ __global__ void k_l2p_gather(DevOp o, const double2 *ybuf, double2 *y)
     y[i] = cadd(y[i], acc);
 }
 
-// ---------------------------------------------------------------------------
-// a9: plane-wave right-hand side, one thread per unknown
-// f_i = - sum_e sum_q e_inc(X_q) . w_q phi_hat_i d_aF
-// ---------------------------------------------------------------------------
-__global__ void k_rhs_plane(DevOp o, double d0, double d1, double d2, double2 p0, double2 p1, double2 p2, double2 *f)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= o.N) return;
-    const int p = o.p, n = o.n, G2 = o.G2, NL = o.nl;
-    double2 acc = make_double2(0, 0);
-    for (int c = 0; c < 2; ++c) {
-        const int32_t *in = o.inc + ((size_t)i * 2 + c) * 5;
-        const int j = in[0];
-        if (j < 0) continue;
-        const int a = in[1], i1 = in[2], i2 = in[3];
-        const double sg = (double)in[4];
-        const int du = (a == 0) ? p : p - 1, dv = (a == 0) ? p - 1 : p;
-        for (int e2 = max(0, i2 - dv); e2 <= min(n - 1, i2); ++e2)
-            for (int e1 = max(0, i1 - du); e1 <= min(n - 1, i1); ++e1) {
-                const int t1 = i1 - e1, t2 = i2 - e2;
-                const int l = (a == 0) ? t2 * (p + 1) + t1 : p * (p + 1) + t2 * p + t1;
-                const int64_t e = ((int64_t)j * n + e2) * n + e1;
-                const double *X = o.eX + e * 3 * G2;
-                const double *Ps = o.ePsi + e * 4 * NL * G2;
-                for (int q = 0; q < G2; ++q) {
-                    const double ph = o.kappa * (d0 * X[q] + d1 * X[G2 + q] + d2 * X[2 * G2 + q]);
-                    double sn, cs;
-                    sincos(ph, &sn, &cs);
-                    const double2 ex = make_double2(cs, sn);
-                    const double f0 = Ps[((size_t)0 * NL + l) * G2 + q], f1 = Ps[((size_t)1 * NL + l) * G2 + q],
-                                 f2 = Ps[((size_t)2 * NL + l) * G2 + q];
-                    const double2 dotp = cadd(cadd(cscale(f0, p0), cscale(f1, p1)), cscale(f2, p2));
-                    acc = cadd(acc, cscale(-sg, cmul(ex, dotp)));
-                }
-            }
-    }
-    f[i] = acc;
-}
-
-// scalar single layer right-hand side f_i = int g phi_i dsigma, one thread per unknown:
-// kind 0 plane wave g = exp(i kappa a.x), kind 1 point source g = G(x - a)
-__global__ void k_rhs_scalar(DevOp o, int kind, double a0, double a1, double a2, double2 *f)
-{
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= o.N) return;
-    const int p = o.p, n = o.n, G2 = o.G2, NL = o.nl;
-    const int32_t *in = o.inc + (size_t)i * 2 * 5;
-    const int j = in[0], i1 = in[2], i2 = in[3];
-    double2 acc = make_double2(0, 0);
-    for (int e2 = max(0, i2 - p); e2 <= min(n - 1, i2); ++e2)
-        for (int e1 = max(0, i1 - p); e1 <= min(n - 1, i1); ++e1) {
-            const int l = (i2 - e2) * (p + 1) + (i1 - e1);
-            const int64_t e = ((int64_t)j * n + e2) * n + e1;
-            const double *X = o.eX + e * 3 * G2;
-            const double *Ps = o.ePsi + (e * 4 + 3) * NL * G2 + (size_t)l * G2;   // weight * value * |J|
-            for (int q = 0; q < G2; ++q) {
-                double2 g;
-                if (kind == 0) {
-                    double sn, cs;
-                    sincos(o.kappa * (a0 * X[q] + a1 * X[G2 + q] + a2 * X[2 * G2 + q]), &sn, &cs);
-                    g = make_double2(cs, sn);
-                } else {
-                    const double d0 = X[q] - a0, d1 = X[G2 + q] - a1, d2 = X[2 * G2 + q] - a2;
-                    g = helmholtz(o.kappa, sqrt(d0 * d0 + d1 * d1 + d2 * d2));
-                }
-                acc = cadd(acc, cscale(Ps[q], g));
-            }
-        }
-    f[i] = acc;
-}
-
 __global__ void k_helmholtz_eval(int64_t n, double kappa, const double *r2, double2 *out, int prec,
                                  const double2 *sctab)
 {
@@ -2161,21 +2078,6 @@ void launch_l2p_gather(ige_op op, double2 *y)
 {
     const DevOp &o = op->view;
     hipLaunchKernelGGL(k_l2p_gather, dim3((o.N + 255) / 256), dim3(256), 0, lstream(op), o, op->d_ybuf.p, y);
-    IGE_LAUNCH_CHECK();
-}
-
-void launch_rhs_scalar(ige_op op, int kind, const double *a, double2 *f)
-{
-    const DevOp &o = op->view;
-    hipLaunchKernelGGL(k_rhs_scalar, dim3((o.N + 255) / 256), dim3(256), 0, lstream(op), o, kind, a[0], a[1], a[2], f);
-    IGE_LAUNCH_CHECK();
-}
-
-void launch_rhs_plane(ige_op op, const double *dir, double2 pol0, double2 pol1, double2 pol2, double2 *f)
-{
-    const DevOp &o = op->view;
-    hipLaunchKernelGGL(k_rhs_plane, dim3((o.N + 127) / 128), dim3(128), 0, lstream(op), o, dir[0], dir[1], dir[2],
-                       pol0, pol1, pol2, f);
     IGE_LAUNCH_CHECK();
 }
 

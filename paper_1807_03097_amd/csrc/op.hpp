@@ -259,6 +259,7 @@ struct ige_op_s {
     ige::DBuf<double2> d_loc;    // [NC][3][Q]   t^1, t^2, t^d
     ige::DBuf<double2> d_ybuf;   // [leaves][2][rowlen][rowlen] L2P results per leaf
     ige::DBuf<double2> d_x, d_y; // staging for host pointers
+    ige::DBuf<double2> d_rhs;    // element moments of the right-hand sides [E][nl][columns]
     // batched-apply workspaces (r columns, column index innermost)
     int bcap = 0;
     ige::DBuf<double2> d_bnpart;       // near-field partial results [nslots][rb]
@@ -375,9 +376,12 @@ size_t potential_scratch_doubles();
 double peak_probe(hipStream_t s, int kind);
 // raise a kernel's dynamic shared-memory limit above 64 KB once per process
 void lds_attr_once(const void *kern, size_t shm);
-// scalar single layer right-hand side (kind 0 plane wave of direction a, 1 point source at a)
-void launch_rhs_scalar(ige_op op, int kind, const double *a, double2 *f);
-void launch_rhs_plane(ige_op op, const double *dir, double2 pol0, double2 pol1, double2 pol2, double2 *f);
+// right-hand sides of nc <= kRhsCols columns into f [nc][N] (kind 0: plane waves of directions
+// a [nc][3] with polarisations pol [nc][3] (EFIE); kind 1: point sources at a, scalar only);
+// element moments in d_rhs
+constexpr int kRhsCols = 16;
+size_t rhs_scratch_values(const DevOp &o, int nc);
+void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f);
 // GMRES vector kernels (V: [k][r][n], vectors [r][n]; gate/run/flag: per-column int masks)
 struct GsPlan {
     int nchk = 0, nblk = 0;             // entry chunks of the dot and update kernels

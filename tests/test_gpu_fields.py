@@ -1,0 +1,38 @@
+"""Right-hand sides and potentials of several columns and points against the oracle, at the
+edges of the kernels' column groups and point tiles."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("p,level,r", [(1, 1, 1), (2, 2, 3), (2, 1, 16), (1, 2, 17), (3, 1, 5), (4, 1, 33)])
+def test_rhs_columns(kind, p, level, r):
+    # sums of at most (p+1)^2 elements x 25 points of unit-modulus terms: a few tens of
+    # roundings each, 1e-13 of the column's norm leaves a factor of more than ten
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B, workloads as W
+    pats = W.cube_sphere()
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    sc = kind == "scalar"
+    op = B.Operator(geom, p, level, 3.0, 4, 1.0, 5, 5, 1, kind=B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE)
+    o = O.Oracle(pats, p, level, 3.0, g=5, gs=5, scalar=sc)
+    dirs, pols = W.random_plane_waves(r, 11 + r)
+    if sc:
+        F = op.rhs_scalar(B.IGE_RHS_PLANE, dirs)
+        ref = [o.rhs_scalar("plane", d) for d in dirs]
+        pts = 0.3 * dirs
+        F = np.concatenate([F, op.rhs_scalar(B.IGE_RHS_POINT, pts)])
+        ref += [o.rhs_scalar("point", a) for a in pts]
+    else:
+        F = op.rhs_plane_wave(dirs, pols)
+        ref = [o.rhs_plane_wave(d, q) for d, q in zip(dirs, pols)]
+    for f, g in zip(F, ref):
+        assert _rel(f, g) < 1e-13
+    ctx.close()
