@@ -917,7 +917,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_work1.bytes() + op->d_wrk_of_tgt1.bytes() + op->d_wrk_of_tgt.bytes();
         b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes() + op->d_part.bytes();
         b += op->d_swork.bytes() + op->d_spartner.bytes() + op->d_sred_ptr.bytes() + op->d_sred_idx.bytes() + op->d_spart.bytes();
-        b += op->d_rhs.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
+        b += op->d_rhs.bytes() + op->d_pot.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
         b += op->d_cnr.bytes() + op->d_cnc.bytes() + op->d_cld.bytes() + op->d_cidx.bytes() + op->d_corder.bytes() + op->d_cred_idx.bytes();
         b += op->d_cocc_ptr.bytes() + op->d_cocc.bytes() + op->d_cnp_ptr.bytes() + op->d_cnp_leaf.bytes();
         b += op->d_cnp_code.bytes() + op->d_csym.bytes() + op->d_cvoff.bytes() + op->d_clst.bytes();
@@ -1782,25 +1782,30 @@ int ige_potential(ige_op op, int r, const ige_c64 *w, int ptr_kind, int npts, co
         set_device(op->ctx);
         hipStream_t s = op->ctx->stream;
         const int64_t N = op->D.N;
-        ige::DBuf<double2> dw, dout;
-        ige::DBuf<double> dpts, dsrc;
-        dsrc.alloc(ige::potential_source_doubles(op));
-        dpts.alloc(std::max<size_t>(1, (size_t)3 * npts));
-        dout.alloc(std::max<size_t>(1, (size_t)3 * npts));
-        if (npts) IGE_HIP(hipMemcpyAsync(dpts.p, points, sizeof(double) * 3 * npts, hipMemcpyHostToDevice, s));
+        // one workspace: parts, results, density (host w), sources, points; kept with the
+        // operator while it is at most 256 MiB
+        const int parts = npts ? ige::potential_parts(op, npts) : 1;
+        const size_t nout = (size_t)3 * npts, nsrc = ige::potential_source_doubles(op);
+        const size_t npart = parts > 1 ? nout * parts : 0, nw = ptr_kind == IGE_HOST ? (size_t)r * N : 0;
+        const size_t need = 2 * (npart + nout + nw) + nsrc + nout;
+        if (op->d_pot.n < need) {
+            IGE_HIP(hipStreamSynchronize(s));
+            op->d_pot.alloc(need);
+        }
+        double2 *dpart = reinterpret_cast<double2 *>(op->d_pot.p), *dout = dpart + npart, *dw = dout + nout;
+        double *dsrc = reinterpret_cast<double *>(dw + nw), *dpts = dsrc + nsrc;
+        if (npts) IGE_HIP(hipMemcpyAsync(dpts, points, sizeof(double) * nout, hipMemcpyHostToDevice, s));
         const double2 *W = reinterpret_cast<const double2 *>(w);
         if (ptr_kind == IGE_HOST) {
-            dw.alloc((size_t)r * N);
-            IGE_HIP(hipMemcpyAsync(dw.p, w, sizeof(double2) * r * N, hipMemcpyHostToDevice, s));
-            W = dw.p;
+            IGE_HIP(hipMemcpyAsync(dw, w, sizeof(double2) * nw, hipMemcpyHostToDevice, s));
+            W = dw;
         }
         for (int c = 0; c < r; ++c) {
-            ige::launch_potential(op, W + (size_t)c * N, npts, dpts.p, dout.p, dsrc.p);
-            if (npts)
-                IGE_HIP(hipMemcpyAsync(E + (size_t)c * 3 * npts, dout.p, sizeof(double2) * 3 * npts,
-                                       hipMemcpyDeviceToHost, s));
+            ige::launch_potential(op, W + (size_t)c * N, npts, dpts, dout, dsrc, parts, dpart);
+            if (npts) IGE_HIP(hipMemcpyAsync(E + (size_t)c * nout, dout, sizeof(double2) * nout, hipMemcpyDeviceToHost, s));
         }
         IGE_HIP(hipStreamSynchronize(s));
+        if (op->d_pot.bytes() > ((size_t)256 << 20)) op->d_pot.release();
     });
 }
 
@@ -1821,8 +1826,10 @@ int ige_potential_noalloc(ige_op op, int r, const ige_c64 *w, int npts, const do
         const int64_t N = op->D.N;
         const double2 *W = reinterpret_cast<const double2 *>(w);
         double2 *out = reinterpret_cast<double2 *>(E);
+        const int parts = npts ? ige::potential_parts(op, npts) : 1;   // in the scratch behind the sources
+        double2 *part = reinterpret_cast<double2 *>(scr + (need + 1) / 2 * 2);
         for (int c = 0; c < r; ++c)
-            ige::launch_potential(op, W + (size_t)c * N, npts, points, out + (size_t)c * 3 * npts, scr);
+            ige::launch_potential(op, W + (size_t)c * N, npts, points, out + (size_t)c * 3 * npts, scr, parts, part);
     });
 }
 

@@ -90,6 +90,28 @@ __device__ inline double2 helmholtz_r2(double kappa, double r2)
 // (the next term, 5e^3/16, is below 1e-21 for the hardware estimate's |e| < 1e-7).
 // Valid for |kappa r| < 5e7 (k fits an int).  Measured against long-double sine and
 // cosine over x in [0, 2000] and [1e-6, 1e6]: within 1.12 ulp(x) of e^{ix}.
+// The second form also returns 1/r and kappa r; it takes k and its table index from the
+// mantissa of x 128/pi + 1.5 2^52 and so holds for kappa r up to 1e13.
+__device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double2 *tab, double &ir, double &kr)
+{
+    constexpr double kInvStep = 40.74366543152521;   // 128/pi
+    constexpr double kStep = 0.02454369260617026;    // pi/128 rounded to double
+    constexpr double kRound = 6755399441055744.0;    // 1.5 2^52
+    const double y0 = __builtin_amdgcn_rsq(r2);
+    const double e = fma(-(r2 * y0), y0, 1.0);
+    const double y = fma(e * y0, fma(e, 0.375, 0.5), y0);
+    const double x = kappa * (r2 * y);
+    const double kb = fma(x, kInvStep, kRound);
+    const double k = kb - kRound;
+    const double t = fma(-k, kStep, x);
+    const double2 cs = tab[__double2loint(kb) & 255];
+    const double z = t * t;
+    const double s = fma(t * z, fma(z, 1.0 / 120.0, -1.0 / 6.0), t);   // 1/5!, -1/3!
+    const double c = fma(z, fma(fma(-1.0 / 720.0, z, 1.0 / 24.0), z, -0.5), 1.0);
+    ir = y;
+    kr = x;
+    return make_double2(fma(cs.x, c, -cs.y * s) * y, fma(cs.y, c, cs.x * s) * y);
+}
 __device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double2 *tab)
 {
     constexpr double kInvStep = 40.74366543152521;   // 128/pi

@@ -259,6 +259,7 @@ struct ige_op_s {
     ige::DBuf<double2> d_loc;    // [NC][3][Q]   t^1, t^2, t^d
     ige::DBuf<double2> d_ybuf;   // [leaves][2][rowlen][rowlen] L2P results per leaf
     ige::DBuf<double2> d_x, d_y; // staging for host pointers
+    ige::DBuf<double> d_pot;     // workspace of the potential: sources, points, results, parts
     ige::DBuf<double2> d_rhs;    // element moments of the right-hand sides [E][nl][columns]
     // batched-apply workspaces (r columns, column index innermost)
     int bcap = 0;
@@ -363,9 +364,12 @@ int near_blk_u(int nF);
 int near_mfma_mtw_ok(int nF, int rc);   // the FP64 matrix-core near product supports these blocks   // 64-column groups per block row (template choice)
 void launch_l2p_leaf(ige_op op);
 void launch_l2p_gather(ige_op op, double2 *y);
-// scattered field at npts points (device arrays; src: potential_source_doubles scratch)
+// scattered field at npts points (device arrays; src: potential_source_doubles scratch; parts
+// of the sources and, with several, their results part [parts][3 npts])
 size_t potential_source_doubles(ige_op op);
-void launch_potential(ige_op op, const double2 *w, int npts, const double *pts, double2 *out, double *src);
+int potential_parts(ige_op op, int npts);
+void launch_potential(ige_op op, const double2 *w, int npts, const double *pts, double2 *out, double *src, int parts,
+                      double2 *part);
 // fixed scratch of the allocation-free potential: address lookup (once per device, with
 // that device current), the device address (nullptr before the lookup), capacity
 void potential_scratch_init(int device);

@@ -36,3 +36,26 @@ def test_rhs_columns(kind, p, level, r):
     for f, g in zip(F, ref):
         assert _rel(f, g) < 1e-13
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("p,level,npts", [(1, 1, 1), (2, 3, 3), (2, 2, 4), (3, 2, 5), (1, 4, 257)])
+def test_potential_points(kind, p, level, npts):
+    # 1e-13: as above, the sum of E x 25 terms; the kernel value itself is good to 1.2 ulp of
+    # the phase kappa r (below 20 here)
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B, workloads as W
+    pats = W.torus()
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    sc = kind == "scalar"
+    op = B.Operator(geom, p, level, 5.0, 4, 1.0, 5, 5, 1, kind=B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE)
+    o = O.Oracle(pats, p, level, 5.0, g=5, gs=5, scalar=sc)
+    w = W.random_coeffs(op.N, 3, nrhs=2)
+    rng = np.random.default_rng(npts)
+    pts = rng.standard_normal((npts, 3))
+    pts *= rng.uniform(1.8, 3.5, (npts, 1)) / np.linalg.norm(pts, axis=1, keepdims=True)
+    E = op.potential(w, pts)
+    for c in range(2):
+        assert _rel(E[c], o.potential(w[c], pts)) < 1e-13
+    ctx.close()
