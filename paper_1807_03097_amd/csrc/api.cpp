@@ -351,7 +351,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
     b += ((size_t)restart + 1 + 8) * D.N * 16 * R;               // Krylov basis and work vectors
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
-    b += (ige::gs_part_count(gp, (int)R, restart) + ige::gs_split_count(gp, D.N, (int)R)) * 16;   // Gram-Schmidt scratch
+    b += ige::gs_part_count(gp, (int)R, restart) * 16;           // Gram-Schmidt scratch
     // copies made on first use by the many-column kernels
     if (R >= 8) b += nfp * 2 * Qp * 2 * Qp * 8;                  // FP64 coupling blocks
     if (R >= 56) {                                               // ordered-pair FP64 near blocks, operands
@@ -877,6 +877,7 @@ int ige_op_destroy(ige_op op)
         if (op->gstream) (void)hipStreamDestroy(op->gstream);
         if (op->ev_fork) (void)hipEventDestroy(op->ev_fork);
         if (op->ev_join) (void)hipEventDestroy(op->ev_join);
+        if (op->ev_gs) (void)hipEventDestroy(op->ev_gs);
         delete op;
     });
 }
@@ -1126,6 +1127,15 @@ bool mx_coupling_ok(const ige_op_s *op)
     return true;
 }
 
+// d_y = A d_x, one column on the operator's own buffers (prec FP64 or FP32 coupling)
+void apply_one_buf(ige_op op, int prec, ApplyGraph *g)
+{
+    if (g && !op->profiling && graphs_enabled())
+        run_graph(op, g, 1, prec, [&] { apply_one(op, op->d_x.p, op->d_y.p, prec); });
+    else
+        apply_one(op, op->d_x.p, op->d_y.p, prec);
+}
+
 // y = A x for r device columns ([r][N]) in the given precision; with g, the operator
 // body runs as a captured graph (not while profiling)
 void apply_dev(ige_op op, int r, const double2 *x, double2 *y, int prec, ApplyGraph *g = nullptr)
@@ -1143,7 +1153,7 @@ void apply_dev(ige_op op, int r, const double2 *x, double2 *y, int prec, ApplyGr
             }
             ensure_staging(op);
             IGE_HIP(hipMemcpyAsync(op->d_x.p, xc, sizeof(double2) * N, hipMemcpyDeviceToDevice, s));
-            run_graph(op, g, 1, prec, [&] { apply_one(op, op->d_x.p, op->d_y.p, prec); });
+            apply_one_buf(op, prec, g);
             IGE_HIP(hipMemcpyAsync(yc, op->d_y.p, sizeof(double2) * N, hipMemcpyDeviceToDevice, s));
         }
         return;
@@ -1427,30 +1437,29 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
     grow(op->d_red, (size_t)r);
     grow(op->d_scal, (size_t)r);
     grow(op->d_gspart, ige::gs_part_count(gp, r, m));
-    grow(op->d_gsplit, std::max<size_t>(1, ige::gs_split_count(gp, N, r)));
-    grow(op->d_hpack, (size_t)r * (m + 1));
-    grow(op->d_gnp, (size_t)r * gp.nblk);
-    grow(op->d_gn, (size_t)2 * r);
+    grow(op->d_gnp, (size_t)2 * r * gp.nblk);
+    grow(op->d_gn, (size_t)r);
     grow(op->d_grun, (size_t)r);
     grow(op->d_gflag, (size_t)r);
     grow(op->d_gact, (size_t)r);
     op->h_hpack.ensure((size_t)r * (m + 1));
-    double2 *split = ige::gs_split_count(gp, N, r) ? op->d_gsplit.p : nullptr;
-    double2 *h1 = op->d_h.p, *h2 = op->d_h.p + (size_t)r * hs;
-    double *nb = op->d_gn.p, *nf = op->d_gn.p + r;
+    if (!op->ev_gs) IGE_HIP(hipEventCreateWithFlags(&op->ev_gs, hipEventDisableTiming));
+    double2 *h1 = op->d_h.p, *h2 = h1 + (size_t)r * hs;
+    double *nb = op->d_gn.p, *np1 = op->d_gnp.p, *np2 = np1 + (size_t)r * gp.nblk;
     double2 *V = b32 ? nullptr : op->d_V.p, *W = op->d_w.p;
     float2 *V32 = b32 ? op->d_V32.p : nullptr;
-    auto dots = [&](int k, const double2 *w, const int *gate, double2 *h, double *nbp) {
-        if (b32) ige::launch_gs_dots(s, gp, N, r, V32, k, w, gate, op->d_gspart.p, h, hs, nbp);
-        else ige::launch_gs_dots(s, gp, N, r, V, k, w, gate, op->d_gspart.p, h, hs, nbp);
+    // one column on the one-column kernels: the operator reads d_x and writes d_y (also as a
+    // captured graph), Gram-Schmidt works on d_y, and its end writes the new basis vector both
+    // into the basis and into d_x, so no copy goes in or out
+    const bool one = r == 1 && prec <= IGE_F32;
+    if (one) ensure_staging(op);
+    auto pass = [&](int k, double2 *y, double2 *h, double *np, int *flag) {
+        if (b32) ige::launch_gs_pass(s, gp, N, r, V32, k, op->d_grun.p, op->d_gspart.p, h, hs, nb, y, np, np1, flag);
+        else ige::launch_gs_pass(s, gp, N, r, V, k, op->d_grun.p, op->d_gspart.p, h, hs, nb, y, np, np1, flag);
     };
-    auto update = [&](int k, const double2 *h, double sign, const int *gate, double2 *y, double *np) {
-        if (b32) ige::launch_gs_update(s, gp, N, r, V32, k, h, hs, sign, gate, y, split, np);
-        else ige::launch_gs_update(s, gp, N, r, V, k, h, hs, sign, gate, y, split, np);
-    };
-    // basis vector j scaled in place (x = y), with its FP32 copy in the FP32 basis
-    auto scale_basis = [&](int j, double2 *x) {
-        if (b32) ige::launch_scale_cols32(op, r, op->d_scal.p, x, x, V32 + (size_t)j * r * N);
+    // basis vector 0 scaled in place, with its FP32 copy in the FP32 basis
+    auto scale_first = [&](double2 *x) {
+        if (b32) ige::launch_scale_cols32(op, r, op->d_scal.p, x, x, V32);
         else ige::launch_scale_cols(op, r, op->d_scal.p, x, x);
     };
     auto norms = [&](const double2 *v) {
@@ -1480,7 +1489,7 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
         if (!budget) return;   // every column used its iterations
         // V0 = B - A X (FP64; with the FP32 basis in the current-vector buffer)
         apply_dev(op, r, X, W, prec, &ag);
-        double2 *cur = b32 ? op->d_wcur.p : V, *nxt = W;
+        double2 *cur = b32 ? (one ? op->d_x.p : op->d_wcur.p) : V, *nxt = W;
         ige::launch_axpby(op, (int64_t)r * N, make_double2(1, 0), B, make_double2(0, 0), cur);
         ige::launch_axpby(op, (int64_t)r * N, make_double2(-1, 0), W, make_double2(1, 0), cur);
         std::vector<double> beta = norms(cur);
@@ -1506,7 +1515,8 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
         std::vector<double> sc(r);
         for (int c = 0; c < r; ++c) sc[c] = act[c] ? 1.0 / beta[c] : 0.0;
         IGE_HIP(hipMemcpyAsync(op->d_scal.p, sc.data(), sizeof(double) * r, hipMemcpyHostToDevice, s));
-        scale_basis(0, cur);
+        scale_first(cur);
+        if (one && !b32) IGE_HIP(hipMemcpyAsync(op->d_x.p, cur, sizeof(double2) * N, hipMemcpyDeviceToDevice, s));
         IGE_HIP(hipStreamSynchronize(s));   // sc leaves scope
         std::vector<int> jdone(r, 0);
         for (int c = 0; c < r; ++c) {
@@ -1515,25 +1525,35 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
         }
         std::vector<char> run = act;
         upload_mask(run, op->d_grun.p);
+        // the operator applied to basis vector j, into the buffer that step j orthogonalises
+        auto apply_basis = [&](int j) {
+            if (one) apply_one_buf(op, prec, &ag);
+            else if (b32) apply_dev(op, r, cur, nxt, prec, &ag);
+            else apply_dev(op, r, V + (size_t)j * r * N, V + (size_t)(j + 1) * r * N, prec, &ag);
+        };
+        bool applied = false;
         for (int jj = 0; jj < m; ++jj) {
-            double2 *Vj = b32 ? cur : V + (size_t)jj * r * N, *Vj1 = b32 ? nxt : V + (size_t)(jj + 1) * r * N;
-            apply_dev(op, r, Vj, Vj1, prec, &ag);
-            // Gram-Schmidt pass 1 on the running columns, pass 2 where it lost more than half
-            dots(jj + 1, Vj1, op->d_grun.p, h1, nb);
-            update(jj + 1, h1, -1.0, op->d_grun.p, Vj1, op->d_gnp.p);
-            ige::launch_gs_norm(s, gp, r, op->d_gnp.p, op->d_grun.p, op->d_grun.p, nb, nf, op->d_scal.p,
-                                op->d_gflag.p);
-            dots(jj + 1, Vj1, op->d_gflag.p, h2, nullptr);
-            update(jj + 1, h2, -1.0, op->d_gflag.p, Vj1, op->d_gnp.p);
-            ige::launch_gs_norm(s, gp, r, op->d_gnp.p, op->d_gflag.p, op->d_grun.p, nullptr, nf, op->d_scal.p,
-                                nullptr);
-            scale_basis(jj + 1, Vj1);
-            if (b32) std::swap(cur, nxt);
-            ige::launch_gs_pack(s, r, jj + 1, h1, h2, hs, nf, op->d_hpack.p);
+            if (!applied) apply_basis(jj);
+            applied = false;
+            // Gram-Schmidt: pass 1 on the running columns, pass 2 where it lost more than half
+            // (decided on the device), and the new basis vector
+            double2 *y = one ? op->d_y.p : (b32 ? nxt : V + (size_t)(jj + 1) * r * N);
+            double2 *v = b32 ? (one ? op->d_x.p : nxt) : V + (size_t)(jj + 1) * r * N;
+            double2 *u = one && !b32 ? op->d_x.p : nullptr;
+            float2 *v32 = b32 ? V32 + (size_t)(jj + 1) * r * N : nullptr;
+            const int k = jj + 1;
+            pass(k, y, h1, np1, nullptr);
+            pass(k, y, h2, np2, op->d_gflag.p);
+            ige::launch_gs_fin(s, gp, N, r, np1, np2, op->d_grun.p, op->d_gflag.p, k, h1, h2, hs, y, v, u, v32, op->h_hpack.p);
+            IGE_HIP(hipEventRecord(op->ev_gs, s));
+            if (b32 && !one) std::swap(cur, nxt);
+            // the next step's operator starts while the host reads this column
+            if (k < m) {
+                apply_basis(k);
+                applied = true;
+            }
+            IGE_HIP(hipEventSynchronize(op->ev_gs));
             const double2 *hp = op->h_hpack.p;
-            IGE_HIP(hipMemcpyAsync(op->h_hpack.p, op->d_hpack.p, sizeof(double2) * r * (jj + 2), hipMemcpyDeviceToHost,
-                                   s));
-            IGE_HIP(hipStreamSynchronize(s));
             int nrun = 0;
             bool changed = false;
             std::vector<Cx> hc(jj + 2);
@@ -1591,7 +1611,10 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
         std::vector<char> upd(r);
         for (int c = 0; c < r; ++c) upd[c] = jdone[c] > 0;
         upload_mask(upd, op->d_gact.p);
-        if (kmax > 0) update(kmax, op->d_h.p, 1.0, op->d_gact.p, X, nullptr);
+        if (kmax > 0) {
+            if (b32) ige::launch_gs_add(s, gp, N, r, V32, kmax, op->d_h.p, hs, op->d_gact.p, X);
+            else ige::launch_gs_add(s, gp, N, r, V, kmax, op->d_h.p, hs, op->d_gact.p, X);
+        }
     }
 }
 }  // namespace

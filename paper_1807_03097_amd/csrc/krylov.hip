@@ -55,15 +55,32 @@ __device__ inline double wave_sum(double v)
     return v;
 }
 
+// |y_c|^2 from its nblk partials: every wave that asks gets the same bits
+__device__ inline double norm_of(const double *np, int nblk, int lane)
+{
+    double a = 0.0;
+    for (int b = lane; b < nblk; b += kWave) a += np[b];
+    return wave_sum(a);
+}
+
 // part[(c (k+1) + kk) nchk + ch] = sum over chunk ch of conj(V[kk][c][i]) w_c[i] for
 // the basis indices kk of this block's group (blockIdx.z); slot kk = k holds |w_c|^2
 // over the chunk.  One wave per basis index, each wave holding the chunk of w.
 template <typename VT>
 __global__ __launch_bounds__(256) void k_gs_dot(int64_t n, int r, const VT *V, int k, int kgs, const double2 *w,
-                                                const int *gate, double2 *part, int nchk)
+                                                const int *gate, double2 *part, int nchk, const double *npart, int nblk,
+                                                const double *nb, int *flag)
 {
     const int c = blockIdx.y, ch = blockIdx.x, wv = threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    if (!gate[c]) return;
+    if (!gate[c]) {
+        if (flag && ch == 0 && blockIdx.z == 0 && threadIdx.x == 0) flag[c] = 0;
+        return;
+    }
+    if (flag) {   // second pass: only when the first left less than half of |w|^2
+        const bool again = norm_of(npart + (size_t)c * nblk, nblk, lane) < 0.5 * nb[c];
+        if (ch == 0 && blockIdx.z == 0 && threadIdx.x == 0) flag[c] = again;
+        if (!again) return;   // the same for every wave of the column
+    }
     const int64_t i0 = (int64_t)ch * kWave * kGsT + lane;
     const double2 *wc = w + (size_t)c * n;
     double2 wl[kGsT];
@@ -127,29 +144,26 @@ __global__ __launch_bounds__(256) void k_gs_sum(int r, int k, int nchk, const do
     else if (nb && gate[c]) nb[c] = a.x;
 }
 
-// y_c -= sum_{kk in group} V[kk][c] h[c][kk] (sign -1) or += (sign +1).  With one
-// group (gridDim.z == 1) the result goes to y in place and the block's |y_c|^2 to
-// npart[c][block] (if npart); with several, group z writes its sum to
-// split[z][c][i] for k_gs_comb.
+// y_c += sign sum_kk V[kk][c] h[c][kk] in place, and the block's |y_c|^2 to npart[c][block] (if
+// npart): many entries (n r of 2^21 and more), a block covers 256 kGsE entries and walks the
+// basis.  Bound by reading the basis once.
 template <typename VT>
-__global__ __launch_bounds__(256) void k_gs_upd(int64_t n, int r, const VT *V, int k, int kgs, const double2 *h,
-                                                int hs, double sign, const int *gate, double2 *y, double2 *split,
-                                                double *npart, int nblk)
+__global__ __launch_bounds__(256) void k_gs_upd(int64_t n, int r, const VT *V, int k, const double2 *h, int hs,
+                                                double sign, const int *gate, double2 *y, double *npart, int nblk)
 {
     __shared__ double sh[4];
     const int c = blockIdx.y;
     if (!gate[c]) return;
     const int64_t i0 = (int64_t)blockIdx.x * 256 * kGsE + threadIdx.x;
-    const int k0 = blockIdx.z * kgs, k1 = min(k, k0 + kgs);
     double2 acc[kGsE];
 #pragma unroll
     for (int e = 0; e < kGsE; ++e) acc[e] = make_double2(0.0, 0.0);
     const double2 *hc = h + (size_t)c * hs;
     // whole blocks: four basis vectors at a time with every load in flight
     const bool full = (int64_t)(blockIdx.x + 1) * 256 * kGsE <= n;
-    int kk = k0;
+    int kk = 0;
     if (full)
-        for (; kk + 4 <= k1; kk += 4) {
+        for (; kk + 4 <= k; kk += 4) {
             double2 vv[4][kGsE], hh[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
@@ -166,7 +180,7 @@ __global__ __launch_bounds__(256) void k_gs_upd(int64_t n, int r, const VT *V, i
                     acc[e].y = fma(vv[u][e].x, hh[u].y, fma(vv[u][e].y, hh[u].x, acc[e].y));
                 }
         }
-    for (; kk < k1; ++kk) {
+    for (; kk < k; ++kk) {
         const double2 hh = hc[kk];
         const VT *v = V + ((size_t)kk * r + c) * n;
 #pragma unroll
@@ -178,14 +192,6 @@ __global__ __launch_bounds__(256) void k_gs_upd(int64_t n, int r, const VT *V, i
                 acc[e].y = fma(vv.x, hh.y, fma(vv.y, hh.x, acc[e].y));
             }
         }
-    }
-    if (gridDim.z > 1) {
-#pragma unroll
-        for (int e = 0; e < kGsE; ++e) {
-            const int64_t i = i0 + 256 * e;
-            if (i < n) split[((size_t)blockIdx.z * r + c) * n + i] = acc[e];
-        }
-        return;
     }
     double s = 0.0;
     double2 *yc = y + (size_t)c * n;
@@ -207,73 +213,124 @@ __global__ __launch_bounds__(256) void k_gs_upd(int64_t n, int r, const VT *V, i
     if (threadIdx.x == 0) npart[(size_t)c * nblk + blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
 }
 
-// y_c += sign sum_z split[z][c] (z in order), and the block's |y_c|^2 to npart
-__global__ __launch_bounds__(256) void k_gs_comb(int64_t n, int r, int ng, const double2 *split, double sign,
-                                                 const int *gate, double2 *y, double *npart, int nblk)
+// The same update for few entries, bound by the latency of a chain of launches: a block of
+// WV waves covers 64 entries, wave w takes the basis indices w, w + WV, ... with kGsU loads
+// in flight, the waves' sums are added in order, and the block that holds all of the basis
+// also finishes its entries (no split over blocks with a sum behind it).  With nchk > 0 the
+// block first sums the dot partials of its column itself (block 0 writes h and |w_c|^2),
+// which saves the launch of k_gs_sum; every block repeats k nchk loads, so only for up to
+// kGsFuse chunks.  One column, n = 3,468, restart 300: the update, its sum over 38 groups
+// and the two sums of dot partials and norms took 30 us per pass, now the update is 6 us and
+// no sums follow it (a solve step 236 -> 183 us with the second pass decided on the device,
+// the column written to host memory by the last kernel, and the next product started
+// before the host reads it).
+constexpr int kGsU = 8;
+constexpr int kGsFuse = 8;      // dot chunks
+constexpr int kGsFuseK = 2048;  // basis indices whose h fits the block's shared memory
+template <typename VT, int WV>
+__global__ __launch_bounds__(64 * WV) void k_gs_updw(int64_t n, int r, const VT *V, int k, const double2 *part, int nchk,
+                                                     double2 *h, int hs, double *nb, double sign, const int *gate,
+                                                     double2 *y, double *npart, int nblk)
 {
-    __shared__ double sh[4];
-    const int c = blockIdx.y;
+    extern __shared__ double2 sg[];   // [WV][64] sums, then [k] h
+    const int c = blockIdx.y, lane = threadIdx.x % kWave, wv = threadIdx.x / kWave;
     if (!gate[c]) return;
-    const int64_t i0 = (int64_t)blockIdx.x * 256 * kGsE + threadIdx.x;
-    double s = 0.0;
-    double2 *yc = y + (size_t)c * n;
-#pragma unroll
-    for (int e = 0; e < kGsE; ++e) {
-        const int64_t i = i0 + 256 * e;
-        if (i >= n) continue;
-        double2 a = make_double2(0.0, 0.0);
-        for (int z = 0; z < ng; ++z) {
-            const double2 v = split[((size_t)z * r + c) * n + i];
-            a.x += v.x;
-            a.y += v.y;
+    double2 *sh = sg + WV * 64;
+    const double2 *hc = h + (size_t)c * hs;
+    if (nchk > 0) {
+        const double2 *pc = part + (size_t)c * (k + 1) * nchk;
+        for (int kk = threadIdx.x; kk <= k; kk += 64 * WV) {
+            double2 a = make_double2(0.0, 0.0);
+            for (int ch = 0; ch < nchk; ++ch) {
+                a.x += pc[(size_t)kk * nchk + ch].x;
+                a.y += pc[(size_t)kk * nchk + ch].y;
+            }
+            if (kk < k) sh[kk] = a;
+            if (blockIdx.x == 0) {
+                if (kk < k) h[(size_t)c * hs + kk] = a;
+                else if (nb) nb[c] = a.x;
+            }
         }
-        double2 t = yc[i];
-        t.x = fma(sign, a.x, t.x);
-        t.y = fma(sign, a.y, t.y);
-        yc[i] = t;
-        s = fma(t.x, t.x, fma(t.y, t.y, s));
+        hc = sh;
+        __syncthreads();
+    }
+    const int64_t i = (int64_t)blockIdx.x * 64 + lane, ic = i < n ? i : n - 1;
+    double2 acc = make_double2(0.0, 0.0);
+    int kk = wv;
+    for (; kk + (kGsU - 1) * WV < k; kk += kGsU * WV) {
+        double2 vv[kGsU];
+#pragma unroll
+        for (int u = 0; u < kGsU; ++u) vv[u] = ld2(V + ((size_t)(kk + u * WV) * r + c) * n + ic);
+#pragma unroll
+        for (int u = 0; u < kGsU; ++u) {
+            const double2 hh = hc[kk + u * WV];
+            acc.x = fma(vv[u].x, hh.x, fma(-vv[u].y, hh.y, acc.x));
+            acc.y = fma(vv[u].x, hh.y, fma(vv[u].y, hh.x, acc.y));
+        }
+    }
+    for (; kk < k; kk += WV) {
+        const double2 vv = ld2(V + ((size_t)kk * r + c) * n + ic), hh = hc[kk];
+        acc.x = fma(vv.x, hh.x, fma(-vv.y, hh.y, acc.x));
+        acc.y = fma(vv.x, hh.y, fma(vv.y, hh.x, acc.y));
+    }
+    sg[threadIdx.x] = acc;
+    __syncthreads();
+    if (wv != 0) return;
+    double2 a = sg[lane];
+#pragma unroll
+    for (int w = 1; w < WV; ++w) {
+        a.x += sg[w * 64 + lane].x;
+        a.y += sg[w * 64 + lane].y;
+    }
+    double s = 0.0;
+    if (i < n) {
+        double2 &yi = y[(size_t)c * n + i];
+        const double2 t = make_double2(fma(sign, a.x, yi.x), fma(sign, a.y, yi.y));
+        yi = t;
+        s = fma(t.x, t.x, t.y * t.y);
     }
     if (!npart) return;
     s = wave_sum(s);
-    if (threadIdx.x % kWave == 0) sh[threadIdx.x / kWave] = s;
-    __syncthreads();
-    if (threadIdx.x == 0) npart[(size_t)c * nblk + blockIdx.x] = ((sh[0] + sh[1]) + sh[2]) + sh[3];
+    if (lane == 0) npart[(size_t)c * nblk + blockIdx.x] = s;
 }
 
-// per column (one wave each): nf[c] = sum_b npart[c][b] for gate columns; then
-// scal[c] = 1/sqrt(nf[c]) for run columns (0 otherwise) and, if flag, flag[c] =
-// run[c] and nf[c] < nb[c] / 2 (the second-pass test)
-__global__ __launch_bounds__(256) void k_gs_norm(int r, int nblk, const double *npart, const int *gate,
-                                                 const int *run, const double *nb, double *nf, double *scal, int *flag)
+// The end of a step: nf = |y_c|^2 from the partials of the column's last pass (npart2 where
+// flag, else npart1; every block sums them, in one fixed order), v_c = y_c / |y_c| into v (may
+// be y), its copies u (the operator's input) and v32 (FP32 basis) where given; columns that
+// are not run get zeros.  Block 0 of a column writes the coefficients of both passes and
+// |y_c| to out [k + 1], pinned host memory, so no copy follows the kernel.
+__global__ __launch_bounds__(256) void k_gs_fin(int64_t n, int r, int nblk, const double *npart1, const double *npart2,
+                                                const int *run, const int *flag, int k, const double2 *h1,
+                                                const double2 *h2, int hs, const double2 *y, double2 *v, double2 *u,
+                                                float2 *v32, double2 *out)
 {
-    const int c = blockIdx.x * 4 + threadIdx.x / kWave, lane = threadIdx.x % kWave;
-    if (c >= r) return;
-    if (gate[c]) {
-        double a = 0.0;
-        for (int b = lane; b < nblk; b += kWave) a += npart[(size_t)c * nblk + b];
-        a = wave_sum(a);
-        if (lane == 0) nf[c] = a;
+    const int c = blockIdx.y;
+    const bool on = run[c] != 0, two = on && flag[c] != 0;
+    const double nf = on ? norm_of((two ? npart2 : npart1) + (size_t)c * nblk, nblk, threadIdx.x % kWave) : 0.0;
+    const double sc = nf > 0.0 ? 1.0 / sqrt(nf) : 0.0;
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) {
+        const size_t o = (size_t)c * n + i;
+        double2 t = make_double2(0.0, 0.0);
+        if (on) {
+            const double2 yi = y[o];
+            t = make_double2(sc * yi.x, sc * yi.y);
+        }
+        v[o] = t;
+        if (u) u[o] = t;
+        if (v32) v32[o] = make_float2((float)t.x, (float)t.y);
     }
-    if (lane != 0) return;
-    const double v = nf[c];
-    if (gate[c] || !run[c]) scal[c] = (run[c] && v > 0.0) ? 1.0 / sqrt(v) : 0.0;
-    if (flag) flag[c] = run[c] && v < 0.5 * nb[c];
-}
-
-// out[c][0..k) = h1[c] + h2[c], out[c][k] = (sqrt(nf[c]), 0): the new Hessenberg column
-__global__ void k_gs_pack(int r, int k, const double2 *h1, const double2 *h2, int hs, const double *nf, double2 *out)
-{
-    const int64_t id = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (id >= (int64_t)r * (k + 1)) return;
-    const int c = (int)(id / (k + 1)), kk = (int)(id % (k + 1));
-    double2 v;
-    if (kk < k) {
-        const double2 a = h1[(size_t)c * hs + kk], b = h2[(size_t)c * hs + kk];
-        v = make_double2(a.x + b.x, a.y + b.y);
-    } else {
-        v = make_double2(sqrt(nf[c]), 0.0);
+    if (blockIdx.x != 0 || !on) return;
+    double2 *oc = out + (size_t)c * (k + 1);
+    for (int kk = threadIdx.x; kk < k; kk += 256) {
+        double2 a = h1[(size_t)c * hs + kk];
+        if (two) {
+            const double2 b = h2[(size_t)c * hs + kk];
+            a = make_double2(a.x + b.x, a.y + b.y);
+        }
+        oc[kk] = a;
     }
-    out[id] = v;
+    if (threadIdx.x == 0) oc[k] = make_double2(sqrt(nf), 0.0);
 }
 
 // y = a x + b y; with b = 0 the old y is not read (it may hold anything, NaN included)
@@ -346,82 +403,85 @@ GsPlan gs_plan(int64_t n, int r, int kmax)
 {
     GsPlan g;
     g.nchk = cdiv(n, kWave * kGsT);
-    g.nblk = cdiv(n, 256 * kGsE);
+    // few entries: the update in blocks of 64 entries, whose waves share the basis (16 waves
+    // while that gives fewer than two blocks per CU)
+    g.waves = cdiv(n, 256 * kGsE) * (int64_t)r >= kFillBlocks ? 0 : (cdiv(n, 64) * (int64_t)r < 512 ? 16 : 4);
+    g.nblk = g.waves ? cdiv(n, 64) : cdiv(n, 256 * kGsE);
     // groups of basis indices so that a pass launches enough blocks to fill the chip
     g.dot_groups = std::max(1, std::min(cdiv(kFillBlocks, (int64_t)g.nchk * r), cdiv(kmax, 4)));
-    g.upd_groups = std::max(1, std::min(cdiv(kFillBlocks, (int64_t)g.nblk * r), cdiv(kmax, 8)));
     return g;
 }
 
 size_t gs_part_count(const GsPlan &g, int r, int kmax) { return (size_t)r * (kmax + 1) * g.nchk; }
-size_t gs_split_count(const GsPlan &g, int64_t n, int r) { return g.upd_groups > 1 ? (size_t)g.upd_groups * r * n : 0; }
 
 namespace {
 template <typename VT>
-void gs_dots(hipStream_t s, const GsPlan &g, int64_t n, int r, const VT *V, int k, const double2 *w, const int *gate,
-             double2 *part, double2 *h, int hs, double *nb)
+void gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const VT *V, int k, const double2 *part, double2 *h,
+               int hs, double *nb, double sign, const int *gate, double2 *y, double *npart)
 {
-    const int ng = std::max(1, std::min(g.dot_groups, cdiv(k, 4)));
-    const int kgs = cdiv(k, ng);
-    hipLaunchKernelGGL(k_gs_dot<VT>, dim3(g.nchk, r, ng), dim3(256), 0, s, n, r, V, k, kgs, w, gate, part, g.nchk);
-    IGE_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_gs_sum, dim3(cdiv((int64_t)r * (k + 1), 4)), dim3(256), 0, s, r, k, g.nchk, part, gate, h, hs,
-                       nb);
+    if (g.waves == 0) {
+        hipLaunchKernelGGL(k_gs_upd<VT>, dim3(g.nblk, r), dim3(256), 0, s, n, r, V, k, h, hs, sign, gate, y, npart, g.nblk);
+    } else {
+        const size_t shm = sizeof(double2) * ((size_t)g.waves * 64 + (part ? k : 0));
+        const int nchk = part ? g.nchk : 0;
+        if (g.waves == 16)
+            hipLaunchKernelGGL((k_gs_updw<VT, 16>), dim3(g.nblk, r), dim3(1024), shm, s, n, r, V, k, part, nchk, h, hs, nb,
+                               sign, gate, y, npart, g.nblk);
+        else
+            hipLaunchKernelGGL((k_gs_updw<VT, 4>), dim3(g.nblk, r), dim3(256), shm, s, n, r, V, k, part, nchk, h, hs, nb,
+                               sign, gate, y, npart, g.nblk);
+    }
     IGE_HIP(hipGetLastError());
 }
 
 template <typename VT>
-void gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const VT *V, int k, const double2 *h, int hs,
-               double sign, const int *gate, double2 *y, double2 *split, double *npart)
+void gs_pass(hipStream_t s, const GsPlan &g, int64_t n, int r, const VT *V, int k, const int *gate, double2 *part,
+             double2 *h, int hs, double *nb, double2 *y, double *npart, const double *npart1, int *flag)
 {
-    const int ng = split ? std::max(1, std::min(g.upd_groups, cdiv(k, 8))) : 1;
-    const int kgs = cdiv(k, ng);
-    hipLaunchKernelGGL(k_gs_upd<VT>, dim3(g.nblk, r, ng), dim3(256), 0, s, n, r, V, k, kgs, h, hs, sign, gate, y,
-                       split, npart, g.nblk);
+    const int ng = std::max(1, std::min(g.dot_groups, cdiv(k, 4)));
+    hipLaunchKernelGGL(k_gs_dot<VT>, dim3(g.nchk, r, ng), dim3(256), 0, s, n, r, V, k, cdiv(k, ng), y, gate, part, g.nchk,
+                       npart1, g.nblk, nb, flag);
     IGE_HIP(hipGetLastError());
-    if (ng > 1) {
-        hipLaunchKernelGGL(k_gs_comb, dim3(g.nblk, r), dim3(256), 0, s, n, r, ng, split, sign, gate, y, npart, g.nblk);
+    if (flag) {
+        gate = flag;
+        nb = nullptr;
+    }
+    const bool fuse = g.waves && g.nchk <= kGsFuse && k <= kGsFuseK;
+    if (!fuse) {
+        hipLaunchKernelGGL(k_gs_sum, dim3(cdiv((int64_t)r * (k + 1), 4)), dim3(256), 0, s, r, k, g.nchk, part, gate, h, hs, nb);
         IGE_HIP(hipGetLastError());
     }
+    gs_update(s, g, n, r, V, k, fuse ? part : nullptr, h, hs, nb, -1.0, gate, y, npart);
 }
 }  // namespace
 
-void launch_gs_dots(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const double2 *w,
-                    const int *gate, double2 *part, double2 *h, int hs, double *nb)
+void launch_gs_pass(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const int *gate,
+                    double2 *part, double2 *h, int hs, double *nb, double2 *y, double *npart, const double *npart1, int *flag)
 {
-    gs_dots(s, g, n, r, V, k, w, gate, part, h, hs, nb);
+    gs_pass(s, g, n, r, V, k, gate, part, h, hs, nb, y, npart, npart1, flag);
+}
+void launch_gs_pass(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const int *gate,
+                    double2 *part, double2 *h, int hs, double *nb, double2 *y, double *npart, const double *npart1, int *flag)
+{
+    gs_pass(s, g, n, r, V, k, gate, part, h, hs, nb, y, npart, npart1, flag);
+}
+void launch_gs_add(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, double2 *h, int hs,
+                   const int *gate, double2 *y)
+{
+    gs_update(s, g, n, r, V, k, (const double2 *)nullptr, h, hs, nullptr, 1.0, gate, y, nullptr);
+}
+void launch_gs_add(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, double2 *h, int hs,
+                   const int *gate, double2 *y)
+{
+    gs_update(s, g, n, r, V, k, (const double2 *)nullptr, h, hs, nullptr, 1.0, gate, y, nullptr);
 }
 
-void launch_gs_dots(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const double2 *w,
-                    const int *gate, double2 *part, double2 *h, int hs, double *nb)
+void launch_gs_fin(hipStream_t s, const GsPlan &g, int64_t n, int r, const double *npart1, const double *npart2,
+                   const int *run, const int *flag, int k, const double2 *h1, const double2 *h2, int hs, const double2 *y,
+                   double2 *v, double2 *u, float2 *v32, double2 *out)
 {
-    gs_dots(s, g, n, r, V, k, w, gate, part, h, hs, nb);
-}
-
-void launch_gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const double2 *h,
-                      int hs, double sign, const int *gate, double2 *y, double2 *split, double *npart)
-{
-    gs_update(s, g, n, r, V, k, h, hs, sign, gate, y, split, npart);
-}
-
-void launch_gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const double2 *h,
-                      int hs, double sign, const int *gate, double2 *y, double2 *split, double *npart)
-{
-    gs_update(s, g, n, r, V, k, h, hs, sign, gate, y, split, npart);
-}
-
-void launch_gs_norm(hipStream_t s, const GsPlan &g, int r, const double *npart, const int *gate, const int *run,
-                    const double *nb, double *nf, double *scal, int *flag)
-{
-    hipLaunchKernelGGL(k_gs_norm, dim3(cdiv(r, 4)), dim3(256), 0, s, r, g.nblk, npart, gate, run, nb, nf, scal, flag);
-    IGE_HIP(hipGetLastError());
-}
-
-void launch_gs_pack(hipStream_t s, int r, int k, const double2 *h1, const double2 *h2, int hs, const double *nf,
-                    double2 *out)
-{
-    const int64_t tot = (int64_t)r * (k + 1);
-    hipLaunchKernelGGL(k_gs_pack, dim3(cdiv(tot, 256)), dim3(256), 0, s, r, k, h1, h2, hs, nf, out);
+    hipLaunchKernelGGL(k_gs_fin, dim3(cdiv(n, 256), r), dim3(256), 0, s, n, r, g.nblk, npart1, npart2, run, flag, k, h1, h2,
+                       hs, y, v, u, v32, out);
     IGE_HIP(hipGetLastError());
 }
 

@@ -272,10 +272,11 @@ struct ige_op_s {
     ige::DBuf<double2> d_wcur;         // FP64 current basis vectors (with the FP32 basis)
     ige::DBuf<double2> d_h;                          // [2][r][restart + 2] per-pass coefficients
     ige::DBuf<double> d_red, d_scal;
-    ige::DBuf<double2> d_gspart, d_gsplit, d_hpack;  // Gram-Schmidt partials, split sums, packed column
-    ige::DBuf<double> d_gnp, d_gn;                   // norm partials; [2][r] norms before / after
+    ige::DBuf<double2> d_gspart;                     // Gram-Schmidt dot partials
+    ige::DBuf<double> d_gnp, d_gn;                   // norm partials of both passes; [r] squared norms before
     ige::DBuf<int> d_grun, d_gflag, d_gact;          // per-column masks
-    ige::HBuf<double2> h_hpack;
+    ige::HBuf<double2> h_hpack;                      // new Hessenberg column, written by the device
+    hipEvent_t ev_gs = nullptr;                      // that column is there
 
     ige::DevOp view{};
 };
@@ -388,29 +389,30 @@ size_t rhs_scratch_values(const DevOp &o, int nc);
 void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f);
 // GMRES vector kernels (V: [k][r][n], vectors [r][n]; gate/run/flag: per-column int masks)
 struct GsPlan {
-    int nchk = 0, nblk = 0;             // entry chunks of the dot and update kernels
-    int dot_groups = 1, upd_groups = 1; // basis-index groups per pass (fill the chip at small n r)
+    int nchk = 0, nblk = 0;             // entry chunks of the dot and blocks of the update kernel
+    int dot_groups = 1;                 // basis-index groups of the dot kernel (fill the chip at small n r)
+    int waves = 0;                      // update: 0 in blocks of 1024 entries, else 64 entries, the basis over this many waves
 };
 GsPlan gs_plan(int64_t n, int r, int kmax);
 size_t gs_part_count(const GsPlan &g, int r, int kmax);        // double2 partials of a dot pass
-size_t gs_split_count(const GsPlan &g, int64_t n, int r);      // double2 split sums of an update
-// h[c][kk] = <V[kk][c], w_c> (kk < k, gate columns; 0 elsewhere), nb[c] = |w_c|^2 if nb
-void launch_gs_dots(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const double2 *w,
-                    const int *gate, double2 *part, double2 *h, int hs, double *nb);
-// y_c += sign V_c h_c for gate columns; npart (if given) gets per-block |y_c|^2
-void launch_gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const double2 *h,
-                      int hs, double sign, const int *gate, double2 *y, double2 *split, double *npart);
-// the same two passes over an FP32 basis (sums and w, y in FP64)
-void launch_gs_dots(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const double2 *w,
-                    const int *gate, double2 *part, double2 *h, int hs, double *nb);
-void launch_gs_update(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const double2 *h,
-                      int hs, double sign, const int *gate, double2 *y, double2 *split, double *npart);
-// nf = |y|^2 of gate columns; scal = 1/|y| for run columns (0 for the others);
-// flag (if given) = second Gram-Schmidt pass needed
-void launch_gs_norm(hipStream_t s, const GsPlan &g, int r, const double *npart, const int *gate, const int *run,
-                    const double *nb, double *nf, double *scal, int *flag);
-void launch_gs_pack(hipStream_t s, int r, int k, const double2 *h1, const double2 *h2, int hs, const double *nf,
-                    double2 *out);
+// one Gram-Schmidt pass over the gate columns: h[c][kk] = <V[kk][c], y_c> (kk < k), nb[c] = |y_c|^2,
+// y_c -= V_c h_c, npart = per-block |y_c|^2 afterwards; FP64 or FP32 basis (sums and y FP64).
+// With flag it is the second pass: it runs for the columns whose first pass (norm partials
+// npart1) left less than half of |y_c|^2 = nb, and sets flag for them; nb is kept
+void launch_gs_pass(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, const int *gate,
+                    double2 *part, double2 *h, int hs, double *nb, double2 *y, double *npart, const double *npart1, int *flag);
+void launch_gs_pass(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, const int *gate,
+                    double2 *part, double2 *h, int hs, double *nb, double2 *y, double *npart, const double *npart1, int *flag);
+// y_c += V_c h_c for gate columns
+void launch_gs_add(hipStream_t s, const GsPlan &g, int64_t n, int r, const double2 *V, int k, double2 *h, int hs,
+                   const int *gate, double2 *y);
+void launch_gs_add(hipStream_t s, const GsPlan &g, int64_t n, int r, const float2 *V, int k, double2 *h, int hs,
+                   const int *gate, double2 *y);
+// the end of a step: v_c = y_c / |y_c| with copies u and v32 (each may be null; columns outside
+// run: zeros), out[c] = (h1_c + h2_c where flag [k], |y_c|) in host memory
+void launch_gs_fin(hipStream_t s, const GsPlan &g, int64_t n, int r, const double *npart1, const double *npart2,
+                   const int *run, const int *flag, int k, const double2 *h1, const double2 *h2, int hs, const double2 *y,
+                   double2 *v, double2 *u, float2 *v32, double2 *out);
 void launch_axpby(ige_op op, int64_t n, double2 a, const double2 *x, double2 b, double2 *y);
 void launch_norm2_b(ige_op op, int r, const double2 *x, double *out);
 void launch_scale_cols(ige_op op, int r, const double *s, const double2 *x, double2 *y);
