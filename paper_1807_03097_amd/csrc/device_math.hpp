@@ -112,6 +112,29 @@ __device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double
     kr = x;
     return make_double2(fma(cs.x, c, -cs.y * s) * y, fma(cs.y, c, cs.x * s) * y);
 }
+// The same in two parts, for kernels that put other work behind the table read: the first
+// returns 1/r, the cosine and sine of the reduced angle and the table entry, the second the value
+__device__ inline void helmholtz_tab_begin(double kappa, double r2, const double2 *tab, double &ir, double &c, double &s,
+                                           double2 &cs)
+{
+    constexpr double kInvStep = 40.74366543152521;   // 128/pi
+    constexpr double kStep = 0.02454369260617026;    // pi/128 rounded to double
+    constexpr double kRound = 6755399441055744.0;    // 1.5 2^52
+    const double y0 = __builtin_amdgcn_rsq(r2);
+    const double e = fma(-(r2 * y0), y0, 1.0);
+    ir = fma(e * y0, fma(e, 0.375, 0.5), y0);
+    const double x = kappa * (r2 * ir);
+    const double kb = fma(x, kInvStep, kRound);
+    cs = tab[__double2loint(kb) & 255];
+    const double t = fma(-(kb - kRound), kStep, x);
+    const double z = t * t;
+    s = fma(t * z, fma(z, 1.0 / 120.0, -1.0 / 6.0), t);                       // 1/5!, -1/3!
+    c = fma(z, fma(fma(-1.0 / 720.0, z, 1.0 / 24.0), z, -0.5), 1.0);
+}
+__device__ inline double2 helmholtz_tab_end(double ir, double c, double s, double2 cs)
+{
+    return make_double2(fma(cs.x, c, -cs.y * s) * ir, fma(cs.y, c, cs.x * s) * ir);
+}
 __device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double2 *tab)
 {
     constexpr double kInvStep = 40.74366543152521;   // 128/pi
@@ -179,6 +202,30 @@ __device__ inline double2 to_c(double2 a, double) { return a; }
 __device__ inline float2 to_c(double2 a, float) { return make_float2((float)a.x, (float)a.y); }
 __device__ inline double2 to_d(double2 a) { return a; }
 __device__ inline double2 to_d(float2 a) { return make_double2(a.x, a.y); }
+
+// v of the lane N places on inside the 16-lane row (rotation)
+template <int N>
+__device__ inline double row_ror(double v)
+{
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), 0x120 + N, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), 0x120 + N, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
+}
+// lanes 0-31: a of the lane + a of lane + 32; lanes 32-63: the same of b (the lower half of b
+// changes places with the upper half of a, no selects)
+__device__ inline double swap32_add(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// 16-lane rows 0, 2: a of the row + a of the next row; rows 1, 3: b of the row before + b of the row
+__device__ inline double swap16_add(double a, double b)
+{
+    const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+    const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+    return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
 
 // Sum V values over the 64 lanes of a wave by recursive halving: at each step a
 // lane keeps half of its values and adds the partner's copy of that half.  On exit
