@@ -346,6 +346,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)E * (3 + 4 * nl) * G2 * 8 + (size_t)E * psi_fragment_doubles(nl, G2) * 8 + (size_t)E * 96;
     b += (size_t)op->NC * Q * (9 * 8 + 11 * 16 * R);             // node data, moments, fields
     b += (size_t)op->T.far.size() * 4 * Q * 16 / 4 * R;          // coupling partials (chunks of partners)
+    b += nfp * ((Q + 16 * kSymTiles - 1) / (16 * kSymTiles)) * 2 * 4 * Q * 16;   // one column: partials per unordered pair
     b += (size_t)op->nsing * 24 + (size_t)D.N * 80 * R;
     b += std::max((size_t)E * nl * 16, std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols)));   // right-hand side element moments
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
@@ -779,49 +780,17 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             op->d_rhs.alloc(ige::rhs_scratch_values(v, 1));
             op->d_ybuf.alloc((size_t)D.P * v.SL * v.SL * 2 * F.rowlen * F.rowlen);
             op->d_part.alloc(std::max<size_t>(1, op->work1.size()) * 4 * v.Q);
-            // one FP64 column, one degree (<= 8) on every level: the coupling over unordered
-            // pairs when asked (IGE_M2L_SYM=1), items = cluster t with up to
-            // IGE_M2L_SYM_CHUNK (default 4) partners s > t
-            op->m2l_sym = false;
-            if (const char *e = std::getenv("IGE_M2L_SYM"))
-                op->m2l_sym = std::atoi(e) != 0 && !F.varq && !T.far.empty() && v.Q <= 81 &&
-                              ige::m2l_sym_shared_bytes(v.Q) <= (size_t)64 * 1024;
-            if (op->m2l_sym) {
-                int CHS = 4;
-                if (const char *e = std::getenv("IGE_M2L_SYM_CHUNK")) CHS = std::max(1, std::min(64, std::atoi(e)));
-                std::vector<int32_t> spart;
-                op->swork.clear();
-                size_t i = 0;
-                while (i < T.far.size()) {   // sorted by level, cluster, partner
-                    const int lvl = T.far[i][0], tg = T.far[i][1];
-                    const int beg = (int)spart.size();
-                    size_t k = i;
-                    for (; k < T.far.size() && T.far[k][0] == lvl && T.far[k][1] == tg; ++k)
-                        if (T.far[k][2] > tg) spart.push_back((int32_t)(op->lvl_off[lvl] + T.far[k][2]));
-                    for (int b = beg; b < (int)spart.size(); b += CHS)
-                        op->swork.push_back({(int32_t)(op->lvl_off[lvl] + tg), b, std::min((int)spart.size(), b + CHS)});
-                    i = k;
+            // one FP64 column: the coupling over unordered pairs; IGE_M2L_SYM=1 takes
+            // IGE_M2L_SYM_CHUNK (default 4) partners per item instead of the rule's
+            if (!T.far.empty()) {
+                int chunk = 0;
+                op->m2l_sym = false;
+                if (const char *e = std::getenv("IGE_M2L_SYM")) op->m2l_sym = std::atoi(e) != 0 && !F.varq && v.Q <= 81;
+                if (op->m2l_sym) {
+                    chunk = 4;
+                    if (const char *e = std::getenv("IGE_M2L_SYM_CHUNK")) chunk = std::max(1, std::min(64, std::atoi(e)));
                 }
-                IGE_REQUIRE(2 * spart.size() == T.far.size(), "far pairs are not symmetric");
-                // the longest items launch first
-                std::stable_sort(op->swork.begin(), op->swork.end(), [](const ige::M2LWork &a, const ige::M2LWork &b) {
-                    return a.end - a.beg > b.end - b.beg;
-                });
-                // per cluster its slots: the row sides of its items, then the column sides
-                // of its pairs, in that fixed order
-                const int nw = (int)op->swork.size();
-                std::vector<int32_t> sptr((size_t)op->NC + 1, 0);
-                for (const auto &w : op->swork) sptr[w.tgt + 1]++;
-                for (int32_t c : spart) sptr[c + 1]++;
-                for (int c = 0; c < op->NC; ++c) sptr[c + 1] += sptr[c];
-                std::vector<int32_t> sidx(sptr[op->NC]), fill(sptr.begin(), sptr.end() - 1);
-                for (int w = 0; w < nw; ++w) sidx[fill[op->swork[w].tgt]++] = w;
-                for (size_t k = 0; k < spart.size(); ++k) sidx[fill[spart[k]]++] = nw + (int32_t)k;
-                op->d_swork.upload(op->swork, s);
-                op->d_spartner.upload(spart, s);
-                op->d_sred_ptr.upload(sptr, s);
-                op->d_sred_idx.upload(sidx, s);
-                op->d_spart.alloc(((size_t)nw + spart.size()) * 4 * v.Q);
+                ige::plan_m2l_sym(op, s, chunk);
             }
             if (op->stored) ige::store_coupling(op);
             IGE_HIP(hipStreamCreate(&op->aux));

@@ -95,6 +95,12 @@ struct NearCmpView {
     const int32_t *occ_ptr, *occ, *np_ptr, *np_leaf, *np_code;
 };
 
+// item of the unordered-pair coupling: cluster, range in its partner list, first row
+struct SymWork {
+    int32_t tgt, beg, end, r0;
+};
+constexpr int kSymTiles = 8;   // most row tiles of 16 per item
+
 struct M2LWork {
     int32_t tgt;      // global cluster id
     int32_t beg, end; // range in the partner array
@@ -134,17 +140,13 @@ struct ige_op_s {
     // 0.1757 against 0.1797 ms per apply, four runs each; alone it is slower, 76 against
     // 70 us, with the registers of the wider items)
     bool near_one = true;
-    // one FP64 column, one degree (<= 8) on every level: the coupling over unordered far
-    // pairs, each kernel value used for both clusters of the pair (IGE_M2L_SYM=1).  Off by
-    // default: at C2 it halves the kernel evaluations and cuts the VALU instructions per
-    // ordered node pair by about a third, yet the kernel is only 7 % faster (86 against
-    // 92 us; the values pass through shared memory, the row layout reads the partner's
-    // nodes and fields once per row instead of once per three rows, and three workgroups
-    // per CU fit instead of four), and the slot reduction costs 4.5 us more: 0.188-0.191
-    // against 0.188 ms per apply
+    // one FP64 column: the coupling over unordered far pairs, each kernel value used for both
+    // clusters of the pair (coupling_sym.hip).  m2l_sym: the item size was asked for
+    // (IGE_M2L_SYM=1 and IGE_M2L_SYM_CHUNK; one degree <= 8 on every level)
     bool m2l_sym = false;
-    std::vector<ige::M2LWork> swork;      // row cluster with a chunk of partners of larger index
-    ige::DBuf<ige::M2LWork> d_swork;
+    int sym_rt = 1;                       // row tiles of 16 per wave (two row halves per item)
+    std::vector<ige::SymWork> swork;      // row cluster with a chunk of partners of larger index
+    ige::DBuf<ige::SymWork> d_swork;
     ige::DBuf<int32_t> d_spartner, d_sred_ptr, d_sred_idx;   // partners; per cluster its slots
     ige::DBuf<double2> d_spart;           // [items + partners][4][Q] partial couplings
     // many columns: the near-field product on the second stream beside the far field
@@ -167,10 +169,10 @@ struct ige_op_s {
     // shared memory per workgroup of the generated single-column coupling (0: what it
     // needs); more limits its workgroups per CU and leaves registers to the near field
     size_t m2l_lds = 0;
-    // wave issue priority of the once-per-entry near-field product (0 or 1, the latter
-    // ahead of the coupling kernel's waves on shared SIMDs; measured: no gain per apply,
-    // and slower alone, so 0)
-    int near_prio = 0;
+    // wave issue priority of the once-per-entry near-field product (0 or 1, the latter ahead of
+    // the coupling kernel's waves on shared SIMDs): its loads go out first and the coupling
+    // computes while they are under way (level 5: 141 us per apply against 146 with 0)
+    int near_prio = 1;
     // BF16 coupling of wide column chunks: real and imaginary row tiles in one wave
     // (IGE_M2L_RM, default 1)
     bool m2l_rm = true;
@@ -357,7 +359,11 @@ void near_bf16(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
 bool near_f64mx_ok(ige_op op, int r);
 void near_f64mx(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
 void launch_m2l_reduce(ige_op op, int prec);
-size_t m2l_sym_shared_bytes(int Q);
+// one FP64 column: work lists of the unordered-pair coupling (chunk partners per item,
+// 0: by rule), its launch and its reduction
+void plan_m2l_sym(ige_op op, hipStream_t s, int chunk);
+void launch_m2l_sym(ige_op op);
+void launch_m2l_reduce_sym(ige_op op);
 void launch_l2l(ige_op op);
 // near-field product; records mid (if given) between the block pass and the reduction
 void launch_spmv(ige_op op, const double2 *x, double2 *y, hipStream_t st, hipEvent_t mid = nullptr);
