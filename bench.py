@@ -505,16 +505,28 @@ def main():
 
     Qc = (q + 1) ** 2
     Qpc = 32 * ((Qc + 31) // 32)
-    # FP64 applies of 8 or more columns: coupling on the FP64 matrix cores (stored blocks)
-    f64mx = (args.prec == 0 and r >= 8 and Qpc <= 128 and info.far_pairs > 0
-             and os.environ.get("IGE_M2L_F64") != "generate")
+    # FP64 applies of several columns: coupling on the FP64 matrix cores, with values evaluated
+    # as the operand, or from stored blocks where the autotuner chose them
+    f64st = args.prec == 0 and bool(tuned) and tuned.get("m2l_f64_matrix_cores") == 1
+    f64mx = args.prec == 0 and r > 1 and info.far_pairs > 0
 
     def roofline_coupling(stage_ms):
-        """Matrix-core coupling (r > 1, BF16 precisions; FP64 with 8 or more columns):
-        issued matrix-core operations of the real product [[Gr,-Gi],[Gi,Gr]] . [Re V; Im V]
-        over padded 2Qp x 2Qp blocks and column chunks, over the kernel's own time."""
+        """Matrix-core coupling (r > 1, FP64 and BF16 precisions): issued matrix-core
+        operations of the real product [[Gr,-Gi],[Gi,Gr]] . [Re V; Im V] over padded 2Qp x 2Qp
+        blocks and column chunks (FP64 with values evaluated in place: rows padded to 16,
+        nodes to 4, columns to 8), over the kernel's own time."""
         if not (f64mx or (args.prec in (2, 3, 4) and r > 1)):
             return None
+        if f64mx and not f64st:
+            rc = -(-r // -(-4 * r // 64))
+            tiles = (r // rc) * -(-4 * rc // 8) + (-(-4 * rc // 8) if r % rc else 0)
+            issued = info.far_pairs * 16.0 * -(-Qc // 16) * 4 * -(-Qc // 4) * tiles * 16 * 2 * 2
+            useful = info.far_pairs * 8.0 * Qc * Qc * 4 * r
+            t_ms = stage_ms["m2l_kernel"]
+            ach = issued / (t_ms * 1e-3) / 1e12
+            return {"kernel": "k_m2l_gen", "bound": "mfma", "achieved": ach, "peak": FP64_MFMA_PEAK_TFLOPS,
+                    "unit": "TFLOP/s", "frac": ach / FP64_MFMA_PEAK_TFLOPS, "traffic": None,
+                    "useful_tflops": useful / (t_ms * 1e-3) / 1e12, "issued_flop": issued, "avg_ms": t_ms}
         Q, Qp = Qc, Qpc
         MT = Qp // 16
         if f64mx:

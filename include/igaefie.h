@@ -207,15 +207,15 @@ enum { IGE_F64 = 0, IGE_F32 = 1, IGE_BF16 = 2, IGE_BF16X3 = 3, IGE_BF16X3_ALL = 
 
 /* y = A x for r right-hand sides (A the compressed operator).  x, y: N*r complex.
  * r > 1 runs the batched kernels (columns in chunks, every kernel value and matrix
- * entry read or computed once per chunk); r >= 8 applies the coupling on the FP64
- * matrix cores (see ige_apply_prec, IGE_F64). */
+ * entry read or computed once per chunk); the coupling runs on the FP64 matrix
+ * cores (see ige_apply_prec, IGE_F64). */
 int ige_apply(ige_op op, int r, const ige_c64 *x, ige_c64 *y, int ptr_kind);
 
 /* As ige_apply, with the coupling stage (interpolated-kernel values and their
  * products, M2L) in the given precision:
- *   IGE_F64   FP64 (as ige_apply; with 8 or more columns the kernel matrices are
- *             stored in FP64, both orientations, and applied on the FP64 matrix cores,
- *             unless autotuned otherwise or IGE_M2L_F64=generate);
+ *   IGE_F64   FP64 (as ige_apply; several columns on the FP64 matrix cores, with kernel
+ *             values evaluated per apply; with 8 or more columns the autotuner may choose
+ *             kernel matrices stored in FP64 instead, both orientations);
  *   IGE_F32   FP32 kernel values: evaluated and accumulated in FP32 when generated
  *             on the fly, an FP32 copy of the stored blocks with FP64 accumulation when
  *             stored; relative error about kappa * diam * 2^-23 on the far field;
@@ -251,8 +251,8 @@ int ige_apply_prec(ige_op op, int r, const ige_c64 *x, ige_c64 *y, int ptr_kind,
  *   1 column tiles per wave of the split-BF16 near-field product (1, 2, 4),
  *   2 column tiles per wave of the FP64 matrix-core near-field product of 8 to 55
  *     columns (1, 2, 4),
- *   3 columns per workgroup of the generated FP64/FP32 coupling (1, 2, 4; capped by
- *     shared memory),
+ *   3 columns per workgroup of the generated FP32 coupling (1, 2, 4; capped by shared
+ *     memory),
  *   4 staging of the BF16 coupling blocks: 1 double-buffered (the next block loaded
  *     step by step during the current product), 0 one buffer with the next block
  *     prefetched into registers,

@@ -354,7 +354,6 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
     b += ige::gs_part_count(gp, (int)R, restart) * 16;           // Gram-Schmidt scratch
     // copies made on first use by the many-column kernels
-    if (R >= 8) b += nfp * 2 * Qp * 2 * Qp * 8;                  // FP64 coupling blocks
     if (R >= 56) {                                               // ordered-pair FP64 near blocks, operands
         b += (size_t)nblk * 2 * Qn * 2 * Qn * 8;
         const size_t SL = s > 0 ? (size_t)D.n / s : 0;
@@ -1227,7 +1226,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
             switch (id) {
                 case ige::kTuneM2lDb: return 1;
                 case ige::kTuneM2lOrder: return 0;
-                case ige::kTuneM2lF64: return 1;
+                case ige::kTuneM2lF64: return 0;
                 case ige::kTuneM2lNcol: return -1;   // the smallest chunk holding all columns
                 case ige::kTuneNearBxNt: return r > 32 ? 4 : (r > 16 ? 2 : 1);
                 case ige::kTuneNearMfmaNt: return r > 16 ? 2 : 1;
@@ -1238,10 +1237,10 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
         const bool mx = r > 1 && prec >= IGE_BF16 && op->mxl.empty(), near_bx = r > 1 && prec == IGE_BF16X3_ALL;
         const bool near_mfma = r >= 8 && prec != IGE_BF16X3_ALL && ige::near_mfma_mtw_ok(op->view.nF, op->view.rc) &&
                                !ige::near_f64mx_ok(op, r);
-        // FP64 coupling on the matrix cores (default) against the generated kernel, whose
-        // columns per workgroup are tuned only where it is the default
+        // FP64 coupling from stored blocks against the kernel evaluated per apply (default);
+        // the columns per workgroup of the generated FP32 coupling
         const bool f64mx = prec == IGE_F64 && ige::m2l_f64mx_ok(op, r);
-        const bool gen = r > 1 && prec <= IGE_F32 && !op->stored && !op->work.empty() && !f64mx;
+        const bool gen = r > 1 && prec == IGE_F32 && !op->stored && !op->work.empty();
         const int split = prec == IGE_BF16 ? 1 : 3;
         struct Knob {
             bool on;
@@ -1255,7 +1254,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
                                             {near_bx, ige::kTuneNearBxNt, 0, {1, 2, 4}},
                                             {near_mfma, ige::kTuneNearMfmaNt, 0, {1, 2, 4}},
                                             {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
-                                            {f64mx, ige::kTuneM2lF64, IGE_F64, {0}}};
+                                            {f64mx, ige::kTuneM2lF64, IGE_F64, {1}}};
         // each candidate timed in two rounds (minimum kept); a candidate replaces the
         // default only when it is more than 2 % faster (the timings vary by about that)
         std::vector<int> chosen(ige::kTuneKnobs, -1);

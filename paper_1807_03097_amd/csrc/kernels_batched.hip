@@ -547,8 +547,10 @@ __global__ void k_m2l_reduce_b(DevOp o, int r, const int32_t *wrk_of_tgt, const 
     for (int t = threadIdx.x; t < Q * r; t += blockDim.x) {
         const int mm = t / r, c = t % r;
         double2 u[4] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
-        for (int w = b; w < e; ++w)
-            for (int k = 0; k < 4; ++k) u[k] = caddb(u[k], to_d2(part[(((size_t)w * 4 + k) * Qs + mm) * r + c]));
+        for (int w = b; w < e; ++w)   // scalar: the fourth field alone
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                if (k == 3 || !o.scalar) u[k] = caddb(u[k], to_d2(part[(((size_t)w * 4 + k) * Qs + mm) * r + c]));
         const double *T = o.nodeT + (size_t)gc * 6 * Qs;
         double2 t1 = make_double2(0, 0), t2 = make_double2(0, 0);
         for (int k = 0; k < 3; ++k) {
@@ -956,13 +958,15 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
             hipLaunchKernelGGL(k_m2l_reduce_b<double2>, dim3(op->NC), dim3(256), 0, s, o, r, op->d_mwrk_of_tgt.p,
                                op->d_bmpart64.p, op->d_bloc.p);
             IGE_HIP(hipGetLastError());
-        } else if (op->stored) {
+        } else if (op->stored && !(prec == IGE_F64 && r >= 8)) {   // many FP64 columns: generating is faster
             mark(12);
             m2l_stored(op, r, prec, op->d_bsrc.p, op->d_bloc.p, s);
             mark(3);
         } else {
             mark(12);
-            {
+            if (prec == IGE_F64) {
+                m2l_generate(op, r, op->d_bsrc.p, s);
+            } else {
                 // shared memory for the largest of the levels' node counts
                 size_t per = 0;
                 for (int lvl = std::max(0, op->lfar); lvl <= o.L; ++lvl) {
@@ -977,24 +981,19 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
                 const int rb = std::min(rbmax, tune_get(op, kTuneM2lRb, r, prec, rbmax));
                 const dim3 grid(op->work.size(), chunks(rb)), blk(kM2LThreadsB);
                 const size_t shm = fixed + per * rb;
-                if (prec == IGE_F32) {
+                {
                     switch (rb) {
                         case 4: hipLaunchKernelGGL((k_m2l_b<float, 4>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
                         case 2: hipLaunchKernelGGL((k_m2l_b<float, 2>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
                         default: hipLaunchKernelGGL((k_m2l_b<float, 1>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
                     }
-                } else {
-                    switch (rb) {
-                        case 4: hipLaunchKernelGGL((k_m2l_b<double, 4>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                        case 2: hipLaunchKernelGGL((k_m2l_b<double, 2>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                        default: hipLaunchKernelGGL((k_m2l_b<double, 1>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                    }
                 }
                 IGE_HIP(hipGetLastError());
             }
             mark(3);
-            hipLaunchKernelGGL(k_m2l_reduce_b<double2>, dim3(op->NC), dim3(256), 0, s, o, r, op->d_wrk_of_tgt.p, op->d_bpart.p,
-                               op->d_bloc.p);
+            hipLaunchKernelGGL(k_m2l_reduce_b<double2>, dim3(op->NC), dim3(256), 0, s, o, r,
+                               prec == IGE_F64 && m2l_gen_long(op, r) ? op->d_mwrk_of_tgt.p : op->d_wrk_of_tgt.p,
+                               op->d_bpart.p, op->d_bloc.p);
             IGE_HIP(hipGetLastError());
         }
         if (o.varq)   // levels of a smaller degree: local expansions back to the degree-q nodes

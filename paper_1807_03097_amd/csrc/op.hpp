@@ -345,6 +345,9 @@ void ensure_coupling_bf16(ige_op op, int split);
 // coupling of the FP64 operator on the FP64 matrix cores (many columns): partials d_bmpart64
 void ensure_coupling_f64(ige_op op);
 void m2l_f64mx(ige_op op, int r, const double2 *src, hipStream_t s, hipEvent_t mid = nullptr);
+// the same with the kernel evaluated per apply: partials d_bpart
+bool m2l_gen_long(const ige_op_s *op, int r);   // items of mwork instead of work
+void m2l_generate(ige_op op, int r, const double2 *src, hipStream_t s);
 // whether the FP64 apply of r columns can take (ok) and takes (use) the matrix-core coupling
 bool m2l_f64mx_ok(ige_op op, int r);
 bool m2l_f64mx_use(ige_op op, int r);
