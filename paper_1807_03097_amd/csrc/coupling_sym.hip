@@ -338,19 +338,18 @@ void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
     const auto &F = op->F;
     // Partners per item when not asked for.  Two: the shorter items hide the kernel's own
     // latencies and end together (level 4 solve, 829 iterations, 107 ms against 113 with three and
-    // 118 with four; level 6, 27,912 ordered pairs, degrees up to 14: 719 us per apply against 725
-    // with four).  Four beside a near-field product that takes at least half as long, when the items
-    // then all start in one round of four per CU: they spread over the CUs that the product's waves
-    // share (level 5, one column, 141 us against 150 with two or three, 153 with six).  The times
-    // compared are near bytes at 4.7 TB/s and steps of 16 rows x 4 columns at 340 cycles on 1,024
-    // SIMDs (level 5, degree 8: 1.2; level 4: 0.2).
+    // 118 with four).  Four beside a near-field product that takes at least half as long: fewer
+    // items start and load their rows beside it (level 5, one column, 141 us against 150 with two
+    // or three, 153 with six; torus level 5, degree 5, near field four times the coupling: 616
+    // against 663; level 6, degrees up to 14: 725 against 719).  The times compared are near bytes
+    // at 4.7 TB/s and steps of 16 rows x 4 columns at 340 cycles on 1,024 SIMDs.
     double steps = 0.0;
     for (const auto &f : T.far) {
         const int Q = (F.ql[f[0]] + 1) * (F.ql[f[0]] + 1);
         steps += 0.5 * ((Q + 12) / 16) * ((Q + 3) / 4);
     }
     const double near_us = (double)op->cmp.nval * 16.0 / 4.7e6, far_us = steps * 340.0 / (1024.0 * 2400.0);
-    if (chunk <= 0) chunk = near_us > 0.5 * far_us && T.far.size() / 2 <= 4 * 1024 ? 4 : 2;
+    if (chunk <= 0) chunk = near_us > 0.5 * far_us ? 4 : 2;
     std::vector<int32_t> spart;
     op->swork.clear();
     int rt = 1;
