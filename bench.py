@@ -571,15 +571,21 @@ def main():
                 return {"kernel": "k_near_bx", "bound": "mfma", "achieved": ach, "peak": BF16_MFMA_PEAK_TFLOPS,
                         "unit": "TFLOP/s", "frac": ach / BF16_MFMA_PEAK_TFLOPS, "traffic": None,
                         "issued_flop": issued, "avg_ms": t_ms}
+            if not (nF <= 128 or r > (4 if nF <= 256 else 2)):
+                passes = (r + 3) // 4
+                alg = info.near_nnz * 16 * passes + N * 16 * r
+                return {"kernel": "k_near_blk_b", "bound": "hbm", "achieved": alg / (t_ms * 1e-3) / 1e9,
+                        "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": alg / (t_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
+                        "traffic": None, "algorithmic_bytes": int(alg), "avg_ms": t_ms}
             flops = info.near_leaf_pairs * nF * nF * 8.0 * r
             ach = flops / (t_ms * 1e-3) / 1e12
-            out = {"kernel": "k_near_md" if r >= 56 else "k_near_mfma", "bound": "mfma", "achieved": ach,
+            out = {"kernel": "k_near_cols", "bound": "mfma", "achieved": ach,
                    "peak": FP64_MFMA_PEAK_TFLOPS, "unit": "TFLOP/s", "frac": ach / FP64_MFMA_PEAK_TFLOPS,
                    "traffic": None, "flop": flops, "avg_ms": t_ms}
-            if r >= 56:
-                # real products over the padded blocks: (2 Qn) x (2 Qn) by 64 columns per chunk
-                Qn = 32 * ((nF + 31) // 32)
-                out["issued_flop"] = info.near_leaf_pairs * (-(-r // 64)) * 2.0 * (2 * Qn) ** 2 * 64
+            # row tiles of 16, groups of 4 slots, tiles of 8 columns per chunk of at most 64
+            nch = -(-r // 64)
+            out["issued_flop"] = (info.near_leaf_pairs * 8.0 * 16 * -(-nF // 16) * 4 * -(-nF // 4)
+                                  * nch * 8 * -(-(-(-r // nch)) // 8))
             return out
         if dom == "near_spmv" and near_once:
             # the method's bytes: every distinct entry of the symmetric near-field matrix
@@ -625,7 +631,7 @@ def main():
         if rf["bound"] == "hbm":
             m = peaks["hbm_GBps"]
         elif rf["bound"] == "mfma":
-            m = peaks["f64_mfma_TFLOPs"] if rf["kernel"] in ("k_m2l_md", "k_near_md", "k_near_mfma") \
+            m = peaks["f64_mfma_TFLOPs"] if rf["kernel"] in ("k_m2l_md", "k_near_cols") \
                 else peaks["bf16_mfma_TFLOPs"]
         rf["peak_measured"] = m
         rf["frac_of_measured"] = None if m is None else rf["achieved"] / m

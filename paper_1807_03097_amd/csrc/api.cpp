@@ -354,11 +354,6 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
     b += ige::gs_part_count(gp, (int)R, restart) * 16;           // Gram-Schmidt scratch
     // copies made on first use by the many-column kernels
-    if (R >= 56) {                                               // ordered-pair FP64 near blocks, operands
-        b += (size_t)nblk * 2 * Qn * 2 * Qn * 8;
-        const size_t SL = s > 0 ? (size_t)D.n / s : 0;
-        b += (size_t)D.P * SL * SL * ((R + 63) / 64) * 64 * 2 * Qn * 8;
-    }
     if (opts && opts->refine) {
         const int ip = opts->inner_prec;
         if (opts->inner_tol >= 1e-5) b += ((size_t)restart + 1) * D.N * 8 * R;   // FP32 inner basis
@@ -647,9 +642,9 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
                 // many FP64 columns: stored blocks on the FP64 matrix cores (default) or
                 // evaluated per apply (IGE_M2L_F64=generate)
                 if (const char *e = std::getenv("IGE_M2L_F64")) op->f64mx_off = std::string(e) == "generate";
-                // many FP64 columns: near field on ordered-pair FP64 blocks (default) or on
-                // the stored unordered blocks and their transposes (IGE_NEAR_F64=blocks)
-                if (const char *e = std::getenv("IGE_NEAR_F64")) op->near_md_off = std::string(e) == "blocks";
+                // several FP64 columns: near field over ordered leaf pairs (default) or every
+                // block once for both of its products (IGE_NEAR_F64=blocks)
+                if (const char *e = std::getenv("IGE_NEAR_F64")) op->near_blocks = std::string(e) == "blocks";
                 if (op->nfp > 0) {
                     op->d_fpair.upload(fpair, s);
                     // matrix-core coupling: per target, work items of up to 32 partners
@@ -878,7 +873,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_fpair.bytes() + op->d_fred_ptr.bytes() + op->d_fred_idx.bytes();
         b += op->d_Gb1.bytes() + op->d_Gb3.bytes() + op->d_vb.bytes() + op->d_bmpart.bytes();
         b += op->d_Gd.bytes() + op->d_vd.bytes() + op->d_bmpart64.bytes();
-        b += op->d_nd.bytes() + op->d_xnd.bytes() + op->d_ndpart.bytes();
+        b += op->d_nfwork.bytes() + op->d_nforder.bytes() + op->d_nfred_ptr.bytes() + op->d_nfred_idx.bytes() + op->d_ndpart.bytes();
         b += op->d_nb3.bytes() + op->d_xnb.bytes() + op->d_nbpart.bytes() + op->d_nbwork.bytes();
         b += op->d_nbpartner.bytes() + op->d_nbslot.bytes() + op->d_nborder.bytes() + op->d_nbred_ptr.bytes();
         b += op->d_nbred_idx.bytes() + op->d_morder.bytes();
@@ -1229,14 +1224,11 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
                 case ige::kTuneM2lF64: return 0;
                 case ige::kTuneM2lNcol: return -1;   // the smallest chunk holding all columns
                 case ige::kTuneNearBxNt: return r > 32 ? 4 : (r > 16 ? 2 : 1);
-                case ige::kTuneNearMfmaNt: return r > 16 ? 2 : 1;
                 default: return -1;                   // the largest that fits
             }
         };
         // coordinate descent over the knobs that the (r, prec) apply uses
         const bool mx = r > 1 && prec >= IGE_BF16 && op->mxl.empty(), near_bx = r > 1 && prec == IGE_BF16X3_ALL;
-        const bool near_mfma = r >= 8 && prec != IGE_BF16X3_ALL && ige::near_mfma_mtw_ok(op->view.nF, op->view.rc) &&
-                               !ige::near_f64mx_ok(op, r);
         // FP64 coupling from stored blocks against the kernel evaluated per apply (default);
         // the columns per workgroup of the generated FP32 coupling
         const bool f64mx = prec == IGE_F64 && ige::m2l_f64mx_ok(op, r);
@@ -1252,7 +1244,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
                                             {mxon, ige::kTuneM2lDb, split, {1, 0}},
                                             {mxon, ige::kTuneM2lNcol, split, {64, 128, 256}},
                                             {near_bx, ige::kTuneNearBxNt, 0, {1, 2, 4}},
-                                            {near_mfma, ige::kTuneNearMfmaNt, 0, {1, 2, 4}},
+                                            {false, ige::kTuneUnused, 0, {}},
                                             {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
                                             {f64mx, ige::kTuneM2lF64, IGE_F64, {1}}};
         // each candidate timed in two rounds (minimum kept); a candidate replaces the

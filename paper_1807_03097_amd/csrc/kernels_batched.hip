@@ -873,9 +873,6 @@ void transpose_cols(hipStream_t s, int64_t N, int r, const double2 *in, double2 
     }                                                                                                        \
     IGE_HIP(hipGetLastError())
 
-int near_mfma_mtw_ok(int nF, int rc);
-void near_batched_mfma(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
-
 void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, double2 *yt, hipEvent_t *ev, int prec)
 {
     const DevOp &o = op->view;
@@ -898,8 +895,7 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
     auto near = [&](hipStream_t st) {
         mark_on(7, st);
         if (prec == IGE_BF16X3_ALL) near_bf16(op, r, xt, yt, st);
-        else if (near_f64mx_ok(op, r)) near_f64mx(op, r, xt, yt, st);
-        else if (r >= 8 && near_mfma_mtw_ok(o.nF, o.rc)) near_batched_mfma(op, r, xt, yt, st);
+        else if (near_cols_use(op, r)) near_cols(op, r, xt, yt, st);
         else near_batched(op, r, xt, yt, st);
         mark_on(11, st);
         mark_on(8, st);
@@ -1052,202 +1048,6 @@ void batched_to_rows(ige_op op, int r, const double2 *x, double2 *xt, hipStream_
 void batched_to_cols(ige_op op, int r, const double2 *yt, double2 *y, hipStream_t s)
 {
     transpose_cols(s, (int64_t)op->view.N, r, yt, y, false);
-}
-
-}  // namespace ige
-
-// ---------------------------------------------------------------------------
-// Near-field product for many columns on the FP64 matrix cores (16x16x4: lane l
-// supplies A[l%16][l/16] and B[l/16][l%16]; accumulator register j of lane l holds
-// D[l/16 + 4j][l%16]).  For a stored block B (target leaf t, source leaf s) and the
-// row chunk [r0, r0 + rc):
-//   DIR 0: Y_t[r0 + m][n] = sum_k B[r0 + m][k] X_s[k][n]            (rows of the chunk)
-//   DIR 1: Y_s[m][n]      = sum_{k < rc} B[r0 + k][m] X_t[r0 + k][n]  (off-diagonal blocks)
-// Complex products as four real ones: Yr += Br Xr - Bi Xi, Yi += Br Xi + Bi Xr.
-// A workgroup takes one (block, row chunk) and 16 NT columns; wave w owns the column
-// tile w % NT and every (4 / NT)-th row tile.  Results go to the partial-result slots
-// ([slot][r]) that the fixed-order per-unknown reduction sums.
-// ---------------------------------------------------------------------------
-namespace ige {
-namespace {
-
-typedef double dx4b __attribute__((ext_vector_type(4)));
-
-constexpr int kNearMfmaMaxK = 1024;   // reduction length staged in shared memory (slots per leaf)
-constexpr int kNearMfmaPD = 2;        // reduction steps loaded ahead of the products
-
-template <int DIR, int NT, int MTW>
-__global__ __launch_bounds__(256) void k_near_mfma(DevOp o, int r, const double2 *xt, double2 *part)
-{
-    __shared__ int32_t skd[kNearMfmaMaxK];   // unknown of every reduction index (-1: none)
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int nF = o.nF;
-    const int64_t b = blockIdx.x / o.nch;
-    const int ch = blockIdx.x % o.nch;
-    const int lt = o.bpair[2 * b], ls = o.bpair[2 * b + 1];
-    if (DIR == 1 && lt == ls) return;   // diagonal blocks: no transposed product
-    const int r0 = ch * o.rc, rc = min(o.rc, nF - r0);
-    const int c0 = blockIdx.y * 16 * NT;
-    const int M = DIR == 0 ? rc : nF, K = DIR == 0 ? nF : rc;
-    const int MT = (M + 15) / 16, KS = (K + 3) / 4;
-    const int nt = wv % NT, mstep = 4 / NT, mfirst = wv / NT;
-    const int n = c0 + 16 * nt + (lane & 15);   // this lane's column (B operand and output)
-    const bool nok = n < r;
-    const int nc = nok ? n : 0;
-    const double2 *Bv = o.bval + (size_t)b * nF * nF;
-    const int32_t *kdof = o.leafdof + (size_t)(DIR == 0 ? ls : lt) * nF + (DIR == 0 ? 0 : r0);
-    for (int i = threadIdx.x; i < K; i += blockDim.x) skd[i] = kdof[i];
-    __syncthreads();
-    dx4b accr[MTW], acci[MTW];
-#pragma unroll
-    for (int i = 0; i < MTW; ++i) {
-        accr[i] = dx4b{0.0, 0.0, 0.0, 0.0};
-        acci[i] = dx4b{0.0, 0.0, 0.0, 0.0};
-    }
-    // operands of reduction step s: every load from a clamped, valid address, zeroed
-    // where out of range (no branches around the loads, so they stay in flight)
-    auto load = [&](int s, double2 &xo, double2 (&ao)[MTW]) {
-        const int k = 4 * s + (lane >> 4);   // reduction index supplied by this lane
-        const int d = (k < K && nok) ? skd[min(k, K - 1)] : -1;
-        const double2 v = xt[(size_t)max(d, 0) * r + nc];
-        xo = d >= 0 ? v : make_double2(0.0, 0.0);
-        const int ka = min(k, K - 1);
-#pragma unroll
-        for (int i = 0; i < MTW; ++i) {
-            const int mt = mfirst + i * mstep;
-            if (mt < MT) {   // uniform over the wave
-                const int m = 16 * mt + (lane & 15), mc = min(m, M - 1);
-                const double2 av = DIR == 0 ? Bv[(size_t)(r0 + mc) * nF + ka] : Bv[(size_t)(r0 + ka) * nF + mc];
-                ao[i] = (m < M && k < K) ? av : make_double2(0.0, 0.0);
-            }
-        }
-    };
-    double2 xb[kNearMfmaPD], ab[kNearMfmaPD][MTW];
-#pragma unroll
-    for (int d = 0; d < kNearMfmaPD; ++d)
-        if (d < KS) load(d, xb[d], ab[d]);
-    for (int s0 = 0; s0 < KS; s0 += kNearMfmaPD) {
-#pragma unroll
-        for (int d = 0; d < kNearMfmaPD; ++d) {
-            const int s = s0 + d;
-            if (s < KS) {   // uniform
-                const double xr = xb[d].x, xi = xb[d].y;
-                double2 a[MTW];
-#pragma unroll
-                for (int i = 0; i < MTW; ++i) a[i] = ab[d][i];
-                if (s + kNearMfmaPD < KS) load(s + kNearMfmaPD, xb[d], ab[d]);
-#pragma unroll
-                for (int i = 0; i < MTW; ++i) {
-                    if (mfirst + i * mstep < MT) {   // uniform over the wave
-                        accr[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, xr, accr[i], 0, 0, 0);
-                        accr[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(-a[i].y, xi, accr[i], 0, 0, 0);
-                        acci[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].x, xi, acci[i], 0, 0, 0);
-                        acci[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[i].y, xr, acci[i], 0, 0, 0);
-                    }
-                }
-            }
-        }
-    }
-    if (!nok) return;
-#pragma unroll
-    for (int i = 0; i < MTW; ++i) {
-        const int mt = mfirst + i * mstep;
-        if (mt >= MT) break;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int m = 16 * mt + (lane >> 4) + 4 * j;
-            if (m >= M) continue;
-            const size_t slot = DIR == 0 ? (size_t)b * nF + r0 + m
-                                         : (size_t)o.nblk * nF + ((size_t)b * o.nch + ch) * nF + m;
-            part[slot * r + n] = make_double2(accr[i][j], acci[i][j]);
-        }
-    }
-}
-
-// yt[i][c] = sum of the partial results of unknown i, column c ([slot][r] layout),
-// 16 lanes per (unknown, column) with a fixed butterfly
-__global__ __launch_bounds__(256) void k_near_gather_r(int N, int r, const int64_t *ptr, const int32_t *idx,
-                                                       const double2 *part, double2 *yt)
-{
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    const int sub = (int)(t & 15);
-    const int64_t ic = t >> 4;
-    const int64_t i = ic / r;
-    const int c = (int)(ic % r);
-    double re = 0.0, im = 0.0;
-    if (i < N)
-        for (int64_t k = ptr[i] + sub; k < ptr[i + 1]; k += 16) {
-            const double2 v = part[(size_t)idx[k] * r + c];
-            re += v.x;
-            im += v.y;
-        }
-#pragma unroll
-    for (int off = 8; off >= 1; off >>= 1) {
-        re += __shfl_xor(re, off, 16);
-        im += __shfl_xor(im, off, 16);
-    }
-    if (i < N && sub == 0) yt[(size_t)i * r + c] = make_double2(re, im);
-}
-
-template <int DIR, int NT>
-void launch_near_mfma(ige_op op, int r, const double2 *xt, double2 *part, hipStream_t s)
-{
-    const DevOp &o = op->view;
-    const int M = DIR == 0 ? o.rc : o.nF;
-    const int MT = (M + 15) / 16, mstep = 4 / NT;
-    const int mtw = (MT + mstep - 1) / mstep;
-    const dim3 grid((unsigned)(o.nblk * o.nch), (unsigned)((r + 16 * NT - 1) / (16 * NT))), blk(256);
-#define IGE_NM_CASE(W)                                                                                   \
-    case W: hipLaunchKernelGGL((k_near_mfma<DIR, NT, W>), grid, blk, 0, s, o, r, xt, part); break;
-    switch (mtw) {
-        IGE_NM_CASE(1)
-        IGE_NM_CASE(2)
-        IGE_NM_CASE(3)
-        IGE_NM_CASE(4)
-        IGE_NM_CASE(6)
-        IGE_NM_CASE(8)
-        IGE_NM_CASE(12)
-        IGE_NM_CASE(16)
-        default: throw Status{IGE_EINVAL, "near-field block too large for the matrix-core product"};
-    }
-#undef IGE_NM_CASE
-    IGE_HIP(hipGetLastError());
-}
-
-}  // namespace
-
-int near_mfma_mtw_ok(int nF, int rc)
-{
-    if (nF > kNearMfmaMaxK) return 0;
-    for (int NT : {1, 2, 4})
-        for (int M : {rc, nF}) {
-            const int MT = (M + 15) / 16, ms = 4 / NT, w = (MT + ms - 1) / ms;
-            if (w > 16 || (w > 4 && w != 6 && w != 8 && w != 12 && w != 16)) return 0;
-        }
-    return 1;
-}
-
-void near_batched_mfma(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s)
-{
-    const DevOp &o = op->view;
-    const size_t need = (size_t)o.nblk * o.nF * (1 + o.nch) * r;
-    if (op->d_bnpart_r.n < need) op->d_bnpart_r.alloc(need);
-    double2 *part = op->d_bnpart_r.p;
-    const int NT = tune_get(op, kTuneNearMfmaNt, r, 0, r > 16 ? 2 : 1);
-    if (NT == 4) {
-        launch_near_mfma<0, 4>(op, r, xt, part, s);
-        launch_near_mfma<1, 4>(op, r, xt, part, s);
-    } else if (NT == 2) {
-        launch_near_mfma<0, 2>(op, r, xt, part, s);
-        launch_near_mfma<1, 2>(op, r, xt, part, s);
-    } else {
-        launch_near_mfma<0, 1>(op, r, xt, part, s);
-        launch_near_mfma<1, 1>(op, r, xt, part, s);
-    }
-    const int64_t tot = (int64_t)o.N * r * 16;
-    hipLaunchKernelGGL(k_near_gather_r, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, o.N, r, o.red_ptr,
-                       o.red_idx, part, yt);
-    IGE_HIP(hipGetLastError());
 }
 
 }  // namespace ige

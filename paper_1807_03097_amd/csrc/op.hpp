@@ -227,10 +227,13 @@ struct ige_op_s {
     ige::DBuf<float2> d_bmpart;          // matrix-core coupling partials [mwork][4][Q][r]
     ige::DBuf<double> d_Gd, d_vd;       // FP64 matrix-core coupling: blocks, right factors
     ige::DBuf<double2> d_bmpart64;      // FP64 matrix-core coupling partials [mwork][4][Q][r]
-    ige::DBuf<double> d_nd, d_xnd;      // FP64 matrix-core near field: ordered-pair blocks, gathered right factors
-    ige::DBuf<double2> d_ndpart;        // its partials [near work items][nF][r]
-    int nd_fit = -1;                    // those blocks fit in device memory (-1: not yet decided)
-    bool near_md_off = false;           // IGE_NEAR_F64=blocks: the unordered-block kernel instead
+    // FP64 near field of several columns: items of at most two partners (small operators),
+    // their launch order, per-unknown lists; partials [near work items][nF][r]
+    ige::DBuf<ige::M2LWork> d_nfwork;
+    ige::DBuf<int32_t> d_nforder, d_nfred_idx;
+    ige::DBuf<int64_t> d_nfred_ptr;
+    ige::DBuf<double2> d_ndpart;
+    bool near_blocks = false;           // IGE_NEAR_F64=blocks: the unordered-block kernel instead
     int gd_fit = -1;                    // FP64 blocks fit in device memory (-1: not yet decided)
     bool f64mx_off = false;             // FP64 coupling of many columns generated per apply (IGE_M2L_F64=generate)
     ige::DBuf<int32_t> d_morder;         // work items by decreasing partner count (per level with mxl)
@@ -266,7 +269,6 @@ struct ige_op_s {
     // batched-apply workspaces (r columns, column index innermost)
     int bcap = 0;
     ige::DBuf<double2> d_bnpart;       // near-field partial results [nslots][rb]
-    ige::DBuf<double2> d_bnpart_r;     // near-field partial results [nslots][r] (matrix-core product)
     ige::DBuf<double2> d_bmom, d_bsrc, d_bpart, d_bloc, d_bybuf, d_bxt, d_byt, d_bx, d_by;
     // GMRES workspace
     ige::DBuf<double2> d_V, d_w, d_r, d_X, d_F, d_D;
@@ -286,7 +288,7 @@ struct ige_op_s {
 namespace ige {
 
 // autotuned tile choices (ige_op_autotune); absent keys take the built-in default
-enum TuneKnob { kTuneM2lNcol = 0, kTuneNearBxNt = 1, kTuneNearMfmaNt = 2, kTuneM2lRb = 3, kTuneM2lDb = 4, kTuneM2lOrder = 5, kTuneM2lF64 = 6, kTuneKnobs = 7 };
+enum TuneKnob { kTuneM2lNcol = 0, kTuneNearBxNt = 1, kTuneUnused = 2, kTuneM2lRb = 3, kTuneM2lDb = 4, kTuneM2lOrder = 5, kTuneM2lF64 = 6, kTuneKnobs = 7 };
 inline long long tune_key(int knob, int r, int prec) { return ((long long)knob << 40) | ((long long)r << 8) | prec; }
 inline int tune_get(const ige_op_s *op, int knob, int r, int prec, int def)
 {
@@ -358,9 +360,9 @@ void plan_near_bf16(ige_op op, const std::vector<int32_t> &pair, const std::vect
 void ensure_near_bf16(ige_op op, hipStream_t s);
 int near_bf16_ok(int nF);
 void near_bf16(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
-// FP64 near field of r >= 56 columns on the FP64 matrix cores (ordered-pair FP64 blocks)
-bool near_f64mx_ok(ige_op op, int r);
-void near_f64mx(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
+// FP64 near field of several columns over ordered leaf pairs
+bool near_cols_use(const ige_op_s *op, int r);
+void near_cols(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
 void launch_m2l_reduce(ige_op op, int prec);
 // one FP64 column: work lists of the unordered-pair coupling (chunk partners per item,
 // 0: by rule), its launch and its reduction
@@ -371,7 +373,6 @@ void launch_l2l(ige_op op);
 // near-field product; records mid (if given) between the block pass and the reduction
 void launch_spmv(ige_op op, const double2 *x, double2 *y, hipStream_t st, hipEvent_t mid = nullptr);
 int near_blk_u(int nF);
-int near_mfma_mtw_ok(int nF, int rc);   // the FP64 matrix-core near product supports these blocks   // 64-column groups per block row (template choice)
 void launch_l2p_leaf(ige_op op);
 void launch_l2p_gather(ige_op op, double2 *y);
 // scattered field at npts points (device arrays; src: potential_source_doubles scratch; parts
