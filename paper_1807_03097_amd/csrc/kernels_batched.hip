@@ -547,10 +547,11 @@ __global__ void k_m2l_reduce_b(DevOp o, int r, const int32_t *wrk_of_tgt, const 
     for (int t = threadIdx.x; t < Q * r; t += blockDim.x) {
         const int mm = t / r, c = t % r;
         double2 u[4] = {make_double2(0, 0), make_double2(0, 0), make_double2(0, 0), make_double2(0, 0)};
-        for (int w = b; w < e; ++w)   // scalar: the fourth field alone
-#pragma unroll
-            for (int k = 0; k < 4; ++k)
-                if (k == 3 || !o.scalar) u[k] = caddb(u[k], to_d2(part[(((size_t)w * 4 + k) * Qs + mm) * r + c]));
+        if (o.scalar)   // the fourth field alone
+            for (int w = b; w < e; ++w) u[3] = caddb(u[3], to_d2(part[(((size_t)w * 4 + 3) * Qs + mm) * r + c]));
+        else
+            for (int w = b; w < e; ++w)
+                for (int k = 0; k < 4; ++k) u[k] = caddb(u[k], to_d2(part[(((size_t)w * 4 + k) * Qs + mm) * r + c]));
         const double *T = o.nodeT + (size_t)gc * 6 * Qs;
         double2 t1 = make_double2(0, 0), t2 = make_double2(0, 0);
         for (int k = 0; k < 3; ++k) {
