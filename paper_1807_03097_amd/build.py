@@ -8,7 +8,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libigaefie.so")
-SOURCES = ["setup.cpp", "api.cpp", "kernels.hip", "kernels_batched.hip", "fields.hip", "coupling.hip", "coupling_sym.hip", "coupling_gen.hip", "coupling_mfma.hip", "near_cols.hip", "krylov.hip", "near_bf16.hip", "near_once.hip", "probe.hip", "serve.cpp"]
+SOURCES = ["setup.cpp", "api.cpp", "kernels.hip", "assembly.hip", "kernels_batched.hip", "fields.hip", "coupling.hip", "coupling_sym.hip", "coupling_gen.hip", "coupling_mfma.hip", "near_cols.hip", "krylov.hip", "near_bf16.hip", "near_once.hip", "probe.hip", "serve.cpp"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -23,7 +23,7 @@ FLAGS = [
 # accumulation registers and copy them there and back around every loop (a loop of eight
 # 16x16x4 FP64 products: 47 TFLOP/s with the copies, 78 without).
 MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-FILE_FLAGS = {"coupling_sym.hip": MFMA_VGPR, "coupling_gen.hip": MFMA_VGPR, "near_cols.hip": MFMA_VGPR}
+FILE_FLAGS = {"assembly.hip": MFMA_VGPR, "coupling_sym.hip": MFMA_VGPR, "coupling_gen.hip": MFMA_VGPR, "near_cols.hip": MFMA_VGPR}
 
 
 # host-code sanitizer variants (the device code is compiled as usual): used by the CPU

@@ -462,6 +462,8 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             op->d_eC.alloc((size_t)E * 12);
             v.eX = op->d_eX.p; v.ePsi = op->d_ePsi.p; v.ePsiF = op->d_ePsiF.p; v.eC = op->d_eC.p;
             ige::launch_element_data(op);
+            op->d_sctab.upload(sincos_table(), s);
+            v.sctab = op->d_sctab.p;
             // near-field blocks and quadrature
             v.W = A.W; v.nF = A.nF; v.nch = A.nch; v.rc = A.rc; v.nblk = A.nblk();
             op->d_bpair.upload(A.pair, s);
@@ -560,8 +562,6 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             IGE_HIP(hipMemsetAsync(op->d_nodeX.p, 0, op->d_nodeX.bytes(), s));
             IGE_HIP(hipMemsetAsync(op->d_nodeT.p, 0, op->d_nodeT.bytes(), s));
             v.nodeX = op->d_nodeX.p; v.nodeT = op->d_nodeT.p;
-            op->d_sctab.upload(sincos_table(), s);
-            v.sctab = op->d_sctab.p;
             ige::launch_node_geometry(op);
             // M2L work items: partners of each target in chunks
             // partners per M2L work item (tuning knob IGE_M2L_CHUNK, default 8)

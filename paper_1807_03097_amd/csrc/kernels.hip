@@ -20,6 +20,7 @@
 #include <vector>
 
 #include "device_math.hpp"
+#include "element.hpp"
 #include "op.hpp"
 
 namespace ige {
@@ -27,333 +28,11 @@ namespace ige {
 namespace {
 
 constexpr int kWave = 64;
-typedef double dx4 __attribute__((ext_vector_type(4)));   // FP64 matrix-core accumulator
 
 __device__ inline double2 cmul(double2 a, double2 b) { return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x + b.x, a.y + b.y); }
 __device__ inline double2 cscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
 using dm::surf_elem;
-
-// Bernstein values and derivatives of degree deg <= kMaxP at x
-__device__ inline void bernstein(int deg, double x, double *B, double *D)
-{
-    double T[kMaxP + 1];
-    T[0] = 1.0;
-    for (int k = 1; k < deg; ++k) {
-        T[k] = x * T[k - 1];
-        for (int i = k - 1; i >= 1; --i) T[i] = (1.0 - x) * T[i] + x * T[i - 1];
-        T[0] = (1.0 - x) * T[0];
-    }
-    if (deg == 0) {
-        B[0] = 1.0;
-        D[0] = 0.0;
-        return;
-    }
-    for (int i = 0; i <= deg; ++i) {
-        const double lo = (i >= 1) ? T[i - 1] : 0.0;
-        const double hi = (i <= deg - 1) ? T[i] : 0.0;
-        D[i] = deg * (lo - hi);
-        B[i] = (1.0 - x) * hi + x * lo;
-    }
-}
-
-// 1-D spline pieces on element e at element-local x: degree p values/derivatives
-// (derivatives w.r.t. the patch parameter) and degree p-1 values
-__device__ inline void spline_pieces(const DevOp &o, int e, double x, double *Pv, double *Pd, double *Qv)
-{
-    const int p = o.p;
-    double B[kMaxP + 1], D[kMaxP + 1];
-    bernstein(p, x, B, D);
-    for (int t = 0; t <= p; ++t) {
-        double v = 0.0, d = 0.0;
-        const double *c = o.ext_p + ((size_t)e * (p + 1) + t) * (p + 1);
-        for (int a = 0; a <= p; ++a) {
-            v += c[a] * B[a];
-            d += c[a] * D[a];
-        }
-        Pv[t] = v;
-        Pd[t] = d / o.h;
-    }
-    double Bq[kMaxP + 1], Dq[kMaxP + 1];
-    bernstein(p - 1, x, Bq, Dq);
-    for (int t = 0; t < p; ++t) {
-        double v = 0.0;
-        const double *c = o.ext_q + ((size_t)e * p + t) * p;
-        for (int a = 0; a < p; ++a) v += c[a] * Bq[a];
-        Qv[t] = v;
-    }
-}
-
-// Fixed-degree variants (fully unrolled, no scratch): Bernstein values and
-// derivatives, spline pieces and rational Bezier patch evaluation.
-template <int DEG>
-__device__ inline void bernstein_t(double x, double *B, double *D)
-{
-    if constexpr (DEG == 0) {
-        B[0] = 1.0;
-        D[0] = 0.0;
-    } else {
-        double T[DEG];
-        T[0] = 1.0;
-#pragma unroll
-        for (int k = 1; k < DEG; ++k) {
-            T[k] = x * T[k - 1];
-#pragma unroll
-            for (int i = k - 1; i >= 1; --i) T[i] = (1.0 - x) * T[i] + x * T[i - 1];
-            T[0] = (1.0 - x) * T[0];
-        }
-#pragma unroll
-        for (int i = 0; i <= DEG; ++i) {
-            const double lo = (i >= 1) ? T[i >= 1 ? i - 1 : 0] : 0.0;
-            const double hi = (i <= DEG - 1) ? T[i <= DEG - 1 ? i : 0] : 0.0;
-            D[i] = DEG * (lo - hi);
-            B[i] = (1.0 - x) * hi + x * lo;
-        }
-    }
-}
-
-template <int P>
-__device__ inline void spline_pieces_t(const DevOp &o, int e, double x, double *Pv, double *Pd, double *Qv)
-{
-    double B[P + 1], D[P + 1];
-    bernstein_t<P>(x, B, D);
-#pragma unroll
-    for (int t = 0; t <= P; ++t) {
-        double v = 0.0, d = 0.0;
-        const double *c = o.ext_p + ((size_t)e * (P + 1) + t) * (P + 1);
-#pragma unroll
-        for (int a = 0; a <= P; ++a) {
-            v += c[a] * B[a];
-            d += c[a] * D[a];
-        }
-        Pv[t] = v;
-        Pd[t] = d / o.h;
-    }
-    double Bq[P], Dq[P];
-    bernstein_t<P - 1>(x, Bq, Dq);
-#pragma unroll
-    for (int t = 0; t < P; ++t) {
-        double v = 0.0;
-        const double *c = o.ext_q + ((size_t)e * P + t) * P;
-#pragma unroll
-        for (int a = 0; a < P; ++a) v += c[a] * Bq[a];
-        Qv[t] = v;
-    }
-}
-
-template <int PU, int PV>
-__device__ inline void bezier_eval_t(const GeomView &g, const PatchHdr &h, double u, double v, double X[3],
-                                     double Xu[3], double Xv[3])
-{
-    int su = 0, sv = 0;
-    while (su < h.su - 1 && u >= g.brk[h.brk_u + su + 1]) ++su;
-    while (sv < h.sv - 1 && v >= g.brk[h.brk_v + sv + 1]) ++sv;
-    const double ua = g.brk[h.brk_u + su], ub = g.brk[h.brk_u + su + 1];
-    const double va = g.brk[h.brk_v + sv], vb = g.brk[h.brk_v + sv + 1];
-    const double t = (u - ua) / (ub - ua), s = (v - va) / (vb - va);
-    double Bu[PU + 1], Du[PU + 1], Bv[PV + 1], Dv[PV + 1];
-    bernstein_t<PU>(t, Bu, Du);
-    bernstein_t<PV>(s, Bv, Dv);
-    const double *c = g.cp + h.cp + (size_t)(sv * h.su + su) * (PV + 1) * (PU + 1) * 4;
-    double A[4] = {0, 0, 0, 0}, Au[4] = {0, 0, 0, 0}, Av[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j2 = 0; j2 <= PV; ++j2)
-#pragma unroll
-        for (int j1 = 0; j1 <= PU; ++j1) {
-            const double *Pc = c + (j2 * (PU + 1) + j1) * 4;
-            const double b = Bu[j1] * Bv[j2], bu = Du[j1] * Bv[j2], bv = Bu[j1] * Dv[j2];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                A[k] += b * Pc[k];
-                Au[k] += bu * Pc[k];
-                Av[k] += bv * Pc[k];
-            }
-        }
-    const double iw = 1.0 / A[3], du = 1.0 / (ub - ua), dv = 1.0 / (vb - va);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        X[k] = A[k] * iw;
-        Xu[k] = (Au[k] - X[k] * Au[3]) * iw * du;
-        Xv[k] = (Av[k] - X[k] * Av[3]) * iw * dv;
-    }
-}
-
-// other degrees: out of line, so that its stack arrays do not enlarge the callers
-__device__ __noinline__ void geom_eval_generic(const GeomView &g, int j, double u, double v, double X[3], double Xu[3],
-                                               double Xv[3])
-{
-    bezier_eval(g, j, u, v, X, Xu, Xv);
-}
-
-// patch evaluation with unrolled paths for bilinear and biquadratic patches
-__device__ inline void geom_eval(const GeomView &g, int j, double u, double v, double X[3], double Xu[3], double Xv[3])
-{
-    const PatchHdr h = g.hdr[j];
-    if (h.pu == 2 && h.pv == 2) bezier_eval_t<2, 2>(g, h, u, v, X, Xu, Xv);
-    else if (h.pu == 1 && h.pv == 1) bezier_eval_t<1, 1>(g, h, u, v, X, Xu, Xv);
-    else geom_eval_generic(g, j, u, v, X, Xu, Xv);
-}
-
-// local function l of an element: (component, t1, t2); the scalar operator has the
-// (p+1)^2 tensor B-splines, t2 major, in component 0
-__device__ inline void local_index(const DevOp &o, int l, int &a, int &t1, int &t2)
-{
-    const int p = o.p;
-    if (o.scalar) {
-        a = 0;
-        t2 = l / (p + 1);
-        t1 = l % (p + 1);
-        return;
-    }
-    const int n0 = p * (p + 1);
-    if (l < n0) {
-        a = 0;
-        t2 = l / (p + 1);
-        t1 = l % (p + 1);
-    } else {
-        a = 1;
-        const int r = l - n0;
-        t2 = r / p;
-        t1 = r % p;
-    }
-}
-
-// values of the local functions at element-local (x, y): Phi (3) and div, unsigned
-// (scalar operator: Phi = 0 and the value times the surface element in place of div)
-template <int NL>
-__device__ inline void local_values(const DevOp &o, int e1, int e2, double x, double y, const double Fu[3],
-                                    const double Fv[3], double Phi[NL][3], double Dv[NL])
-{
-    double Pu[kMaxP + 1], dPu[kMaxP + 1], Qu[kMaxP + 1], Pv[kMaxP + 1], dPv[kMaxP + 1], Qv[kMaxP + 1];
-    spline_pieces(o, e1, x, Pu, dPu, Qu);
-    spline_pieces(o, e2, y, Pv, dPv, Qv);
-    if (o.scalar) {   // value times the surface element, no field part
-        const double J = surf_elem(Fu, Fv);
-#pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            int a, t1, t2;
-            local_index(o, l, a, t1, t2);
-            Phi[l][0] = Phi[l][1] = Phi[l][2] = 0.0;
-            Dv[l] = Pu[t1] * Pv[t2] * J;
-        }
-        return;
-    }
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        int a, t1, t2;
-        local_index(o, l, a, t1, t2);
-        double val, div;
-        if (a == 0) {
-            val = Pu[t1] * Qv[t2];
-            div = dPu[t1] * Qv[t2];
-        } else {
-            val = Qu[t1] * Pv[t2];
-            div = Qu[t1] * dPv[t2];
-        }
-        const double *F = (a == 0) ? Fu : Fv;
-        Phi[l][0] = val * F[0];
-        Phi[l][1] = val * F[1];
-        Phi[l][2] = val * F[2];
-        Dv[l] = div;
-    }
-}
-
-// The same values written straight to a row of shared memory: (Phi_l, cdiv * div_l).
-template <int NL>
-__device__ inline void local_values_lds(const DevOp &o, int e1, int e2, double x, double y, const double Fu[3],
-                                        const double Fv[3], double cdiv, double (*dst)[4])
-{
-    double Pu[kMaxP + 1], dPu[kMaxP + 1], Qu[kMaxP + 1], Pv[kMaxP + 1], dPv[kMaxP + 1], Qv[kMaxP + 1];
-    spline_pieces(o, e1, x, Pu, dPu, Qu);
-    spline_pieces(o, e2, y, Pv, dPv, Qv);
-    if (o.scalar) {
-        const double J = surf_elem(Fu, Fv);
-#pragma unroll
-        for (int l = 0; l < NL; ++l) {
-            int a, t1, t2;
-            local_index(o, l, a, t1, t2);
-            dst[l][0] = dst[l][1] = dst[l][2] = 0.0;
-            dst[l][3] = cdiv * Pu[t1] * Pv[t2] * J;
-        }
-        return;
-    }
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        int a, t1, t2;
-        local_index(o, l, a, t1, t2);
-        double val, div;
-        if (a == 0) {
-            val = Pu[t1] * Qv[t2];
-            div = dPu[t1] * Qv[t2];
-        } else {
-            val = Qu[t1] * Pv[t2];
-            div = Qu[t1] * dPv[t2];
-        }
-        const double *F = (a == 0) ? Fu : Fv;
-        dst[l][0] = val * F[0];
-        dst[l][1] = val * F[1];
-        dst[l][2] = val * F[2];
-        dst[l][3] = cdiv * div;
-    }
-}
-
-// (Phi_l, cdiv * div_l) for the NL = 2P(P+1) local functions, into rows of shared memory
-template <int P, bool SC = false>
-__device__ inline void local_values_lds_t(const DevOp &o, int e1, int e2, double x, double y, const double Fu[3],
-                                          const double Fv[3], double cdiv, double (*dst)[4])
-{
-    constexpr int NL = 2 * P * (P + 1);
-    double Pu[P + 1], dPu[P + 1], Qu[P], Pv[P + 1], dPv[P + 1], Qv[P];
-    spline_pieces_t<P>(o, e1, x, Pu, dPu, Qu);
-    spline_pieces_t<P>(o, e2, y, Pv, dPv, Qv);
-    if constexpr (SC) {   // scalar: (p+1)^2 tensor B-splines, value times |J| in slot 3
-        const double J = surf_elem(Fu, Fv);
-#pragma unroll
-        for (int l = 0; l < (P + 1) * (P + 1); ++l) {
-            dst[l][0] = dst[l][1] = dst[l][2] = 0.0;
-            dst[l][3] = cdiv * Pu[l % (P + 1)] * Pv[l / (P + 1)] * J;
-        }
-        return;
-    }
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        const bool a0 = l < P * (P + 1);
-        const int r = a0 ? l : l - P * (P + 1);
-        const int t2 = a0 ? r / (P + 1) : r / P, t1 = a0 ? r % (P + 1) : r % P;
-        const double val = a0 ? Pu[t1] * Qv[t2] : Qu[t1] * Pv[t2];
-        const double div = a0 ? dPu[t1] * Qv[t2] : Qu[t1] * dPv[t2];
-        const double *F = a0 ? Fu : Fv;
-        dst[l][0] = val * F[0];
-        dst[l][1] = val * F[1];
-        dst[l][2] = val * F[2];
-        dst[l][3] = cdiv * div;
-    }
-}
-
-__device__ inline void elem_of(const DevOp &o, int64_t e, int &j, int &e1, int &e2)
-{
-    const int nn = o.n * o.n;
-    j = (int)(e / nn);
-    const int r = (int)(e % nn);
-    e2 = r / o.n;
-    e1 = r % o.n;
-}
-
-__device__ inline void local_dof(const DevOp &o, int j, int e1, int e2, int l, int &idx, double &sg)
-{
-    int a, t1, t2;
-    local_index(o, l, a, t1, t2);
-    const size_t off = (((size_t)j * 2 + a) * o.nb + (e2 + t2)) * o.nb + (e1 + t1);
-    idx = o.dof[off];
-    sg = (double)o.sgn[off];
-}
-
-// FP64 matrix-core instruction 16x16x4: lane l supplies A[l % 16][l / 16] and
-// B[l / 16][l % 16]; accumulator register j of lane l holds D[l / 16 + 4 j][l % 16].
-// Operand order: for step t a lane supplies the entry with quadrature index
-// q = frag_q(t, lane) in reduction slot lane / 16, so that accumulator register j of
-// a first product over tile qt is the operand of step t = 4 qt + j of a second.
-__device__ inline int frag_q(int t, int lane) { return 16 * (t >> 2) + 4 * (t & 3) + (lane >> 4); }
 
 // ---------------------------------------------------------------------------
 // a0: element data at the regular Gauss points
@@ -422,440 +101,6 @@ __global__ void k_node_geometry(DevOp o, int NC, double *nodeX, double *nodeT)
         nodeT[((size_t)gc * 6 + d) * o.Q + mm] = Fu[d];
         nodeT[((size_t)gc * 6 + 3 + d) * o.Q + mm] = Fv[d];
     }
-}
-
-__device__ inline bool share_corner(const DevOp &o, int64_t e, int64_t f)
-{
-    const double *A = o.eC + e * 12, *B = o.eC + f * 12;
-    for (int x = 0; x < 4; ++x)
-        for (int y = 0; y < 4; ++y) {
-            const double d0 = A[3 * x] - B[3 * y], d1 = A[3 * x + 1] - B[3 * y + 1], d2 = A[3 * x + 2] - B[3 * y + 2];
-            if (sqrt(d0 * d0 + d1 * d1 + d2 * d2) <= o.scale_tol) return true;
-        }
-    return false;
-}
-
-// row tiles of test functions per workgroup of k_near_regular: all up to 24 local
-// functions, one 16-row tile for more (p = 4: 40 functions, three workgroups)
-constexpr int near_regular_lr(int nl) { return nl <= 24 ? (nl + 15) / 16 : 1; }
-
-// ---------------------------------------------------------------------------
-// a1: regular element pairs (no shared corner).  With S = (1, 1, 1, -kappa^-2) and
-// the weights folded into Psi,
-//   B[l][l'] = sum_c S_c sum_q Psi_e^c[l][q] sum_q' K(q, q') Psi_f^c[l'][q'],
-// computed as two products on the FP64 matrix cores per trial element f:
-//   Y_c(q', l) = sum_q K(q, q') Psi_e^c[l][q]      (K as operand A, Psi_e as B)
-//   B(l, l') += sum_q' Y_c(q', l) Psi_f^c[l'][q']  (Y from the accumulators as A)
-// The accumulator layout of the first product (row lane/16 + 4 j) is the operand
-// layout of the second when its reduction slots are ordered by frag_q.
-// A workgroup takes one block, one test element e of the target leaf and a square
-// of sb x sb trial elements of the source leaf.  The four waves take the trial
-// elements four at a time; their element-pair blocks are added to the block rows of
-// e in shared memory one wave after the other (trial elements in ascending order),
-// then the element pairs of e that share a corner with a trial element of the square
-// (computed before by k_near_singular) in list order.  Every sum therefore has a
-// fixed order.
-// Launched once per colour: the test elements of a launch are p + 1 apart in both
-// directions (no glued function in common, so no block row in common), and with
-// several trial squares per leaf the squares of a launch are two apart (sb >= p: no
-// column in common).  Each block entry thus has at most one writer per launch, and
-// the launches run in a fixed order on one stream: the assembled blocks are the same
-// bits on every run.
-// ---------------------------------------------------------------------------
-template <int NL, int QT, int LR>
-__device__ __forceinline__ void near_regular_body(const DevOp &o, int sb, int ce1, int ce2, int cs1, int cs2, int sstep)
-{
-    // LR of the LT 16-row tiles of test functions per workgroup (LR = LT: all rows;
-    // otherwise the rows are split over LT / LR workgroups, for the larger degrees)
-    constexpr int LT = (NL + 15) / 16, T = 4 * QT, NRT = LT / LR;
-    constexpr int NR = LR == LT ? NL : 16 * LR;       // test-function rows of this workgroup
-    extern __shared__ double2 sacc[];                 // [NR][2 Wsb^2], then [4][NR][NL] staging
-    __shared__ double sXe[3][16 * QT];                // test element points (zero padded)
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int s = o.s, nsb = s / sb, Wsb = sb + o.p, nslot = 2 * Wsb * Wsb, P1 = o.p + 1;
-    double2 *sstage = sacc + NR * nslot;
-    // test elements and trial squares of this colour
-    const int n1 = (s - ce1 + P1 - 1) / P1, n2 = (s - ce2 + P1 - 1) / P1;
-    const int m1 = (nsb - cs1 + sstep - 1) / sstep, m2 = (nsb - cs2 + sstep - 1) / sstep;
-    int64_t blk = blockIdx.x;
-    const int u0 = LR * (int)(blk % NRT);             // first row tile
-    blk /= NRT;
-    const int l0 = 16 * u0;                           // first test function
-    const int sub = (int)(blk % (m1 * m2));
-    blk /= m1 * m2;
-    const int tc = (int)(blk % (n1 * n2));
-    const int64_t b = blk / (n1 * n2);
-    const int lt = o.bpair[2 * b], ls = o.bpair[2 * b + 1];
-    const int SL = o.SL;
-    const int jt = lt / (SL * SL), jr = lt % (SL * SL), js = ls / (SL * SL), jsr = ls % (SL * SL);
-    const int tl1 = ce1 + P1 * (tc % n1), tl2 = ce2 + P1 * (tc / n1);   // e inside its leaf
-    const int ti = tl2 * s + tl1;
-    const int te1 = (jr % SL) * s + tl1, te2 = (jr / SL) * s + tl2;
-    const int sl1 = (cs1 + sstep * (sub % m1)) * sb, sl2 = (cs2 + sstep * (sub / m1)) * sb;   // trial square
-    const int fx0 = (jsr % SL) * s + sl1, fy0 = (jsr / SL) * s + sl2;
-    const int64_t e = ((int64_t)jt * o.n + te2) * o.n + te1;
-    const int G2 = o.G2;
-    for (int i = threadIdx.x; i < NR * nslot; i += blockDim.x) sacc[i] = make_double2(0.0, 0.0);
-    for (int i = threadIdx.x; i < 3 * 16 * QT; i += blockDim.x) {
-        const int d = i / (16 * QT), q = i % (16 * QT);
-        sXe[d][q] = q < G2 ? o.eX[(e * 3 + d) * G2 + q] : 0.0;
-    }
-    constexpr size_t FE = (size_t)4 * LT * T * 64;
-    double pa[4][LR][T];
-    {
-        const double *Fe = o.ePsiF + (size_t)e * FE;
-#pragma unroll
-        for (int c = 0; c < 4; ++c)
-#pragma unroll
-            for (int u = 0; u < LR; ++u)
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-                    pa[c][u][t] = Fe[((c * LT + u0 + u) * T + t) * 64 + lane] * (c == 3 ? o.cdiv : 1.0);
-    }
-    __syncthreads();
-    const int nfe = sb * sb, nround = (nfe + 3) / 4;
-    for (int rd = 0; rd < nround; ++rd) {
-        const int fi = 4 * rd + wv;
-        const int fe1 = fx0 + fi % sb, fe2 = fy0 + fi / sb;
-        const int64_t f = ((int64_t)js * o.n + fe2) * o.n + fe1;
-        // wave-uniform: trial element exists and shares no corner with e (those pairs
-        // come from the singular kernel)
-        const bool act = fi < nfe && !share_corner(o, e, f);
-        dx4 br[LR][LT], bi[LR][LT];
-        if (act) {
-#pragma unroll
-            for (int u = 0; u < LR; ++u)
-#pragma unroll
-                for (int v = 0; v < LT; ++v) {
-                    br[u][v] = dx4{0.0, 0.0, 0.0, 0.0};
-                    bi[u][v] = dx4{0.0, 0.0, 0.0, 0.0};
-                }
-            // kernel values as operand A: row q' = 16 qt + lane % 16, slot q = frag_q(t, lane)
-            double kre[QT][T], kim[QT][T];
-#pragma unroll
-            for (int qt = 0; qt < QT; ++qt) {
-                const int qb = 16 * qt + (lane & 15);
-                const bool okb = qb < G2;
-                double xb0 = 0.0, xb1 = 0.0, xb2 = 0.0;
-                if (okb) {
-                    xb0 = o.eX[(f * 3 + 0) * G2 + qb];
-                    xb1 = o.eX[(f * 3 + 1) * G2 + qb];
-                    xb2 = o.eX[(f * 3 + 2) * G2 + qb];
-                }
-#pragma unroll
-                for (int t = 0; t < T; ++t) {
-                    const int qa = frag_q(t, lane);
-                    double2 K = make_double2(0.0, 0.0);
-                    if (okb && qa < G2) {
-                        const double d0 = sXe[0][qa] - xb0, d1 = sXe[1][qa] - xb1, d2 = sXe[2][qa] - xb2;
-                        K = dm::helmholtz_r2(o.kappa, fma(d0, d0, fma(d1, d1, d2 * d2)));
-                    }
-                    kre[qt][t] = K.x;
-                    kim[qt][t] = K.y;
-                }
-            }
-            const double *Ff = o.ePsiF + (size_t)f * FE;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                dx4 yr[QT][LR], yi[QT][LR];
-#pragma unroll
-                for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                    for (int u = 0; u < LR; ++u) {
-                        yr[qt][u] = dx4{0.0, 0.0, 0.0, 0.0};
-                        yi[qt][u] = dx4{0.0, 0.0, 0.0, 0.0};
-                    }
-#pragma unroll
-                for (int t = 0; t < T; ++t)
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                        for (int u = 0; u < LR; ++u) {
-                            yr[qt][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(kre[qt][t], pa[c][u][t], yr[qt][u], 0, 0, 0);
-                            yi[qt][u] = __builtin_amdgcn_mfma_f64_16x16x4f64(kim[qt][t], pa[c][u][t], yi[qt][u], 0, 0, 0);
-                        }
-#pragma unroll
-                for (int v = 0; v < LT; ++v)
-#pragma unroll
-                    for (int qt = 0; qt < QT; ++qt)
-#pragma unroll
-                        for (int j = 0; j < 4; ++j) {
-                            const double pb = Ff[((c * LT + v) * T + 4 * qt + j) * 64 + lane];
-#pragma unroll
-                            for (int u = 0; u < LR; ++u) {
-                                br[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(yr[qt][u][j], pb, br[u][v], 0, 0, 0);
-                                bi[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(yi[qt][u][j], pb, bi[u][v], 0, 0, 0);
-                            }
-                        }
-            }
-        }
-        // rows l = 16 u + lane / 16 + 4 j, columns l' = 16 v + lane % 16 into this wave's
-        // staging block, then the four staged blocks are added in wave order
-        double2 *stg = sstage + (size_t)wv * NR * NL;
-        if (act) {
-#pragma unroll
-            for (int v = 0; v < LT; ++v) {
-                const int lb = 16 * v + (lane & 15);
-#pragma unroll
-                for (int u = 0; u < LR; ++u)
-#pragma unroll
-                    for (int j = 0; j < 4; ++j) {
-                        const int lr = 16 * u + (lane >> 4) + 4 * j;   // row of this workgroup
-                        if (l0 + lr < NL && lb < NL) stg[lr * NL + lb] = make_double2(br[u][v][j], bi[u][v][j]);
-                    }
-            }
-        }
-        __syncthreads();
-        for (int w = 0; w < 4; ++w) {
-            const int fw = 4 * rd + w;
-            // uniform over the workgroup: whether wave w computed a pair this round
-            const bool aw = fw < nfe && !share_corner(o, e, ((int64_t)js * o.n + fy0 + fw / sb) * o.n + fx0 + fw % sb);
-            if (aw) {
-                const int q1 = fw % sb, q2 = fw / sb;
-                const double2 *sw = sstage + (size_t)w * NR * NL;
-                for (int i = threadIdx.x; i < NR * NL; i += blockDim.x) {
-                    const int l = i / NL, lb = i % NL;
-                    if (l0 + l >= NL) continue;
-                    int a, t1, t2;
-                    local_index(o, lb, a, t1, t2);
-                    const int slot = a * Wsb * Wsb + (q2 + t2) * Wsb + (q1 + t1);
-                    const double2 v = sw[i];
-                    double2 &acc = sacc[l * nslot + slot];
-                    acc.x += v.x;
-                    acc.y += v.y;
-                }
-            }
-            __syncthreads();
-        }
-    }
-    // element pairs of e with a shared corner whose trial element lies in the square
-    const int kb = o.sing_ptr[b * (int64_t)(s * s) + ti], ke = o.sing_ptr[b * (int64_t)(s * s) + ti + 1];
-    for (int k = kb; k < ke; ++k) {
-        const int64_t f = o.sing[k].f;
-        int jf, f1, f2;
-        elem_of(o, f, jf, f1, f2);
-        const int q1 = f1 - fx0, q2 = f2 - fy0;
-        if (q1 < 0 || q1 >= sb || q2 < 0 || q2 >= sb) continue;   // uniform over the workgroup
-        const double2 *P = o.sblk + (size_t)k * NL * NL + (size_t)l0 * NL;
-        for (int i = threadIdx.x; i < NR * NL; i += blockDim.x) {
-            const int l = i / NL, lb = i % NL;
-            if (l0 + l >= NL) continue;
-            int a, t1, t2;
-            local_index(o, lb, a, t1, t2);
-            const int slot = a * Wsb * Wsb + (q2 + t2) * Wsb + (q1 + t1);
-            const double2 v = P[i];
-            double2 &acc = sacc[l * nslot + slot];
-            acc.x += v.x;
-            acc.y += v.y;
-        }
-        __syncthreads();
-    }
-    const int W = o.W, nF = o.nF;
-    for (int i = threadIdx.x; i < NR * nslot; i += blockDim.x) {
-        const double2 v = sacc[i];
-        if (v.x == 0.0 && v.y == 0.0) continue;
-        const int l = l0 + i / nslot, sl = i % nslot;
-        if (l >= NL) continue;
-        const int a = sl / (Wsb * Wsb), r = sl % (Wsb * Wsb);
-        const int i1 = sl1 + r % Wsb, i2 = sl2 + r / Wsb;
-        if (i1 >= (a == 0 ? W : W - 1) || i2 >= ((a == 0 && !o.scalar) ? W - 1 : W)) {
-            atomicAdd(o.err, 1);
-            continue;
-        }
-        const int kc = leaf_slot(W, a, i1, i2);
-        int ar, t1, t2;
-        local_index(o, l, ar, t1, t2);
-        const int kr = leaf_slot(W, ar, tl1 + t1, tl2 + t2);
-        // signs of the glued unknowns folded in; slots without an unknown are skipped
-        const double sg = (double)o.leafsgn[(size_t)lt * nF + kr] * (double)o.leafsgn[(size_t)ls * nF + kc];
-        if (sg == 0.0) continue;
-        double2 *dst = o.bval + ((size_t)b * nF + kr) * nF + kc;   // the only writer in this launch
-        double2 cur = *dst;
-        cur.x += sg * v.x;
-        cur.y += sg * v.y;
-        *dst = cur;
-    }
-}
-
-// the small rules (one or two 16-point tiles, up to 12 local functions) fit two
-// workgroups per CU without spilling; the others take all registers of one
-template <int NL, int QT>
-__global__ __launch_bounds__(256) void k_near_regular(DevOp o, int sb, int ce1, int ce2, int cs1, int cs2, int sstep)
-{
-    near_regular_body<NL, QT, near_regular_lr(NL)>(o, sb, ce1, ce2, cs1, cs2, sstep);
-}
-template <int NL, int QT>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_near_regular_o2(DevOp o, int sb, int ce1,
-                                                                                                   int ce2, int cs1, int cs2,
-                                                                                                   int sstep)
-{
-    near_regular_body<NL, QT, near_regular_lr(NL)>(o, sb, ce1, ce2, cs1, cs2, sstep);
-}
-
-// ---------------------------------------------------------------------------
-// a1: element pairs sharing a corner (relative-coordinate / Duffy sub-rules),
-// one wavefront per pair; each pair's NL x NL block is written to its own slot of a
-// scratch array (no accumulation here).
-// ---------------------------------------------------------------------------
-__device__ inline void frame_map(int code, double c1, double c2, double &x, double &y)
-{
-    const int o1 = code & 1, o2 = (code >> 1) & 1, sw = (code >> 2) & 1;
-    const double du = o1 ? -1.0 : 1.0, dv = o2 ? -1.0 : 1.0;
-    if (!sw) {
-        x = o1 + du * c1;
-        y = o2 + dv * c2;
-    } else {
-        x = o1 + du * c2;
-        y = o2 + dv * c1;
-    }
-}
-
-// canonical point (s1, s2) on the test element, (t1, t2) on the trial element and
-// weight of sub-rule point idx
-__device__ inline void singular_point(const DevOp &o, int kind, int idx, double &s1, double &s2, double &t1,
-                                      double &t2, double &wt)
-{
-    const int gs = o.gs, g4 = gs * gs * gs * gs;
-    const int sub = idx / g4;
-    int r = idx % g4;
-    const int id = r % gs; r /= gs;
-    const int ic = r % gs; r /= gs;
-    const int ib = r % gs; r /= gs;
-    const int ia = r;
-    const double xi = o.sx[ia], y1 = o.sx[ib], y2 = o.sx[ic], y3 = o.sx[id];
-    const double w4 = o.sw[ia] * o.sw[ib] * o.sw[ic] * o.sw[id];
-    if (kind == 1) {
-        // identical: per direction |x_k - y_k| = w_k with both orders; (w1, w2) triangle split
-        const int tri = sub >> 2, sg1 = (sub >> 1) & 1, sg2 = sub & 1;
-        const double w1 = tri == 0 ? xi : xi * y1;
-        const double w2 = tri == 0 ? xi * y1 : xi;
-        if (!sg1) { s1 = (1.0 - w1) * y2; t1 = s1 + w1; } else { t1 = (1.0 - w1) * y2; s1 = t1 + w1; }
-        if (!sg2) { s2 = (1.0 - w2) * y3; t2 = s2 + w2; } else { t2 = (1.0 - w2) * y3; s2 = t2 + w2; }
-        wt = w4 * xi * (1.0 - w1) * (1.0 - w2);
-    } else if (kind == 2) {
-        // common edge at s1 = t1 = 0: distances A, B to the edge and W = |s2 - t2|
-        const int pyr = sub >> 1, sg = sub & 1;
-        double A, B, W;
-        if (pyr == 0) { A = xi; B = xi * y1; W = xi * y2; }
-        else if (pyr == 1) { B = xi; A = xi * y1; W = xi * y2; }
-        else { W = xi; A = xi * y1; B = xi * y2; }
-        double a2, b2;
-        if (!sg) { a2 = (1.0 - W) * y3; b2 = a2 + W; } else { b2 = (1.0 - W) * y3; a2 = b2 + W; }
-        s1 = A; s2 = a2; t1 = B; t2 = b2;
-        wt = w4 * xi * xi * (1.0 - W);
-    } else {
-        // common vertex at the origin of both: the largest of the four coordinates is xi
-        double z[4];
-        const double rest[3] = {xi * y1, xi * y2, xi * y3};
-        int k = 0;
-        for (int i = 0; i < 4; ++i) z[i] = (i == sub) ? xi : rest[k++];
-        s1 = z[0]; s2 = z[1]; t1 = z[2]; t2 = z[3];
-        wt = w4 * xi * xi * xi;
-    }
-}
-
-// Singular pairs: one wave per pair.  The points of the sub-rules are processed in
-// batches of 32: the lower half-wave evaluates geometry and local values on the
-// test element, the upper half on the trial element, into shared memory; then
-//   B[l][l'] += sum_q K_q sum_c Psi_a[q][l][c] Psi_b[q][l'][c]
-// runs on the FP64 matrix cores with the four components c as the reduction slots
-// of one instruction per point (K_q = weight * kernel folded into the test side).
-template <int P, bool SC = false>
-__global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPair *list)
-{
-    // points per batch: 32 (16 for p = 4, whose 40 local functions would not fit);
-    // SC: the scalar operator's (p+1)^2 local functions
-    constexpr int NL = SC ? (P + 1) * (P + 1) : 2 * P * (P + 1), LT = (NL + 15) / 16;
-    constexpr int NB = (SC ? 2 * P * (P + 1) : NL) > 24 ? 16 : 32;
-    __shared__ double sPa[NB][NL][4];
-    __shared__ double sPb[NB][NL][4];
-    __shared__ double2 sK[NB];
-    __shared__ double sX[NB][3];
-    const SingularPair sp = list[blockIdx.x];
-    const int lane = threadIdx.x, half = lane >> 5, qi = lane & 31;
-    int ja, a1, a2, jb, b1, b2;
-    elem_of(o, sp.e, ja, a1, a2);
-    elem_of(o, sp.f, jb, b1, b2);
-    const int gs = o.gs, g4 = gs * gs * gs * gs;
-    const int nsub = sp.kind == 1 ? 8 : (sp.kind == 2 ? 6 : 4);
-    const int npts = nsub * g4;
-    const double h4 = o.h * o.h * o.h * o.h;
-    dx4 br[LT][LT], bi[LT][LT];
-#pragma unroll
-    for (int u = 0; u < LT; ++u)
-#pragma unroll
-        for (int v = 0; v < LT; ++v) {
-            br[u][v] = dx4{0.0, 0.0, 0.0, 0.0};
-            bi[u][v] = dx4{0.0, 0.0, 0.0, 0.0};
-        }
-    const int c = lane >> 4, m = lane & 15;
-    for (int p0 = 0; p0 < npts; p0 += NB) {
-        const int pt = p0 + qi;
-        double X[3] = {0.0, 0.0, 0.0}, wt = 0.0;
-        __syncthreads();   // the previous batch has been consumed
-        if (pt < npts && qi < NB) {
-            double s1, s2, t1, t2;
-            singular_point(o, sp.kind, pt, s1, s2, t1, t2, wt);
-            double xa, ya, xb, yb;
-            if (sp.kind == 1) {
-                xa = s1; ya = s2; xb = t1; yb = t2;
-            } else {
-                frame_map(sp.fa, s1, s2, xa, ya);
-                frame_map(sp.fb, t1, t2, xb, yb);
-            }
-            double Fu[3], Fv[3];
-            if (half == 0) {
-                geom_eval(o.geo, ja, (a1 + xa) * o.h, (a2 + ya) * o.h, X, Fu, Fv);
-                local_values_lds_t<P, SC>(o, a1, a2, xa, ya, Fu, Fv, o.cdiv, sPa[qi]);
-            } else {
-                geom_eval(o.geo, jb, (b1 + xb) * o.h, (b2 + yb) * o.h, X, Fu, Fv);
-                local_values_lds_t<P, SC>(o, b1, b2, xb, yb, Fu, Fv, 1.0, sPb[qi]);
-                sX[qi][0] = X[0];
-                sX[qi][1] = X[1];
-                sX[qi][2] = X[2];
-            }
-        }
-        __syncthreads();
-        if (half == 0 && qi < NB) {
-            double2 K = make_double2(0.0, 0.0);
-            if (pt < npts) {
-                const double d0 = X[0] - sX[qi][0], d1 = X[1] - sX[qi][1], d2 = X[2] - sX[qi][2];
-                K = cscale(wt * h4, dm::helmholtz_r2(o.kappa, fma(d0, d0, fma(d1, d1, d2 * d2))));
-            }
-            sK[qi] = K;
-        }
-        __syncthreads();
-        const int nb = min(NB, npts - p0);
-        for (int q = 0; q < nb; ++q) {
-            const double2 K = sK[q];
-            double av[LT], bv[LT];
-#pragma unroll
-            for (int u = 0; u < LT; ++u) {
-                const int l = 16 * u + m;
-                av[u] = l < NL ? sPa[q][l][c] : 0.0;
-                bv[u] = l < NL ? sPb[q][l][c] : 0.0;
-            }
-#pragma unroll
-            for (int u = 0; u < LT; ++u)
-#pragma unroll
-                for (int v = 0; v < LT; ++v) {
-                    br[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(K.x * av[u], bv[v], br[u][v], 0, 0, 0);
-                    bi[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(K.y * av[u], bv[v], bi[u][v], 0, 0, 0);
-                }
-        }
-    }
-    // lane holds B[16 u + lane/16 + 4 j][16 v + lane % 16]; the element-pair block goes
-    // to its own slot, added to the near-field block by k_near_regular in list order
-    double2 *dst = o.sblk + (size_t)blockIdx.x * NL * NL;
-#pragma unroll
-    for (int u = 0; u < LT; ++u)
-#pragma unroll
-        for (int v = 0; v < LT; ++v)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const int l = 16 * u + (lane >> 4) + 4 * j, lb = 16 * v + (lane & 15);
-                if (l < NL && lb < NL) dst[l * NL + lb] = make_double2(br[u][v][j], bi[u][v][j]);
-            }
 }
 
 // ---------------------------------------------------------------------------
@@ -1572,103 +817,6 @@ size_t psi_fragment_doubles(int nl, int G2)
 {
     const int LT = (nl + 15) / 16, QT = (G2 + 15) / 16;
     return (size_t)4 * LT * 4 * QT * 64;
-}
-
-namespace {
-template <int NL>
-void launch_near_regular_nl(ige_op op, dim3 grid, size_t shm, int sb, int ce1, int ce2, int cs1, int cs2, int sstep)
-{
-    const DevOp &o = op->view;
-    hipStream_t s = lstream(op);
-    switch ((o.G2 + 15) / 16) {
-        case 1:
-            if constexpr (NL <= 12) hipLaunchKernelGGL((k_near_regular_o2<NL, 1>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep);
-            else hipLaunchKernelGGL((k_near_regular<NL, 1>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep);
-            break;
-        case 2:
-            if constexpr (NL <= 12) hipLaunchKernelGGL((k_near_regular_o2<NL, 2>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep);
-            else hipLaunchKernelGGL((k_near_regular<NL, 2>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep);
-            break;
-        case 3: hipLaunchKernelGGL((k_near_regular<NL, 3>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep); break;
-        default: hipLaunchKernelGGL((k_near_regular<NL, 4>), grid, dim3(256), shm, s, o, sb, ce1, ce2, cs1, cs2, sstep); break;
-    }
-}
-}  // namespace
-
-// shared memory of k_near_regular: block rows of the test element over a trial
-// square of sb x sb elements, and four staged element-pair blocks
-size_t near_regular_shm(int sb, int p, int nl)
-{
-    const size_t nr = nl <= 24 ? nl : 16 * near_regular_lr(nl);   // rows per workgroup
-    return sizeof(double2) * (nr * 2 * (sb + p) * (sb + p) + (size_t)4 * nr * nl);
-}
-
-int near_regular_sb(int s, int p, int nl)
-{
-    // trial squares of sb x sb elements: the largest power of two <= s that fits in
-    // 64 KB of shared memory
-    int sb = s;
-    while (sb > 1 && near_regular_shm(sb, p, nl) > 64 * 1024) sb /= 2;
-    return sb;
-}
-
-void launch_near_regular(ige_op op)
-{
-    const DevOp &o = op->view;
-    if (o.nblk == 0) return;
-    IGE_REQUIRE(o.G2 <= 64, "regular near-field rule limited to 8 x 8 points");
-    const int sb = near_regular_sb(o.s, o.p, o.nl);
-    const int nsb = o.s / sb;
-    // colours: test elements p + 1 apart (a glued function spans at most p + 1
-    // elements per direction); with several trial squares per leaf, squares whose gap
-    // of (sstep - 1) sb elements is at least p
-    const int P1 = o.p + 1, sstep = nsb > 1 ? 1 + (o.p + sb - 1) / sb : 1;
-    const size_t shm = near_regular_shm(sb, o.p, o.nl);
-    for (int ce2 = 0; ce2 < std::min(P1, o.s); ++ce2)
-        for (int ce1 = 0; ce1 < std::min(P1, o.s); ++ce1)
-            for (int cs2 = 0; cs2 < std::min(sstep, nsb); ++cs2)
-                for (int cs1 = 0; cs1 < std::min(sstep, nsb); ++cs1) {
-                    const int64_t n1 = (o.s - ce1 + P1 - 1) / P1, n2 = (o.s - ce2 + P1 - 1) / P1;
-                    const int64_t m1 = (nsb - cs1 + sstep - 1) / sstep, m2 = (nsb - cs2 + sstep - 1) / sstep;
-                    const int LT = (o.nl + 15) / 16;
-                    const int64_t nrt = LT / near_regular_lr(o.nl);   // row-tile workgroups per element
-                    const int64_t nwg = o.nblk * n1 * n2 * m1 * m2 * nrt;
-                    if (nwg == 0) continue;
-                    const dim3 grid((unsigned)nwg);
-                    switch (o.nl) {
-                        case 4: launch_near_regular_nl<4>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        case 9: launch_near_regular_nl<9>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        case 12: launch_near_regular_nl<12>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        case 16: launch_near_regular_nl<16>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        case 24: launch_near_regular_nl<24>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        case 25: launch_near_regular_nl<25>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                        default: launch_near_regular_nl<40>(op, grid, shm, sb, ce1, ce2, cs1, cs2, sstep); break;
-                    }
-                    IGE_LAUNCH_CHECK();
-                }
-}
-
-void launch_near_singular(ige_op op)
-{
-    const DevOp &o = op->view;
-    if (op->nsing == 0) return;
-    hipStream_t s = lstream(op);
-    if (o.scalar) {
-        switch (o.p) {
-            case 1: hipLaunchKernelGGL((k_near_singular<1, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 2: hipLaunchKernelGGL((k_near_singular<2, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 3: hipLaunchKernelGGL((k_near_singular<3, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            default: hipLaunchKernelGGL((k_near_singular<4, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-        }
-    } else {
-        switch (o.p) {
-            case 1: hipLaunchKernelGGL(k_near_singular<1>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 2: hipLaunchKernelGGL(k_near_singular<2>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 3: hipLaunchKernelGGL(k_near_singular<3>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            default: hipLaunchKernelGGL(k_near_singular<4>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-        }
-    }
-    IGE_LAUNCH_CHECK();
 }
 
 void launch_p2m(ige_op op, const double2 *x)

@@ -315,7 +315,6 @@ size_t planned_device_bytes(const ige_op_s *op, int restart, int r, const ige_so
 void launch_element_data(ige_op op);
 void launch_node_geometry(ige_op op);
 void launch_near_regular(ige_op op);
-int near_regular_sb(int s, int p, int nl);
 // doubles of matrix-core operand data per element (see k_element_data)
 size_t psi_fragment_doubles(int nl, int G2);
 void launch_near_singular(ige_op op);
