@@ -495,11 +495,11 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
                 for (size_t i = 1; i < sptr.size(); ++i) sptr[i] += sptr[i - 1];
                 op->d_sing_ptr.upload(sptr, s);
             }
-            op->d_sblk.alloc(std::max<size_t>(1, (size_t)op->nsing * v.nl * v.nl));
+            op->d_sblk.alloc(ige::near_singular_scratch(op));
             v.sing = op->d_sing.p; v.sing_ptr = op->d_sing_ptr.p; v.sblk = op->d_sblk.p;
             // singular element pairs into their own slots, then the regular pairs and those
             // slots summed into the blocks in a fixed order (colour by colour)
-            ige::launch_near_singular(op);
+            ige::launch_near_singular(op, geom->G);
             ige::launch_near_regular(op);
             // the same near field once per distinct entry, for the product of one column
             // (IGE_NEAR_COMPACT=0 keeps the leaf-pair blocks for it)

@@ -277,19 +277,6 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
 // one wavefront per pair; each pair's NL x NL block is written to its own slot of a
 // scratch array (no accumulation here).
 // ---------------------------------------------------------------------------
-__device__ inline void frame_map(int code, double c1, double c2, double &x, double &y)
-{
-    const int o1 = code & 1, o2 = (code >> 1) & 1, sw = (code >> 2) & 1;
-    const double du = o1 ? -1.0 : 1.0, dv = o2 ? -1.0 : 1.0;
-    if (!sw) {
-        x = o1 + du * c1;
-        y = o2 + dv * c2;
-    } else {
-        x = o1 + du * c2;
-        y = o2 + dv * c1;
-    }
-}
-
 // canonical point (s1, s2) on the test element, (t1, t2) on the trial element and
 // weight of sub-rule point idx
 __device__ inline void singular_point(const DevOp &o, int kind, int idx, double &s1, double &s2, double &t1,
@@ -334,32 +321,94 @@ __device__ inline void singular_point(const DevOp &o, int kind, int idx, double 
     }
 }
 
+// The rule of each kind as a table: rule[kind - 1] holds s1, s2, t1, t2 and the weight of its
+// points, one array after the other (kinds of 8, 6 and 4 sub-rules of gs^4 points).
+__host__ __device__ inline int singular_subrules(int kind) { return kind == 1 ? 8 : (kind == 2 ? 6 : 4); }
+__host__ __device__ inline int singular_rule_offset(int kind, int g4) { return 5 * g4 * (kind == 1 ? 0 : (kind == 2 ? 8 : 14)); }
+size_t singular_rule_doubles(int gs) { return (size_t)5 * 18 * gs * gs * gs * gs; }
+
+__global__ __launch_bounds__(256) void k_singular_rule(DevOp o, double *rule)
+{
+    const int g4 = o.gs * o.gs * o.gs * o.gs;
+    int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= 18 * g4) return;
+    const int kind = i < 8 * g4 ? 1 : (i < 14 * g4 ? 2 : 3);
+    i -= kind == 1 ? 0 : (kind == 2 ? 8 * g4 : 14 * g4);
+    const int n = singular_subrules(kind) * g4;
+    double *r = rule + singular_rule_offset(kind, g4), v[5];
+    singular_point(o, kind, i, v[0], v[1], v[2], v[3], v[4]);
+    for (int k = 0; k < 5; ++k) r[(size_t)k * n + i] = v[k];
+}
+
 // Singular pairs: one wave per pair.  The points of the sub-rules are processed in
 // batches of 32: the lower half-wave evaluates geometry and local values on the
 // test element, the upper half on the trial element, into shared memory; then
 //   B[l][l'] += sum_q K_q sum_c Psi_a[q][l][c] Psi_b[q][l'][c]
-// runs on the FP64 matrix cores with the four components c as the reduction slots
-// of one instruction per point (K_q = weight * kernel folded into the test side).
-template <int P, bool SC = false>
-__global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPair *list)
+// runs on the FP64 matrix cores (K_q = weight * kernel folded into the test side) with
+// the four components c as the reduction slots of one instruction per point, or four
+// points as its slots where only one component is not zero (the scalar operator).  A
+// point's row of shared memory holds the scalar values and divergences of the local functions
+// and the two tangents; the products Psi_l^c are formed as they are read, so a row is half
+// as long and twice the waves fit.  Control points and spline coefficients of the two elements
+// are kept in shared memory, the points come from the rule's table.
+// GD: degree in both directions of all patches of the surface (1 or 2; 0: any, out of line)
+// Bound by FP64 issue: two instructions of 64 cycles per point and 400 vector FP64 operations
+// per batch (two of the longest at a time on a SIMD).  Before, a point's rule came from five
+// integer divisions, every coefficient and control point from global memory, eleven FP64
+// divisions, and its rows (48 values per side) left room for six waves per CU: sphere level 5,
+// p = 2, 5 Gauss points (160 million points): 45.5 ms, 19.2 now.
+template <int P, bool SC, int GD>
+__global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPair *list, const double *rule)
 {
     // points per batch: 32 (16 for p = 4, whose 40 local functions would not fit);
     // SC: the scalar operator's (p+1)^2 local functions
     constexpr int NL = SC ? (P + 1) * (P + 1) : 2 * P * (P + 1), LT = (NL + 15) / 16;
-    constexpr int NB = (SC ? 2 * P * (P + 1) : NL) > 24 ? 16 : 32;
-    __shared__ double sPa[NB][NL][4];
-    __shared__ double sPb[NB][NL][4];
+    constexpr int NB = 2 * P * (P + 1) > 24 ? 16 : 32;
+    // a point's row: values, divergences, (Fu, 1), (Fv, 1), 0; scalar: values, 0 (odd lengths)
+    constexpr int ROW = SC ? (NL + 1) | 1 : 2 * NL + 9, ZERO = ROW - 1, FU = 2 * NL;
+    constexpr int NP = (P + 1) * (P + 1), NQ = P * P, NE = NP + NQ, NC = GD > 0 ? 4 * (GD + 1) * (GD + 1) : 1;
+    __shared__ double sV[2][NB][ROW];
     __shared__ double2 sK[NB];
     __shared__ double sX[NB][3];
+    __shared__ double sExt[2][2][NE];   // spline coefficients by side and direction: degree p, degree p - 1
+    __shared__ double sCp[2][NC];       // control points of the element's span, by side
     const SingularPair sp = list[blockIdx.x];
     const int lane = threadIdx.x, half = lane >> 5, qi = lane & 31;
     int ja, a1, a2, jb, b1, b2;
     elem_of(o, sp.e, ja, a1, a2);
     elem_of(o, sp.f, jb, b1, b2);
-    const int gs = o.gs, g4 = gs * gs * gs * gs;
-    const int nsub = sp.kind == 1 ? 8 : (sp.kind == 2 ? 6 : 4);
-    const int npts = nsub * g4;
-    const double h4 = o.h * o.h * o.h * o.h;
+    const int g4 = o.gs * o.gs * o.gs * o.gs, npts = singular_subrules(sp.kind) * g4;
+    const double h = o.h, h4 = h * h * h * h;
+    // this half's element, its frame and the span that holds it
+    const int j = half ? jb : ja, e1 = half ? b1 : a1, e2 = half ? b2 : a2;
+    const int code = sp.kind == 1 ? 0 : (half ? sp.fb : sp.fa);
+    const double ox = code & 1, oy = (code >> 1) & 1, dx = 1.0 - 2.0 * ox, dy = 1.0 - 2.0 * oy;
+    const bool swap = (code & 4) != 0;
+    double ua = 0.0, va = 0.0, du = 1.0, dv = 1.0;
+    bool inside = false;   // the element lies in one span
+    if constexpr (GD > 0) {
+        const PatchHdr hd = o.geo.hdr[j];
+        const double *bu = o.geo.brk + hd.brk_u, *bv = o.geo.brk + hd.brk_v;
+        int su = 0, sv = 0;
+        while (su < hd.su - 1 && (e1 + 0.5) * h >= bu[su + 1]) ++su;
+        while (sv < hd.sv - 1 && (e2 + 0.5) * h >= bv[sv + 1]) ++sv;
+        ua = bu[su];
+        va = bv[sv];
+        inside = (su == 0 || e1 * h >= ua) && (su == hd.su - 1 || (e1 + 1) * h <= bu[su + 1]) &&
+                 (sv == 0 || e2 * h >= va) && (sv == hd.sv - 1 || (e2 + 1) * h <= bv[sv + 1]);
+        du = 1.0 / (bu[su + 1] - ua);
+        dv = 1.0 / (bv[sv + 1] - va);
+        const double *c = o.geo.cp + hd.cp + (size_t)(sv * hd.su + su) * NC;
+        for (int i = qi; i < NC; i += 32) sCp[half][i] = c[i];
+    }
+    for (int i = qi; i < 2 * NE; i += 32) {
+        const int d = i / NE, k = i % NE, e = d ? e2 : e1;
+        sExt[half][d][k] = k < NP ? o.ext_p[(size_t)e * NP + k] : o.ext_q[(size_t)e * NQ + k - NP];
+    }
+    for (int i = qi; i < NB; i += 32) sV[half][i][ZERO] = 0.0;
+    const double ih = 1.0 / h, cdiv = half ? 1.0 : o.cdiv;
+    const double *r1 = rule + singular_rule_offset(sp.kind, g4) + (size_t)(half ? 2 : 0) * npts, *r2 = r1 + npts;
+    const double *rw = rule + singular_rule_offset(sp.kind, g4) + (size_t)4 * npts;
     dx4 br[LT][LT], bi[LT][LT];
 #pragma unroll
     for (int u = 0; u < LT; ++u)
@@ -369,27 +418,86 @@ __global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPai
             bi[u][v] = dx4{0.0, 0.0, 0.0, 0.0};
         }
     const int c = lane >> 4, m = lane & 15;
+    // where this lane reads its operands in a point's row: value (or divergence) and tangent component
+    int vo[LT], fo[LT];
+#pragma unroll
+    for (int u = 0; u < LT; ++u) {
+        const int l = 16 * u + m;
+        vo[u] = l >= NL ? ZERO : (SC || c < 3 ? l : NL + l);
+        fo[u] = SC ? ZERO : FU + (l < P * (P + 1) ? 0 : 4) + c;
+    }
     for (int p0 = 0; p0 < npts; p0 += NB) {
-        const int pt = p0 + qi;
-        double X[3] = {0.0, 0.0, 0.0}, wt = 0.0;
+        const int pt = min(p0 + qi, npts - 1);   // beyond the end: the last point with the weight 0
+        const double p1 = r1[pt], p2 = r2[pt], wt = p0 + qi < npts ? rw[pt] : 0.0;
         __syncthreads();   // the previous batch has been consumed
-        if (pt < npts && qi < NB) {
-            double s1, s2, t1, t2;
-            singular_point(o, sp.kind, pt, s1, s2, t1, t2, wt);
-            double xa, ya, xb, yb;
-            if (sp.kind == 1) {
-                xa = s1; ya = s2; xb = t1; yb = t2;
-            } else {
-                frame_map(sp.fa, s1, s2, xa, ya);
-                frame_map(sp.fb, t1, t2, xb, yb);
-            }
+        double X[3] = {0.0, 0.0, 0.0};
+        if (qi < NB) {
+            const double x = ox + dx * (swap ? p2 : p1), y = oy + dy * (swap ? p1 : p2);
             double Fu[3], Fv[3];
-            if (half == 0) {
-                geom_eval(o.geo, ja, (a1 + xa) * o.h, (a2 + ya) * o.h, X, Fu, Fv);
-                local_values_lds_t<P, SC>(o, a1, a2, xa, ya, Fu, Fv, o.cdiv, sPa[qi]);
+            if (GD > 0 && inside) {
+                constexpr int D = GD > 0 ? GD : 1;
+                double Bu[D + 1], Du[D + 1], Bv[D + 1], Dv[D + 1];
+                bernstein_t<D>(((e1 + x) * h - ua) * du, Bu, Du);
+                bernstein_t<D>(((e2 + y) * h - va) * dv, Bv, Dv);
+                double A[4] = {0, 0, 0, 0}, Au[4] = {0, 0, 0, 0}, Av[4] = {0, 0, 0, 0};
+#pragma unroll
+                for (int j2 = 0; j2 <= D; ++j2)
+#pragma unroll
+                    for (int k = 0; k < 4; ++k) {
+                        double w = 0.0, wu = 0.0;
+#pragma unroll
+                        for (int j1 = 0; j1 <= D; ++j1) {
+                            const double q = sCp[half][(j2 * (D + 1) + j1) * 4 + k];
+                            w = fma(Bu[j1], q, w);
+                            wu = fma(Du[j1], q, wu);
+                        }
+                        A[k] = fma(Bv[j2], w, A[k]);
+                        Au[k] = fma(Bv[j2], wu, Au[k]);
+                        Av[k] = fma(Dv[j2], w, Av[k]);
+                    }
+                const double iw = 1.0 / A[3];
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    X[k] = A[k] * iw;
+                    Fu[k] = (Au[k] - X[k] * Au[3]) * iw * du;
+                    Fv[k] = (Av[k] - X[k] * Av[3]) * iw * dv;
+                }
             } else {
-                geom_eval(o.geo, jb, (b1 + xb) * o.h, (b2 + yb) * o.h, X, Fu, Fv);
-                local_values_lds_t<P, SC>(o, b1, b2, xb, yb, Fu, Fv, 1.0, sPb[qi]);
+                double Y[3], Yu[3], Yv[3];
+                geom_eval_generic(o.geo, j, (e1 + x) * h, (e2 + y) * h, Y, Yu, Yv);
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    X[k] = Y[k];
+                    Fu[k] = Yu[k];
+                    Fv[k] = Yv[k];
+                }
+            }
+            double Pu[P + 1], dPu[P + 1], Qu[P], Pv[P + 1], dPv[P + 1], Qv[P];
+            spline_pieces_lds<P>(sExt[half][0], ih, x, Pu, dPu, Qu);
+            spline_pieces_lds<P>(sExt[half][1], ih, y, Pv, dPv, Qv);
+            double *row = sV[half][qi];
+            if constexpr (SC) {
+                const double J = cdiv * dm::surf_elem(Fu, Fv);
+#pragma unroll
+                for (int l = 0; l < NL; ++l) row[l] = Pu[l % (P + 1)] * Pv[l / (P + 1)] * J;
+            } else {
+#pragma unroll
+                for (int l = 0; l < NL; ++l) {
+                    const bool a0 = l < P * (P + 1);
+                    const int r = a0 ? l : l - P * (P + 1);
+                    const int t2 = a0 ? r / (P + 1) : r / P, t1 = a0 ? r % (P + 1) : r % P;
+                    row[l] = a0 ? Pu[t1] * Qv[t2] : Qu[t1] * Pv[t2];
+                    row[NL + l] = cdiv * (a0 ? dPu[t1] * Qv[t2] : Qu[t1] * dPv[t2]);
+                }
+#pragma unroll
+                for (int k = 0; k < 3; ++k) {
+                    row[FU + k] = Fu[k];
+                    row[FU + 4 + k] = Fv[k];
+                }
+                row[FU + 3] = 1.0;
+                row[FU + 7] = 1.0;
+            }
+            if (half == 1) {
                 sX[qi][0] = X[0];
                 sX[qi][1] = X[1];
                 sX[qi][2] = X[2];
@@ -397,23 +505,20 @@ __global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPai
         }
         __syncthreads();
         if (half == 0 && qi < NB) {
-            double2 K = make_double2(0.0, 0.0);
-            if (pt < npts) {
-                const double d0 = X[0] - sX[qi][0], d1 = X[1] - sX[qi][1], d2 = X[2] - sX[qi][2];
-                K = cscale(wt * h4, dm::helmholtz_r2(o.kappa, fma(d0, d0, fma(d1, d1, d2 * d2))));
-            }
-            sK[qi] = K;
+            const double d0 = X[0] - sX[qi][0], d1 = X[1] - sX[qi][1], d2 = X[2] - sX[qi][2];
+            const double2 K = dm::helmholtz_r2(o.kappa, fma(d0, d0, fma(d1, d1, d2 * d2)));
+            sK[qi] = p0 + qi < npts ? cscale(wt * h4, K) : make_double2(0.0, 0.0);
         }
         __syncthreads();
-        const int nb = min(NB, npts - p0);
-        for (int q = 0; q < nb; ++q) {
+#pragma unroll 8
+        for (int q0 = 0; q0 < NB; q0 += SC ? 4 : 1) {
+            const int q = SC ? q0 + c : q0;
             const double2 K = sK[q];
             double av[LT], bv[LT];
 #pragma unroll
             for (int u = 0; u < LT; ++u) {
-                const int l = 16 * u + m;
-                av[u] = l < NL ? sPa[q][l][c] : 0.0;
-                bv[u] = l < NL ? sPb[q][l][c] : 0.0;
+                av[u] = SC ? sV[0][q][vo[u]] : sV[0][q][vo[u]] * sV[0][q][fo[u]];
+                bv[u] = SC ? sV[1][q][vo[u]] : sV[1][q][vo[u]] * sV[1][q][fo[u]];
             }
 #pragma unroll
             for (int u = 0; u < LT; ++u)
@@ -518,27 +623,50 @@ void launch_near_regular(ige_op op)
                 }
 }
 
-void launch_near_singular(ige_op op)
+namespace {
+template <int P, bool SC>
+void launch_near_singular_p(ige_op op, int gd, const double *rule)
+{
+    const DevOp &o = op->view;
+    const dim3 grid((unsigned)op->nsing), blk(64);
+    hipStream_t s = lstream(op);
+    if (gd == 1) hipLaunchKernelGGL((k_near_singular<P, SC, 1>), grid, blk, 0, s, o, op->d_sing.p, rule);
+    else if (gd == 2) hipLaunchKernelGGL((k_near_singular<P, SC, 2>), grid, blk, 0, s, o, op->d_sing.p, rule);
+    else hipLaunchKernelGGL((k_near_singular<P, SC, 0>), grid, blk, 0, s, o, op->d_sing.p, rule);
+    IGE_HIP(hipGetLastError());
+}
+}  // namespace
+
+// scratch of launch_near_singular: the pairs' blocks, then the rule's table
+size_t near_singular_scratch(ige_op op)
+{
+    const DevOp &o = op->view;
+    return std::max<size_t>(1, (size_t)op->nsing * o.nl * o.nl) + singular_rule_doubles(o.gs) / 2;
+}
+
+void launch_near_singular(ige_op op, const Geometry &G)
 {
     const DevOp &o = op->view;
     if (op->nsing == 0) return;
-    hipStream_t s = lstream(op);
-    if (o.scalar) {
-        switch (o.p) {
-            case 1: hipLaunchKernelGGL((k_near_singular<1, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 2: hipLaunchKernelGGL((k_near_singular<2, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 3: hipLaunchKernelGGL((k_near_singular<3, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            default: hipLaunchKernelGGL((k_near_singular<4, true>), dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-        }
-    } else {
-        switch (o.p) {
-            case 1: hipLaunchKernelGGL(k_near_singular<1>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 2: hipLaunchKernelGGL(k_near_singular<2>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            case 3: hipLaunchKernelGGL(k_near_singular<3>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-            default: hipLaunchKernelGGL(k_near_singular<4>, dim3(op->nsing), dim3(64), 0, s, o, op->d_sing.p); break;
-        }
-    }
+    // unrolled geometry where all patches are bilinear or all biquadratic
+    int gd = G.hdr.empty() ? 0 : G.hdr[0].pu;
+    for (const auto &h : G.hdr)
+        if (h.pu != gd || h.pv != gd) gd = 0;
+    double *rule = reinterpret_cast<double *>(op->d_sblk.p + (size_t)op->nsing * o.nl * o.nl);
+    const int n = 18 * o.gs * o.gs * o.gs * o.gs;
+    hipLaunchKernelGGL(k_singular_rule, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, lstream(op), o, rule);
     IGE_HIP(hipGetLastError());
+#define IGE_SP(P) \
+    if (o.scalar) launch_near_singular_p<P, true>(op, gd, rule); \
+    else launch_near_singular_p<P, false>(op, gd, rule); \
+    break
+    switch (o.p) {
+        case 1: IGE_SP(1);
+        case 2: IGE_SP(2);
+        case 3: IGE_SP(3);
+        default: IGE_SP(4);
+    }
+#undef IGE_SP
 }
 
 }  // namespace ige

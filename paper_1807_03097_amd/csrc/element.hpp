@@ -90,69 +90,32 @@ __device__ inline void bernstein_t(double x, double *B, double *D)
     }
 }
 
+// 1-D spline pieces of degree P and P - 1 at element-local x from the element's coefficients
+// (degree P row by row, then degree P - 1); ih: 1 / element length
 template <int P>
-__device__ inline void spline_pieces_t(const DevOp &o, int e, double x, double *Pv, double *Pd, double *Qv)
+__device__ inline void spline_pieces_lds(const double *c, double ih, double x, double *Pv, double *Pd, double *Qv)
 {
     double B[P + 1], D[P + 1];
     bernstein_t<P>(x, B, D);
 #pragma unroll
     for (int t = 0; t <= P; ++t) {
         double v = 0.0, d = 0.0;
-        const double *c = o.ext_p + ((size_t)e * (P + 1) + t) * (P + 1);
 #pragma unroll
         for (int a = 0; a <= P; ++a) {
-            v += c[a] * B[a];
-            d += c[a] * D[a];
+            v += c[t * (P + 1) + a] * B[a];
+            d += c[t * (P + 1) + a] * D[a];
         }
         Pv[t] = v;
-        Pd[t] = d / o.h;
+        Pd[t] = d * ih;
     }
     double Bq[P], Dq[P];
     bernstein_t<P - 1>(x, Bq, Dq);
 #pragma unroll
     for (int t = 0; t < P; ++t) {
         double v = 0.0;
-        const double *c = o.ext_q + ((size_t)e * P + t) * P;
 #pragma unroll
-        for (int a = 0; a < P; ++a) v += c[a] * Bq[a];
+        for (int a = 0; a < P; ++a) v += c[(P + 1) * (P + 1) + t * P + a] * Bq[a];
         Qv[t] = v;
-    }
-}
-
-template <int PU, int PV>
-__device__ inline void bezier_eval_t(const GeomView &g, const PatchHdr &h, double u, double v, double X[3],
-                                     double Xu[3], double Xv[3])
-{
-    int su = 0, sv = 0;
-    while (su < h.su - 1 && u >= g.brk[h.brk_u + su + 1]) ++su;
-    while (sv < h.sv - 1 && v >= g.brk[h.brk_v + sv + 1]) ++sv;
-    const double ua = g.brk[h.brk_u + su], ub = g.brk[h.brk_u + su + 1];
-    const double va = g.brk[h.brk_v + sv], vb = g.brk[h.brk_v + sv + 1];
-    const double t = (u - ua) / (ub - ua), s = (v - va) / (vb - va);
-    double Bu[PU + 1], Du[PU + 1], Bv[PV + 1], Dv[PV + 1];
-    bernstein_t<PU>(t, Bu, Du);
-    bernstein_t<PV>(s, Bv, Dv);
-    const double *c = g.cp + h.cp + (size_t)(sv * h.su + su) * (PV + 1) * (PU + 1) * 4;
-    double A[4] = {0, 0, 0, 0}, Au[4] = {0, 0, 0, 0}, Av[4] = {0, 0, 0, 0};
-#pragma unroll
-    for (int j2 = 0; j2 <= PV; ++j2)
-#pragma unroll
-        for (int j1 = 0; j1 <= PU; ++j1) {
-            const double *Pc = c + (j2 * (PU + 1) + j1) * 4;
-            const double b = Bu[j1] * Bv[j2], bu = Du[j1] * Bv[j2], bv = Bu[j1] * Dv[j2];
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                A[k] += b * Pc[k];
-                Au[k] += bu * Pc[k];
-                Av[k] += bv * Pc[k];
-            }
-        }
-    const double iw = 1.0 / A[3], du = 1.0 / (ub - ua), dv = 1.0 / (vb - va);
-#pragma unroll
-    for (int k = 0; k < 3; ++k) {
-        X[k] = A[k] * iw;
-        Xu[k] = (Au[k] - X[k] * Au[3]) * iw * du;
-        Xv[k] = (Av[k] - X[k] * Av[3]) * iw * dv;
     }
 }
 
@@ -161,15 +124,6 @@ __device__ __noinline__ void geom_eval_generic(const GeomView &g, int j, double 
                                                double Xv[3])
 {
     bezier_eval(g, j, u, v, X, Xu, Xv);
-}
-
-// patch evaluation with unrolled paths for bilinear and biquadratic patches
-__device__ inline void geom_eval(const GeomView &g, int j, double u, double v, double X[3], double Xu[3], double Xv[3])
-{
-    const PatchHdr h = g.hdr[j];
-    if (h.pu == 2 && h.pv == 2) bezier_eval_t<2, 2>(g, h, u, v, X, Xu, Xv);
-    else if (h.pu == 1 && h.pv == 1) bezier_eval_t<1, 1>(g, h, u, v, X, Xu, Xv);
-    else geom_eval_generic(g, j, u, v, X, Xu, Xv);
 }
 
 // local function l of an element: (component, t1, t2); the scalar operator has the
@@ -233,39 +187,6 @@ __device__ inline void local_values(const DevOp &o, int e1, int e2, double x, do
         Phi[l][1] = val * F[1];
         Phi[l][2] = val * F[2];
         Dv[l] = div;
-    }
-}
-
-// (Phi_l, cdiv * div_l) for the NL = 2P(P+1) local functions, into rows of shared memory
-template <int P, bool SC = false>
-__device__ inline void local_values_lds_t(const DevOp &o, int e1, int e2, double x, double y, const double Fu[3],
-                                          const double Fv[3], double cdiv, double (*dst)[4])
-{
-    constexpr int NL = 2 * P * (P + 1);
-    double Pu[P + 1], dPu[P + 1], Qu[P], Pv[P + 1], dPv[P + 1], Qv[P];
-    spline_pieces_t<P>(o, e1, x, Pu, dPu, Qu);
-    spline_pieces_t<P>(o, e2, y, Pv, dPv, Qv);
-    if constexpr (SC) {   // scalar: (p+1)^2 tensor B-splines, value times |J| in slot 3
-        const double J = dm::surf_elem(Fu, Fv);
-#pragma unroll
-        for (int l = 0; l < (P + 1) * (P + 1); ++l) {
-            dst[l][0] = dst[l][1] = dst[l][2] = 0.0;
-            dst[l][3] = cdiv * Pu[l % (P + 1)] * Pv[l / (P + 1)] * J;
-        }
-        return;
-    }
-#pragma unroll
-    for (int l = 0; l < NL; ++l) {
-        const bool a0 = l < P * (P + 1);
-        const int r = a0 ? l : l - P * (P + 1);
-        const int t2 = a0 ? r / (P + 1) : r / P, t1 = a0 ? r % (P + 1) : r % P;
-        const double val = a0 ? Pu[t1] * Qv[t2] : Qu[t1] * Pv[t2];
-        const double div = a0 ? dPu[t1] * Qv[t2] : Qu[t1] * dPv[t2];
-        const double *F = a0 ? Fu : Fv;
-        dst[l][0] = val * F[0];
-        dst[l][1] = val * F[1];
-        dst[l][2] = val * F[2];
-        dst[l][3] = cdiv * div;
     }
 }
 

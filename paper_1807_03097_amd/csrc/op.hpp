@@ -317,7 +317,9 @@ void launch_node_geometry(ige_op op);
 void launch_near_regular(ige_op op);
 // doubles of matrix-core operand data per element (see k_element_data)
 size_t psi_fragment_doubles(int nl, int G2);
-void launch_near_singular(ige_op op);
+// pairs with a shared corner: scratch (op->d_sblk, double2) and launch
+size_t near_singular_scratch(ige_op op);
+void launch_near_singular(ige_op op, const Geometry &G);
 // values of the once-per-entry near field from the leaf-pair blocks (fixed order)
 void launch_near_merge(ige_op op);
 // largest rectangle side the once-per-entry product supports
