@@ -286,8 +286,19 @@ void check_params(const ige_params &P)
         IGE_REQUIRE(P.q_level[l] >= 0 && P.q_level[l] <= 15, "q_level entries must be 0 (q) or 1..15");
 }
 
-// host part: unknowns, trees, near pattern, singular pairs, far tables
-void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige::SingularPair> &sing)
+// lists of the near field once per distinct entry
+void plan_compact(ige_op op, const ige::NearBlocks &A)
+{
+    // rows per work item of the once-per-entry product (tuning knob IGE_NEAR_ROWS,
+    // default 128, at most 128)
+    int nrows = 128;
+    if (const char *e = std::getenv("IGE_NEAR_ROWS")) nrows = std::max(8, std::min(128, std::atoi(e)));
+    ige::build_near_compact(op->cmp, op->D, op->T, A, nrows);
+}
+
+// host part: unknowns, trees, near pattern, singular pairs, far tables; the assembly leaves the lists
+// of distinct entries (compact) until its quadrature is under way
+void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige::SingularPair> &sing, bool compact)
 {
     const ige_params &P = op->prm;
     int d = P.leaf_depth;
@@ -303,11 +314,7 @@ void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige
     if (const char *e = std::getenv("IGE_NEAR_CHUNKS")) nch = std::max(1, std::min(64, std::atoi(e)));
     ige::build_near_blocks(A, op->D, op->T, nch);
     op->nnz = A.nblk() * A.nF * A.nF;
-    // rows per work item of the once-per-entry product (tuning knob IGE_NEAR_ROWS,
-    // default 128, at most 128)
-    int nrows = 128;
-    if (const char *e = std::getenv("IGE_NEAR_ROWS")) nrows = std::max(8, std::min(128, std::atoi(e)));
-    ige::build_near_compact(op->cmp, op->D, op->T, A, nrows);
+    if (compact) plan_compact(op, A);
     if (const char *e = std::getenv("IGE_NEAR_RS")) op->cmp_rs = std::atoi(e) == 4 ? 4 : 2;
     if (const char *e = std::getenv("IGE_NEAR_PRIO")) op->near_prio = std::max(0, std::min(1, std::atoi(e)));
     if (const char *e = std::getenv("IGE_M2L_RM")) op->m2l_rm = std::atoi(e) != 0;
@@ -350,6 +357,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)op->nsing * 24 + (size_t)D.N * 80 * R;
     b += std::max((size_t)E * nl * 16, std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols)));   // right-hand side element moments
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
+    b += (size_t)5 * 18 * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * 8;   // and rule
     b += ((size_t)restart + 1 + 8) * D.N * 16 * R;               // Krylov basis and work vectors
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
     b += ige::gs_part_count(gp, (int)R, restart) * 16;           // Gram-Schmidt scratch
@@ -379,7 +387,7 @@ int ige_op_plan(ige_geom geom, const ige_params *prm, ige_op *out)
         try {
             ige::NearBlocks A;
             std::vector<ige::SingularPair> sing;
-            plan(op, geom, A, sing);
+            plan(op, geom, A, sing, true);
         } catch (...) {
             delete op;
             throw;
@@ -410,7 +418,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
         try {
             ige::NearBlocks A;
             std::vector<ige::SingularPair> sing;
-            plan(op, geom, A, sing);
+            plan(op, geom, A, sing, false);
             op->assembled = true;
             const auto &D = op->D;
             const auto &T = op->T;
@@ -501,6 +509,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // slots summed into the blocks in a fixed order (colour by colour)
             ige::launch_near_singular(op, geom->G);
             ige::launch_near_regular(op);
+            plan_compact(op, A);   // on the host meanwhile
             // the same near field once per distinct entry, for the product of one column
             // (IGE_NEAR_COMPACT=0 keeps the leaf-pair blocks for it)
             {

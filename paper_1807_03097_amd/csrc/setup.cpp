@@ -6,6 +6,7 @@
 #include <cstring>
 #include <map>
 #include <numeric>
+#include <tuple>
 
 namespace ige {
 
@@ -636,25 +637,47 @@ void build_near_compact(NearCompact &C, const Discretisation &D, const Partition
             if (g.first == owner) return g.second;
         throw Status{IGE_EINVAL, "internal: owner slice not found"};
     };
-    // off-diagonal owner blocks: for every row, the leaves that give it columns;
-    // diagonal owner blocks: their unknowns
-    std::map<std::pair<int32_t, int32_t>, std::map<int32_t, std::vector<int32_t>>> off;
-    std::map<int32_t, std::vector<int32_t>> diag;
+    // the unknowns of every owner in classes: those held by the same leaves
+    struct Class {
+        std::vector<int32_t> leaves, rows;   // both ascending
+    };
+    std::vector<std::vector<Class>> cls((size_t)nleaf);
+    {
+        std::vector<std::vector<int32_t>> in((size_t)N);   // leaves that hold the unknown
+        for (int t = 0; t < nleaf; ++t)
+            for (const auto &g : grp[t])
+                for (int32_t i : g.second) in[i].push_back(t);
+        for (int64_t i = 0; i < N; ++i) {
+            auto &co = cls[own[i]];
+            size_t k = 0;
+            while (k < co.size() && co[k].leaves != in[i]) ++k;
+            if (k == co.size()) co.push_back({in[i], {}});
+            co[k].rows.push_back((int32_t)i);
+        }
+    }
+    // off-diagonal owner blocks (T, S > T): the leaves that hold rows of T and the leaves that
+    // give those rows columns of S; diagonal owner blocks: the leaves that hold their unknowns
+    struct Source {
+        int32_t S, row_leaf, col_leaf;
+        bool operator<(const Source &o) const
+        {
+            return std::tie(S, row_leaf, col_leaf) < std::tie(o.S, o.row_leaf, o.col_leaf);
+        }
+    };
+    std::vector<std::vector<Source>> off((size_t)nleaf);
+    std::vector<std::vector<int32_t>> diag((size_t)nleaf);
     for (int64_t b = 0; b < B.nblk(); ++b) {
         const int t = B.pair[2 * b], u = B.pair[2 * b + 1];
         for (const auto &gt : grp[t])
             for (const auto &gu : grp[u]) {
                 const int32_t Tt = gt.first, Su = gu.first;
                 if (Tt == Su) {
-                    auto &dv = diag[Tt];
-                    dv.insert(dv.end(), gt.second.begin(), gt.second.end());
-                    dv.insert(dv.end(), gu.second.begin(), gu.second.end());
+                    diag[Tt].push_back(t);
+                    diag[Tt].push_back(u);
                 } else if (Tt < Su) {
-                    auto &rows = off[{Tt, Su}];
-                    for (int32_t i : gt.second) rows[i].push_back(u);
+                    off[Tt].push_back({Su, t, u});
                 } else {
-                    auto &rows = off[{Su, Tt}];
-                    for (int32_t i : gu.second) rows[i].push_back(t);
+                    off[Su].push_back({Tt, u, t});
                 }
             }
     }
@@ -675,34 +698,47 @@ void build_near_compact(NearCompact &C, const Discretisation &D, const Partition
         C.maxn = std::max(C.maxn, (int)std::max(rows.size(), cols.size()));
     };
     // in owner order: the diagonal square of T, then its off-diagonal blocks (T, S > T)
-    auto it = off.begin();
+    std::vector<int32_t> v, ls;
     for (int32_t Tt = 0; Tt < nleaf; ++Tt) {
-        auto dt = diag.find(Tt);
-        if (dt != diag.end()) {
-            auto &v = dt->second;
+        if (!diag[Tt].empty()) {
+            std::sort(diag[Tt].begin(), diag[Tt].end());
+            diag[Tt].erase(std::unique(diag[Tt].begin(), diag[Tt].end()), diag[Tt].end());
+            v.clear();
+            for (int32_t t : diag[Tt]) {
+                const auto &sl = slice(t, Tt);
+                v.insert(v.end(), sl.begin(), sl.end());
+            }
             std::sort(v.begin(), v.end());
             v.erase(std::unique(v.begin(), v.end()), v.end());
             add_sub(v, v, true);
         }
-        for (; it != off.end() && it->first.first == Tt; ++it) {
-            const int32_t Su = it->first.second;
+        auto &src = off[Tt];
+        std::sort(src.begin(), src.end());
+        for (size_t k0 = 0, k1; k0 < src.size(); k0 = k1) {
+            const int32_t Su = src[k0].S;
+            for (k1 = k0; k1 < src.size() && src[k1].S == Su; ++k1) {}
             // rows with the same set of column leaves form one rectangle
             std::map<std::vector<int32_t>, std::vector<int32_t>> byset;
-            for (auto &rv : it->second) {
-                auto &ls = rv.second;
+            for (const auto &c : cls[Tt]) {
+                ls.clear();
+                for (size_t k = k0; k < k1; ++k)
+                    if (std::binary_search(c.leaves.begin(), c.leaves.end(), src[k].row_leaf)) ls.push_back(src[k].col_leaf);
+                if (ls.empty()) continue;
                 std::sort(ls.begin(), ls.end());
                 ls.erase(std::unique(ls.begin(), ls.end()), ls.end());
-                byset[ls].push_back(rv.first);
+                auto &rows = byset[ls];
+                rows.insert(rows.end(), c.rows.begin(), c.rows.end());
             }
             for (auto &kv : byset) {
-                std::vector<int32_t> cols;
+                std::sort(kv.second.begin(), kv.second.end());
+                v.clear();
                 for (int32_t leaf : kv.first) {
                     const auto &sl = slice(leaf, Su);
-                    cols.insert(cols.end(), sl.begin(), sl.end());
+                    v.insert(v.end(), sl.begin(), sl.end());
                 }
-                std::sort(cols.begin(), cols.end());
-                cols.erase(std::unique(cols.begin(), cols.end()), cols.end());
-                add_sub(kv.second, cols, false);
+                std::sort(v.begin(), v.end());
+                v.erase(std::unique(v.begin(), v.end()), v.end());
+                add_sub(kv.second, v, false);
             }
         }
     }
@@ -819,6 +855,21 @@ void build_singular_pairs(std::vector<SingularPair> &S, std::vector<double> &cor
                 rad[e] = r;
             }
     const double tol = 1e-9 * G.scale;
+    // spheres around the leaves' elements, a little larger than the elements' own
+    const size_t nleaf = (size_t)D.P * SL * SL;
+    std::vector<double> lcen(nleaf * 3, 0.0), lrad(nleaf, 0.0);
+    for (size_t l = 0; l < nleaf; ++l) {
+        const size_t j = l / (SL * SL), r = l % (SL * SL), r2 = r / SL, r1 = r % SL;
+        auto each = [&](auto &&fn) {
+            for (int a2 = 0; a2 < s; ++a2)
+                for (int a1 = 0; a1 < s; ++a1) fn((j * n + r2 * s + a2) * n + r1 * s + a1);
+        };
+        each([&](size_t e) {
+            for (int d = 0; d < 3; ++d) lcen[l * 3 + d] += cen[e * 3 + d] / (s * s);
+        });
+        each([&](size_t e) { lrad[l] = std::max(lrad[l], dist3(&lcen[l * 3], &cen[e * 3]) + rad[e]); });
+        lrad[l] = lrad[l] * (1.0 + 1e-9) + 2 * tol;
+    }
     S.clear();
     for (int64_t blk = 0; blk < B.nblk(); ++blk) {
         const int lt = B.pair[2 * blk], ls = B.pair[2 * blk + 1];
@@ -827,6 +878,7 @@ void build_singular_pairs(std::vector<SingularPair> &S, std::vector<double> &cor
         for (int a2 = 0; a2 < s; ++a2)
             for (int a1 = 0; a1 < s; ++a1) {
                 const size_t e = ((size_t)jt * n + jt2 * s + a2) * n + jt1 * s + a1;
+                if (dist3(&cen[e * 3], &lcen[(size_t)ls * 3]) > rad[e] * (1.0 + 1e-9) + lrad[ls] + 2 * tol) continue;
                 for (int b2 = 0; b2 < s; ++b2)
                     for (int b1 = 0; b1 < s; ++b1) {
                         const size_t f = ((size_t)js * n + js2 * s + b2) * n + js1 * s + b1;
