@@ -127,21 +127,39 @@ __global__ __launch_bounds__(1024) __attribute__((amdgpu_waves_per_eu(WPE))) voi
         }
 }
 
-// yt[i][c] = sum of the item sums of unknown i, in list order
-__global__ __launch_bounds__(256) void k_near_cols_sum(int64_t N, int r, const int64_t *ptr, const int32_t *idx,
+// yt[i][c] = sum of the item sums of unknown i: S threads per (unknown, column) take every S-th
+// one, eight loads at a time, and are added in order
+__global__ __launch_bounds__(256) void k_near_cols_sum(int64_t N, int r, int S, const int64_t *ptr, const int32_t *idx,
                                                        const double2 *part, double2 *yt)
 {
-    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (t >= N * r) return;
-    const int64_t i = t / r;
-    const int c = (int)(t % r);
+    __shared__ double2 sh[256];
+    const int per = blockDim.x / S, j = threadIdx.x % per, q = threadIdx.x / per;
+    const int64_t t = (int64_t)blockIdx.x * per + j;
     double re = 0.0, im = 0.0;
-    for (int64_t k = ptr[i]; k < ptr[i + 1]; ++k) {
-        const double2 v = part[(size_t)idx[k] * r + c];
-        re += v.x;
-        im += v.y;
+    if (t < N * r) {
+        const int64_t i = t / r, e = ptr[i + 1];
+        const int c = (int)(t % r);
+        for (int64_t k0 = ptr[i] + q; k0 < e; k0 += 8 * S) {
+            double2 v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = k0 + u * S < e ? part[(size_t)idx[k0 + u * S] * r + c] : make_double2(0.0, 0.0);
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (k0 + u * S < e) {
+                    re += v[u].x;
+                    im += v[u].y;
+                }
+        }
     }
-    yt[t] = make_double2(re, im);
+    if (S > 1) {
+        sh[threadIdx.x] = make_double2(re, im);
+        __syncthreads();
+        for (int s = 1; s < S && q == 0; ++s) {
+            re += sh[s * per + j].x;
+            im += sh[s * per + j].y;
+        }
+    }
+    if (q == 0 && t < N * r) yt[t] = make_double2(re, im);
 }
 
 }  // namespace
@@ -194,10 +212,14 @@ void near_cols(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s)
     }
 #undef IGE_NC
     IGE_HIP(hipGetLastError());
+    // one thread per four item sums of an unknown, up to eight
     const int64_t tot = (int64_t)o.N * r;
-    hipLaunchKernelGGL(k_near_cols_sum, dim3((unsigned)((tot + 255) / 256)), dim3(256), 0, s, (int64_t)o.N, r,
-                       fine ? op->d_nfred_ptr.p : op->d_nbred_ptr.p, fine ? op->d_nfred_idx.p : op->d_nbred_idx.p,
-                       op->d_ndpart.p, yt);
+    const DBuf<int32_t> &ridx = fine ? op->d_nfred_idx : op->d_nbred_idx;
+    int S = 1;
+    while (S < 8 && (int64_t)ridx.n > 8 * S * (int64_t)o.N) S *= 2;
+    const int per = 256 / S;
+    hipLaunchKernelGGL(k_near_cols_sum, dim3((unsigned)((tot + per - 1) / per)), dim3(256), 0, s, (int64_t)o.N, r, S,
+                       fine ? op->d_nfred_ptr.p : op->d_nbred_ptr.p, ridx.p, op->d_ndpart.p, yt);
     IGE_HIP(hipGetLastError());
 }
 
