@@ -82,7 +82,14 @@ void apply_one(ige_op op, const double2 *x, double2 *y, int prec = IGE_F64)
         if (prof && ige::prof_records(op, i)) IGE_HIP(hipEventRecord(ev[i], st));
     };
     const bool far = !op->work.empty();
-    if (!far || !op->overlap) {
+    // The near-field product on the second stream, except where it is so short that fork and join
+    // cost more than it hides.  Captured in a graph (per iteration of a solve): near field 5 us at
+    // the memory's rate, coupling 24: 134 us with, 131 without; 7 and 8 us: 5 % less without.  Enqueued
+    // by the host, which then sets the pace: 17 and 1 us: 68 with, 56 without; 7 and 8: 66 and 62;
+    // but 1 and 18 (a coupling of three levels): 77 and 83.
+    const bool brief = op->near_us + op->far_us < 20.0;
+    const bool in_line = op->lst ? op->near_us < 10.0 || brief : op->far_us < 10.0 && brief;
+    if (!far || !op->overlap || in_line) {
         if (far) {
             mark(0, s);
             ige::launch_p2m(op, x);

@@ -349,12 +349,21 @@ void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
         steps += 0.5 * ((Q + 12) / 16) * ((Q + 3) / 4);
     }
     const double near_us = (double)op->cmp.nval * 16.0 / 4.7e6, far_us = steps * 340.0 / (1024.0 * 2400.0);
-    if (chunk <= 0) chunk = near_us > 0.5 * far_us ? 4 : 2;
     std::vector<int32_t> spart;
     op->swork.clear();
     int rt = 1;
     for (const auto &f : T.far) rt = std::max(rt, ((F.ql[f[0]] + 1) * (F.ql[f[0]] + 1) + 15) / 16);   // node tiles of a cluster
     rt = 2 * ((std::min(rt, kSymTiles) + 1) / 2);
+    // Few pairs: one partner per item where that makes no more than four items per CU, and with less
+    // than one per CU 64 rows per item.  A wave is then bound by its own latencies (level 4, 60
+    // pairs of 81 nodes: 39 us with two partners and all rows, 14 now; torus level 3, 72 pairs of 225
+    // nodes, 128 rows per item: 70 and 47).
+    int64_t items = 0;
+    for (const auto &f : T.far) items += ((F.ql[f[0]] + 1) * (F.ql[f[0]] + 1) + 16 * rt - 1) / (16 * rt);
+    op->near_us = near_us;
+    op->far_us = far_us;
+    if (chunk <= 0) chunk = items / 2 < 1024 ? 1 : (near_us > 0.5 * far_us ? 4 : 2);
+    if (items / 2 < 256) rt = std::min(rt, 4);
     op->sym_rt = rt / 2;
     size_t i = 0;
     while (i < T.far.size()) {   // sorted by level, cluster, partner
