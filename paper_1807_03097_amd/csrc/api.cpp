@@ -82,12 +82,25 @@ void apply_one(ige_op op, const double2 *x, double2 *y, int prec = IGE_F64)
         if (prof && ige::prof_records(op, i)) IGE_HIP(hipEventRecord(ev[i], st));
     };
     const bool far = !op->work.empty();
-    // The near-field product on the second stream, except where it is so short that fork and join
-    // cost more than it hides.  Captured in a graph (per iteration of a solve): near field 5 us at
-    // the memory's rate, coupling 24: 134 us with, 131 without; 7 and 8 us: 5 % less without.  Enqueued
-    // by the host, which then sets the pace: 17 and 1 us: 68 with, 56 without; 7 and 8: 66 and 62;
-    // but 1 and 18 (a coupling of three levels): 77 and 83.
+    // A brief near-field product shares the coupling's launch (not while stages are timed).  Times at
+    // their rates (near, far), two streams against one launch: 17 and 1 us: 68 and 46; 7 and 8: 66 and
+    // 55; 1 and 18: 77 and 72; 44 and 8: 83 and 78; 51 and 312: 532 and 538; longer ones fill the
+    // device each for itself
     const bool brief = op->near_us + op->far_us < 20.0;
+    if (far && op->overlap && !prof && prec == IGE_F64 && (op->near_us < 20.0 || op->near_us + op->far_us < 60.0) &&
+        !op->stored && ige::m2l_sym_near_ok(op)) {
+        ige::launch_p2m(op, x);
+        ige::launch_m2m(op);
+        ige::launch_m2l_sym_near(op, x);
+        ige::launch_m2l_reduce(op, prec);
+        ige::launch_l2l(op);
+        ige::launch_l2p_leaf(op);
+        ige::launch_gather(op, y);
+        return;
+    }
+    // Otherwise on the second stream, except where fork and join cost more than it hides: captured in a
+    // graph, near 5 us and far 24: 134 us per iteration with, 131 without; enqueued by the host, which
+    // then sets the pace, 7 and 8: 66 with, 62 without; but 1 and 18: 77 and 83
     const bool in_line = op->lst ? op->near_us < 10.0 || brief : op->far_us < 10.0 && brief;
     if (!far || !op->overlap || in_line) {
         if (far) {

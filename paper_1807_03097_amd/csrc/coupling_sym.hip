@@ -5,6 +5,7 @@
 #include <algorithm>
 
 #include "device_math.hpp"
+#include "near_item.hpp"
 #include "op.hpp"
 
 namespace ige {
@@ -282,32 +283,72 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT <= 3 ? 4
     m2l_sym_body<RT>(o, blockIdx.x, nwork, wk, partner, src, part, Q, sh);
 }
 
-// per cluster, the sum of its slots in list order (row sides of its items, then the column
-// sides of its pairs; loads issued eight slots at a time), converted to the test-side fields
-__global__ __launch_bounds__(512) void k_m2l_reduce_sym(DevOp o, const int32_t *ptr, const int32_t *idx,
-                                                        const double2 *part, double2 *loc)
+// The same with the near-field product's items in the same launch, behind the coupling's: where that
+// product is short, a second stream's fork and join cost more than the two hide (level 4, 64 nodes
+// per cluster: 40.4 and 17.0 us one after the other, 49.9 together)
+template <int RT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RT <= 3 ? 4 : 3))) void k_m2l_sym_near(
+    DevOp o, int nwork, const SymWork *work, const int32_t *partner, const double2 *src, double2 *part, NearCmpView v,
+    int64_t na, int64_t nw, const double2 *x, double2 *npart)
 {
-    __shared__ double2 su[4][kMaxQ1 * kMaxQ1];
+    struct NearShared {
+        double2 xr[kCmpRows], yc[3][256];
+    };
+    constexpr size_t kBytes = sizeof(SymShared<RT>) > sizeof(NearShared) ? sizeof(SymShared<RT>) : sizeof(NearShared);
+    __shared__ __attribute__((aligned(16))) char smem[kBytes];
+    if ((int)blockIdx.x < nwork) {
+        SymShared<RT> &sh = *reinterpret_cast<SymShared<RT> *>(smem);
+        sh.tab[threadIdx.x] = o.sctab[threadIdx.x];
+        const SymWork wk = work[blockIdx.x];
+        int lvl = 0;
+        while (lvl < o.L && wk.tgt >= o.lvl_off[lvl + 1]) ++lvl;
+        const int Q = (o.ql[lvl] + 1) * (o.ql[lvl] + 1);
+        m2l_sym_body<RT>(o, blockIdx.x, nwork, wk, partner, src, part, Q, sh);
+        return;
+    }
+    NearShared &ns = *reinterpret_cast<NearShared *>(smem);
+    const int64_t b = (int64_t)blockIdx.x - nwork;
+    if (b < nw) near_cmp_item<3, 2, 0>(v, v.order[na + b], x, npart, ns.xr, ns.yc);
+    else near_cmp_item<2, 2, 0>(v, v.order[b - nw], x, npart, ns.xr, ns.yc);
+}
+
+// Per cluster, the sum of its slots (row sides of its items, then the column sides of its pairs),
+// converted to the test-side fields.  S threads per value take every S-th slot, eight loads at a
+// time, and are added in order: one thread per value waited for six rounds of loads (level 4,
+// 64 nodes, about 40 slots: 10.2 us, 7 now).
+__global__ __launch_bounds__(1024) void k_m2l_reduce_sym(DevOp o, int S, const int32_t *ptr, const int32_t *idx,
+                                                         const double2 *part, double2 *loc)
+{
+    extern __shared__ double2 su[];   // [S][4][Q]
     const int gc = blockIdx.x, Qs = o.Q;
     int lvl = 0;
     while (lvl < o.L && gc >= o.lvl_off[lvl + 1]) ++lvl;
     const int Q = (o.ql[lvl] + 1) * (o.ql[lvl] + 1);
     const int b = ptr[gc], e = ptr[gc + 1];
-    for (int i = threadIdx.x; i < 4 * Q; i += blockDim.x) {
-        const int f = i / Q, mm = i % Q;
+    const int G = blockDim.x / S, q = __builtin_amdgcn_readfirstlane(threadIdx.x / G);   // uniform: scalar list reads
+    for (int r = threadIdx.x - q * G; r < 4 * Q; r += G) {
+        const int f = r / Q, mm = r - f * Q;
         double2 v = make_double2(0, 0);
-        for (int w0 = b; w0 < e; w0 += 8) {
+        for (int w0 = b + q; w0 < e; w0 += 8 * S) {
             double2 t[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                t[u] = w0 + u < e ? part[((size_t)idx[w0 + u] * 4 + f) * Qs + mm] : make_double2(0, 0);
+                t[u] = w0 + u * S < e ? part[((size_t)idx[w0 + u * S] * 4 + f) * Qs + mm] : make_double2(0, 0);
 #pragma unroll
             for (int u = 0; u < 8; ++u)
-                if (w0 + u < e) v = cadd(v, t[u]);
+                if (w0 + u * S < e) v = cadd(v, t[u]);
         }
-        su[f][mm] = v;
+        su[q * 4 * Q + r] = v;
     }
     __syncthreads();
+    if (S > 1) {
+        for (int i = threadIdx.x; i < 4 * Q; i += blockDim.x) {
+            double2 v = su[i];
+            for (int q = 1; q < S; ++q) v = cadd(v, su[q * 4 * Q + i]);
+            su[i] = v;
+        }
+        __syncthreads();
+    }
     const double ik2 = 1.0 / (o.kappa * o.kappa);
     for (int mm = threadIdx.x; mm < Q; mm += blockDim.x) {
         const double *T = o.nodeT + (size_t)gc * 6 * Qs;
@@ -316,17 +357,17 @@ __global__ __launch_bounds__(512) void k_m2l_reduce_sym(DevOp o, const int32_t *
             const double Fu[3] = {T[mm], T[Qs + mm], T[2 * Qs + mm]}, Fv[3] = {T[3 * Qs + mm], T[4 * Qs + mm], T[5 * Qs + mm]};
             L[mm] = make_double2(0, 0);
             L[Qs + mm] = make_double2(0, 0);
-            L[2 * Qs + mm] = cscale(surf_elem(Fu, Fv), su[3][mm]);
+            L[2 * Qs + mm] = cscale(surf_elem(Fu, Fv), su[3 * Q + mm]);
             continue;
         }
         double2 t1 = make_double2(0, 0), t2 = make_double2(0, 0);
         for (int k = 0; k < 3; ++k) {
-            t1 = cadd(t1, cscale(T[k * Qs + mm], su[k][mm]));
-            t2 = cadd(t2, cscale(T[(3 + k) * Qs + mm], su[k][mm]));
+            t1 = cadd(t1, cscale(T[k * Qs + mm], su[k * Q + mm]));
+            t2 = cadd(t2, cscale(T[(3 + k) * Qs + mm], su[k * Q + mm]));
         }
         L[mm] = t1;
         L[Qs + mm] = t2;
-        L[2 * Qs + mm] = cscale(-ik2, su[3][mm]);
+        L[2 * Qs + mm] = cscale(-ik2, su[3 * Q + mm]);
     }
 }
 
@@ -418,11 +459,43 @@ void launch_m2l_sym(ige_op op)
     IGE_HIP(hipGetLastError());
 }
 
+// whether the near-field product of one column can go into the coupling's launch
+bool m2l_sym_near_ok(const ige_op_s *op)
+{
+    return op->cmp_on && op->near_one && op->cmp_rs == 2 && op->cmp.maxn <= 192 && !op->swork.empty();
+}
+
+void launch_m2l_sym_near(ige_op op, const double2 *x)
+{
+    const DevOp &o = op->view;
+    const NearCmpView &v = op->cview;
+    const int nw = (int)op->swork.size();
+    const int64_t na = op->cmp.nnarrow, nn = v.nwork;
+    hipStream_t s = lstream(op);
+#define IGE_MSN(RT) \
+    hipLaunchKernelGGL(k_m2l_sym_near<RT>, dim3((unsigned)(nw + nn)), dim3(256), 0, s, o, nw, op->d_swork.p, op->d_spartner.p, \
+                       op->d_src.p, op->d_spart.p, v, na, nn - na, x, op->d_cpart.p)
+    switch (op->sym_rt) {
+        case 1: IGE_MSN(1); break;
+        case 2: IGE_MSN(2); break;
+        case 3: IGE_MSN(3); break;
+        default: IGE_MSN(4); break;
+    }
+#undef IGE_MSN
+    IGE_HIP(hipGetLastError());
+}
+
 void launch_m2l_reduce_sym(ige_op op)
 {
     const DevOp &o = op->view;
-    const int nt = std::min(512, (4 * o.Q + 63) / 64 * 64);
-    hipLaunchKernelGGL(k_m2l_reduce_sym, dim3(op->NC), dim3(nt), 0, lstream(op), o, op->d_sred_ptr.p, op->d_sred_idx.p,
+    // up to four threads per value where a list is long
+    const int64_t len = ((int64_t)op->swork.size() + (int64_t)op->d_spartner.n) / std::max(1, op->NC);
+    int S = 1;
+    const int G = std::min(512, (4 * o.Q + 63) / 64 * 64);
+    while (S < 4 && len > 8 * S && 2 * S * G <= 1024) S *= 2;
+    const int nt = S * G;
+    const size_t shm = sizeof(double2) * 4 * o.Q * S;
+    hipLaunchKernelGGL(k_m2l_reduce_sym, dim3(op->NC), dim3(nt), shm, lstream(op), o, S, op->d_sred_ptr.p, op->d_sred_idx.p,
                        op->d_spart.p, op->d_loc.p);
     IGE_HIP(hipGetLastError());
 }

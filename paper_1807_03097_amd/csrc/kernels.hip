@@ -120,6 +120,13 @@ __global__ __launch_bounds__(256) void k_p2m(DevOp o, const double2 *x, double2 
     double2 *Z1 = X2 + w2b * w1b;             // [w2a][Q1]
     double2 *Zd = Z1 + w2a * Q1;              // [w2a][Q1]
     double2 *Z2 = Zd + w2a * Q1;              // [w2b][Q1]
+    // Mp, Mq, Mdp of k1, then of k2, read with the coefficients
+    const int QR = Q1 * RL;
+    double *Mt = reinterpret_cast<double *>(Z2 + w2b * Q1);
+    for (int i = threadIdx.x; i < 6 * QR; i += blockDim.x) {
+        const int a = i / QR, m = i - a * QR, k = a < 3 ? k1 : k2, b = a % 3;
+        Mt[i] = (b == 0 ? o.Mp : (b == 1 ? o.Mq : o.Mdp))[(size_t)k * QR + m];
+    }
     for (int i = threadIdx.x; i < w2a * w1a; i += blockDim.x) {
         const int i2 = i / w1a, i1 = i % w1a;
         const size_t off = (((size_t)j * 2 + 0) * o.nb + (k2 * s + i2)) * o.nb + (k1 * s + i1);
@@ -133,8 +140,7 @@ __global__ __launch_bounds__(256) void k_p2m(DevOp o, const double2 *x, double2 
         X2[i] = cscale((double)o.sgn[off], v);
     }
     __syncthreads();
-    const double *Mpu = o.Mp + (size_t)k1 * Q1 * RL, *Mqu = o.Mq + (size_t)k1 * Q1 * RL, *Mdu = o.Mdp + (size_t)k1 * Q1 * RL;
-    const double *Mpv = o.Mp + (size_t)k2 * Q1 * RL, *Mqv = o.Mq + (size_t)k2 * Q1 * RL, *Mdv = o.Mdp + (size_t)k2 * Q1 * RL;
+    const double *Mpu = Mt, *Mqu = Mt + QR, *Mdu = Mt + 2 * QR, *Mpv = Mt + 3 * QR, *Mqv = Mt + 4 * QR, *Mdv = Mt + 5 * QR;
     // contract along u
     for (int i = threadIdx.x; i < w2a * Q1; i += blockDim.x) {
         const int i2 = i / Q1, m1 = i % Q1;
@@ -222,7 +228,12 @@ __global__ __launch_bounds__(256) void k_p2m_sc(DevOp o, const double2 *x, doubl
 // a4: M2M, parents on level lvl from children on lvl+1
 // parent[m2][m1] = sum_c sum_{n1,n2} T_c1[n1][m1] T_c2[n2][m2] child_c[n2][n1]
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_m2m(DevOp o, int lvl, double2 *mom, double2 *src)
+// Bound by latency (a few dozen to a few hundred workgroups, two short sums): the transfer
+// matrices come to shared memory with the children's moments, the node tangents to registers,
+// a workgroup has a thread per value and the sums over the four children are taken apart.
+// 96 parents of 225 nodes: 27.9 us with 256 threads and the matrices from
+// global memory, 11.5 now; 24 of 64 nodes: 7.8 and 6.4.
+__global__ __launch_bounds__(1024) void k_m2m(DevOp o, int lvl, double2 *mom, double2 *src)
 {
     extern __shared__ double2 sm2[];
     const int id = blockIdx.x;
@@ -231,52 +242,55 @@ __global__ __launch_bounds__(256) void k_m2m(DevOp o, int lvl, double2 *mom, dou
     const int gc = (int)o.lvl_off[lvl] + id;
     double2 *ch = sm2;            // [4 children][3 fields][Q]
     double2 *W = ch + 12 * Q;     // [4][3][Q1 (n2)][Q1 (m1)]
-    // one read phase: the moments of the four children
+    double *T = reinterpret_cast<double *>(W + 12 * Q);   // [2][Q1 (n)][Q1 (m)]
+    // one read phase: the moments of the four children, the transfer matrices, this thread's tangents
     for (int i = threadIdx.x; i < 12 * Q; i += blockDim.x) {
         const int c = i / (3 * Q), rem = i % (3 * Q);
         const int c1 = c & 1, c2 = c >> 1;
         const int cgc = (int)o.lvl_off[lvl + 1] + (j * 2 * S + 2 * k2 + c2) * 2 * S + 2 * k1 + c1;
         ch[i] = mom[(size_t)cgc * 3 * Q + rem];
     }
+    for (int i = threadIdx.x; i < 2 * Q; i += blockDim.x) T[i] = i < Q ? o.T0[i] : o.T1[i - Q];
+    double F[6];   // a workgroup has at least Q threads
+#pragma unroll
+    for (int k = 0; k < 6; ++k) F[k] = threadIdx.x < Q ? o.nodeT[((size_t)gc * 6 + k) * Q + threadIdx.x] : 0.0;
     __syncthreads();
     // contract along u: W[c][f][n2][m1] = sum_n1 T_c1[n1][m1] child_c[f][n2][n1]
     for (int i = threadIdx.x; i < 12 * Q; i += blockDim.x) {
-        const int c = i / (3 * Q), rem = i % (3 * Q), f = rem / Q, nm = rem % Q, n2 = nm / Q1, m1 = nm % Q1;
-        const double *Tu = (c & 1) ? o.T1 : o.T0;
-        const double2 *cf = ch + (size_t)(c * 3 + f) * Q + n2 * Q1;
+        const int cf = i / Q, nm = i - cf * Q, n2 = nm / Q1, m1 = nm - n2 * Q1;
+        const double *Tu = T + (cf / 3 & 1) * Q + m1;
+        const double2 *v = ch + cf * Q + n2 * Q1;
         double2 z = make_double2(0, 0);
-        for (int n1 = 0; n1 < Q1; ++n1) z = cadd(z, cscale(Tu[n1 * Q1 + m1], cf[n1]));
+        for (int n1 = 0; n1 < Q1; ++n1) z = cadd(z, cscale(Tu[n1 * Q1], v[n1]));
         W[i] = z;
     }
     __syncthreads();
-    // contract along v and sum the children: parent[f][m2][m1]
-    for (int i = threadIdx.x; i < 3 * Q; i += blockDim.x) {
-        const int f = i / Q, mm = i % Q, m2 = mm / Q1, m1 = mm % Q1;
+    // contract along v (into the place of the children, no longer needed)
+    for (int i = threadIdx.x; i < 12 * Q; i += blockDim.x) {
+        const int cf = i / Q, mm = i - cf * Q, m2 = mm / Q1, m1 = mm - m2 * Q1;
+        const double *Tv = T + (cf / 6) * Q + m2;
+        const double2 *v = W + cf * Q + m1;
         double2 z = make_double2(0, 0);
-        for (int c = 0; c < 4; ++c) {
-            const double *Tv = (c >> 1) ? o.T1 : o.T0;
-            const double2 *wf = W + (size_t)(c * 3 + f) * Q;
-            for (int n2 = 0; n2 < Q1; ++n2) z = cadd(z, cscale(Tv[n2 * Q1 + m2], wf[n2 * Q1 + m1]));
-        }
-        ch[i] = z;   // children no longer needed
+        for (int n2 = 0; n2 < Q1; ++n2) z = cadd(z, cscale(Tv[n2 * Q1], v[n2 * Q1]));
+        ch[i] = z;
     }
     __syncthreads();
-    for (int mm = threadIdx.x; mm < Q; mm += blockDim.x) {
-        double2 *M = mom + (size_t)gc * 3 * Q;
-        const double2 s1 = ch[mm], s2v = ch[Q + mm], d = ch[2 * Q + mm];
-        M[mm] = s1;
-        M[Q + mm] = s2v;
-        M[2 * Q + mm] = d;
-        const double *T = o.nodeT + (size_t)gc * 6 * Q;
-        double2 *Sv = src + (size_t)gc * 4 * Q;
-        for (int k = 0; k < 3; ++k) Sv[k * Q + mm] = cadd(cscale(T[k * Q + mm], s1), cscale(T[(3 + k) * Q + mm], s2v));
-        if (o.scalar) {   // scalar: the moments times the surface element at the node
-            const double Fu[3] = {T[mm], T[Q + mm], T[2 * Q + mm]}, Fv[3] = {T[3 * Q + mm], T[4 * Q + mm], T[5 * Q + mm]};
-            Sv[3 * Q + mm] = cscale(surf_elem(Fu, Fv), d);
-        } else {
-            Sv[3 * Q + mm] = d;
-        }
+    const int mm = threadIdx.x;
+    if (mm >= Q) return;
+    double2 f[3];
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {   // sum of the children
+        f[k] = ch[k * Q + mm];
+        for (int c = 1; c < 4; ++c) f[k] = cadd(f[k], ch[(c * 3 + k) * Q + mm]);
     }
+    double2 *M = mom + (size_t)gc * 3 * Q, *Sv = src + (size_t)gc * 4 * Q;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        M[k * Q + mm] = f[k];
+        Sv[k * Q + mm] = cadd(cscale(F[k], f[0]), cscale(F[3 + k], f[1]));
+    }
+    // scalar: the moments times the surface element at the node
+    Sv[3 * Q + mm] = o.scalar ? cscale(surf_elem(F, F + 3), f[2]) : f[2];
 }
 
 // Levels of a smaller interpolation degree q_l (variable order): their moments are the
@@ -663,34 +677,75 @@ __global__ __launch_bounds__(256) void k_near_gather(int N, const int64_t *ptr, 
 // then one thread per unknown gathers (with the gluing sign) the entries of the
 // leaf clusters that its incarnations touch: the scatter T^T without atomics.
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void k_l2p_leaf(DevOp o, const double2 *loc, double2 *ybuf)
+// With the expansions of the parents (down): the leaf's own L2L comes first, in the same
+// workgroup.  Bound by latency: fields and tables come to shared memory in one read phase.
+__device__ __forceinline__ void leaf_l2l(const DevOp &o, int k1, int k2, int Q1, int Q, double2 *t, const double2 *par, double2 *W,
+                                         const double *T, int f0, int nf)
+{
+    // t[f][n2][n1] += sum T_c2[n2][m2] sum T_c1[n1][m1] par[f][m2][m1] (fields f0 .. f0 + nf - 1)
+    const double *Tu = T + (k1 & 1) * Q, *Tv = T + (k2 & 1) * Q;
+    for (int i = threadIdx.x; i < nf * Q; i += blockDim.x) {
+        const int f = i / Q, rem = i - f * Q, m2 = rem / Q1, n1 = rem - m2 * Q1;
+        double2 z = make_double2(0, 0);
+        for (int m1 = 0; m1 < Q1; ++m1) z = cadd(z, cscale(Tu[n1 * Q1 + m1], par[(f0 + f) * Q + m2 * Q1 + m1]));
+        W[i] = z;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i < nf * Q; i += blockDim.x) {
+        const int f = i / Q, rem = i - f * Q, n2 = rem / Q1, n1 = rem - n2 * Q1;
+        double2 z = t[(f0 + f) * Q + rem];
+        for (int m2 = 0; m2 < Q1; ++m2) z = cadd(z, cscale(Tv[n2 * Q1 + m2], W[f * Q + m2 * Q1 + n1]));
+        t[(f0 + f) * Q + rem] = z;
+    }
+    __syncthreads();
+}
+
+// the leaf's fields (and its parent's) and the transfer matrices to shared memory
+__device__ __forceinline__ void leaf_read(const DevOp &o, bool down, int id, int k1, int k2, int Q, const double2 *loc, double2 *t,
+                                          double2 *par, double *T)
+{
+    const int SL = o.SL, gc = (int)o.lvl_off[o.L] + id;
+    for (int i = threadIdx.x; i < 3 * Q; i += blockDim.x) t[i] = loc[(size_t)gc * 3 * Q + i];
+    if (!down) return;
+    const int Sp = SL / 2, pgc = (int)o.lvl_off[o.L - 1] + (id / (SL * SL) * Sp + k2 / 2) * Sp + k1 / 2;
+    for (int i = threadIdx.x; i < 3 * Q; i += blockDim.x) par[i] = loc[(size_t)pgc * 3 * Q + i];
+    for (int i = threadIdx.x; i < 2 * Q; i += blockDim.x) T[i] = i < Q ? o.T0[i] : o.T1[i - Q];
+}
+
+__global__ __launch_bounds__(512) void k_l2p_leaf(DevOp o, int down, const double2 *loc, double2 *ybuf)
 {
     extern __shared__ double2 sm2[];
     const int id = blockIdx.x;
-    const int SL = o.SL, s = o.s, p = o.p, Q1 = o.Q1, Q = o.Q, RL = o.rowlen;
+    const int SL = o.SL, s = o.s, p = o.p, Q1 = o.Q1, Q = o.Q, RL = o.rowlen, QR = Q1 * RL;
     const int r = id % (SL * SL), k2 = r / SL, k1 = r % SL;
-    const int gc = (int)o.lvl_off[o.L] + id;
-    const double2 *t = loc + (size_t)gc * 3 * Q;
-    const double *Mpu = o.Mp + (size_t)k1 * Q1 * RL, *Mqu = o.Mq + (size_t)k1 * Q1 * RL, *Mdu = o.Mdp + (size_t)k1 * Q1 * RL;
-    const double *Mpv = o.Mp + (size_t)k2 * Q1 * RL, *Mqv = o.Mq + (size_t)k2 * Q1 * RL, *Mdv = o.Mdp + (size_t)k2 * Q1 * RL;
     double2 *W0 = sm2;                 // [Q1 (m2)][RL (i1)]  component 0 field + divergence
-    double2 *W1 = W0 + Q1 * RL;        // component 1 field
-    double2 *W1d = W1 + Q1 * RL;       // component 1 divergence
+    double2 *W1 = W0 + QR;             // component 1 field
+    double2 *W1d = W1 + QR;            // component 1 divergence
+    double2 *t = W1d + QR;             // [3][Q] the leaf's fields
+    double *M = reinterpret_cast<double *>(t + 3 * Q);   // Mp, Mq, Mdp of k1, then of k2
+    double2 *par = reinterpret_cast<double2 *>(M + 6 * QR + (6 * QR & 1)), *W = par + 3 * Q;   // with down only
+    double *T = reinterpret_cast<double *>(W + 3 * Q);
+    for (int i = threadIdx.x; i < 6 * QR; i += blockDim.x) {
+        const int a = i / QR, m = i - a * QR, k = a < 3 ? k1 : k2, b = a % 3;
+        M[i] = (b == 0 ? o.Mp : (b == 1 ? o.Mq : o.Mdp))[(size_t)k * QR + m];
+    }
+    leaf_read(o, down != 0, id, k1, k2, Q, loc, t, par, T);
+    __syncthreads();
+    if (down) leaf_l2l(o, k1, k2, Q1, Q, t, par, W, T, 0, 3);
+    const double *Mpu = M, *Mqu = M + QR, *Mdu = M + 2 * QR, *Mpv = M + 3 * QR, *Mqv = M + 4 * QR, *Mdv = M + 5 * QR;
     const int w1a = s + p, w1b = s + p - 1;
-    for (int i = threadIdx.x; i < Q1 * RL; i += blockDim.x) {
-        const int m2 = i / RL, i1 = i % RL;
-        double2 a = make_double2(0, 0), b = make_double2(0, 0), bd = make_double2(0, 0);
-        for (int m1 = 0; m1 < Q1; ++m1) {
-            const double2 f1 = t[m2 * Q1 + m1], f2 = t[Q + m2 * Q1 + m1], fd = t[2 * Q + m2 * Q1 + m1];
-            if (i1 < w1a) a = cadd(a, cadd(cscale(Mpu[m1 * RL + i1], f1), cscale(Mdu[m1 * RL + i1], fd)));
-            if (i1 < w1b) {
-                b = cadd(b, cscale(Mqu[m1 * RL + i1], f2));
-                bd = cadd(bd, cscale(Mqu[m1 * RL + i1], fd));
-            }
+    for (int i = threadIdx.x; i < 3 * QR; i += blockDim.x) {
+        const int g = i / QR, e = i - g * QR, m2 = e / RL, i1 = e - m2 * RL;
+        double2 a = make_double2(0, 0);
+        if (g == 0) {
+            if (i1 < w1a)
+                for (int m1 = 0; m1 < Q1; ++m1)
+                    a = cadd(a, cadd(cscale(Mpu[m1 * RL + i1], t[m2 * Q1 + m1]), cscale(Mdu[m1 * RL + i1], t[2 * Q + m2 * Q1 + m1])));
+        } else if (i1 < w1b) {
+            const double2 *f = t + g * Q + m2 * Q1;   // field 2, then the divergence
+            for (int m1 = 0; m1 < Q1; ++m1) a = cadd(a, cscale(Mqu[m1 * RL + i1], f[m1]));
         }
         W0[i] = a;
-        W1[i] = b;
-        W1d[i] = bd;
     }
     __syncthreads();
     double2 *Y = ybuf + (size_t)id * 2 * RL * RL;
@@ -709,20 +764,26 @@ __global__ __launch_bounds__(256) void k_l2p_leaf(DevOp o, const double2 *loc, d
 
 // scalar single layer: Y[i2][i1] = sum (M_p (x) M_p)^T t^d over the leaf's W x W window
 // (component 0 of the leaf's result rows)
-__global__ __launch_bounds__(256) void k_l2p_leaf_sc(DevOp o, const double2 *loc, double2 *ybuf)
+__global__ __launch_bounds__(512) void k_l2p_leaf_sc(DevOp o, int down, const double2 *loc, double2 *ybuf)
 {
     extern __shared__ double2 sm2[];
     const int id = blockIdx.x;
-    const int SL = o.SL, s = o.s, p = o.p, Q1 = o.Q1, Q = o.Q, RL = o.rowlen, W = s + p;
+    const int SL = o.SL, s = o.s, p = o.p, Q1 = o.Q1, Q = o.Q, RL = o.rowlen, W = s + p, QR = Q1 * RL;
     const int r = id % (SL * SL), k2 = r / SL, k1 = r % SL;
-    const int gc = (int)o.lvl_off[o.L] + id;
-    const double2 *t = loc + (size_t)gc * 3 * Q + 2 * Q;
-    const double *Mpu = o.Mp + (size_t)k1 * Q1 * RL, *Mpv = o.Mp + (size_t)k2 * Q1 * RL;
-    double2 *Wm = sm2;   // [Q1 (m2)][W (i1)]
+    double2 *Wm = sm2;       // [Q1 (m2)][W (i1)]
+    double2 *t = Wm + QR;    // [3][Q] the leaf's fields (the third one counts)
+    double *M = reinterpret_cast<double *>(t + 3 * Q);   // Mp of k1, then of k2
+    double2 *par = reinterpret_cast<double2 *>(M + 2 * QR), *Wd = par + 3 * Q;   // with down only
+    double *T = reinterpret_cast<double *>(Wd + Q);
+    for (int i = threadIdx.x; i < 2 * QR; i += blockDim.x) M[i] = o.Mp[(size_t)(i < QR ? k1 : k2) * QR + i % QR];
+    leaf_read(o, down != 0, id, k1, k2, Q, loc, t, par, T);
+    __syncthreads();
+    if (down) leaf_l2l(o, k1, k2, Q1, Q, t, par, Wd, T, 2, 1);
+    const double *Mpu = M, *Mpv = M + QR;
     for (int i = threadIdx.x; i < Q1 * W; i += blockDim.x) {
         const int m2 = i / W, i1 = i % W;
         double2 a = make_double2(0, 0);
-        for (int m1 = 0; m1 < Q1; ++m1) a = cadd(a, cscale(Mpu[m1 * RL + i1], t[m2 * Q1 + m1]));
+        for (int m1 = 0; m1 < Q1; ++m1) a = cadd(a, cscale(Mpu[m1 * RL + i1], t[2 * Q + m2 * Q1 + m1]));
         Wm[i] = a;
     }
     __syncthreads();
@@ -736,10 +797,9 @@ __global__ __launch_bounds__(256) void k_l2p_leaf_sc(DevOp o, const double2 *loc
     }
 }
 
-__global__ void k_l2p_gather(DevOp o, const double2 *ybuf, double2 *y)
+// contributions of the leaf clusters that the incarnations of unknown i touch
+__device__ __forceinline__ double2 l2p_sum(const DevOp &o, int i, const double2 *ybuf)
 {
-    const int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= o.N) return;
     const int s = o.s, p = o.p, SL = o.SL, n = o.n, RL = o.rowlen;
     double2 acc = make_double2(0, 0);
     for (int c = 0; c < 2; ++c) {
@@ -758,7 +818,38 @@ __global__ void k_l2p_gather(DevOp o, const double2 *ybuf, double2 *y)
                 acc = cadd(acc, cscale(sg, v));
             }
     }
-    y[i] = cadd(y[i], acc);
+    return acc;
+}
+
+__global__ void k_l2p_gather(DevOp o, const double2 *ybuf, double2 *y)
+{
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i >= o.N) return;
+    y[i] = cadd(y[i], l2p_sum(o, i, ybuf));
+}
+
+// k_near_gather and k_l2p_gather in one launch, the same sums in the same order
+__global__ __launch_bounds__(256) void k_gather(DevOp o, const int64_t *ptr, const int32_t *idx, const double2 *part,
+                                                const double2 *ybuf, double2 *y)
+{
+    const int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int i = (int)(t >> 4), sub = (int)(t & 15);
+    double re = 0.0, im = 0.0;
+    double2 far = make_double2(0.0, 0.0);
+    if (i < o.N) {
+        for (int64_t k = ptr[i] + sub; k < ptr[i + 1]; k += 16) {
+            const double2 v = part[idx[k]];
+            re += v.x;
+            im += v.y;
+        }
+        if (sub == 0) far = l2p_sum(o, i, ybuf);
+    }
+#pragma unroll
+    for (int off = 8; off >= 1; off >>= 1) {
+        re += __shfl_xor(re, off, 16);
+        im += __shfl_xor(im, off, 16);
+    }
+    if (i < o.N && sub == 0) y[i] = cadd(make_double2(re, im), far);
 }
 
 __global__ void k_helmholtz_eval(int64_t n, double kappa, const double *r2, double2 *out, int prec,
@@ -831,7 +922,8 @@ void launch_p2m(ige_op op, const double2 *x)
         return;
     }
     const int w1a = o.s + o.p, w2a = o.s + o.p - 1;
-    const size_t shm = sizeof(double2) * (2 * w1a * w2a + 3 * (size_t)(w1a) * o.Q1);
+    const size_t shm = sizeof(double2) * (2 * w1a * w2a + 3 * (size_t)(w1a) * o.Q1) + sizeof(double) * 6 * o.Q1 * o.rowlen;
+    lds_attr_once(reinterpret_cast<const void *>(&k_p2m), shm);
     hipLaunchKernelGGL(k_p2m, dim3(nleaf), dim3(256), shm, lstream(op), o, x, op->d_mom.p, op->d_src.p);
     IGE_LAUNCH_CHECK();
 }
@@ -839,12 +931,13 @@ void launch_p2m(ige_op op, const double2 *x)
 void launch_m2m(ige_op op)
 {
     const DevOp &o = op->view;
-    const size_t shm = sizeof(double2) * 24 * o.Q;
+    const size_t shm = sizeof(double2) * 25 * o.Q;
+    const int nth = std::min(1024, std::max((o.Q + 63) / 64 * 64, (12 * o.Q / 2 + 63) / 64 * 64));   // two values a thread
     lds_attr_once(reinterpret_cast<const void *>(&k_m2m), shm);
     // parents down to the coarsest level with far pairs (coarser moments are unused)
     for (int lvl = o.L - 1; lvl >= std::max(0, op->lfar); --lvl) {
         const int ncl = o.P << (2 * lvl);
-        hipLaunchKernelGGL(k_m2m, dim3(ncl), dim3(256), shm, lstream(op), o, lvl, op->d_mom.p, op->d_src.p);
+        hipLaunchKernelGGL(k_m2m, dim3(ncl), dim3(nth), shm, lstream(op), o, lvl, op->d_mom.p, op->d_src.p);
         IGE_LAUNCH_CHECK();
     }
     if (!o.varq) return;
@@ -935,17 +1028,21 @@ void launch_m2l_reduce(ige_op op, int prec)
     }
 }
 
-void launch_l2l(ige_op op)
+// children from level first to level last
+static void l2l_levels(ige_op op, int last)
 {
     const DevOp &o = op->view;
     const size_t shm = sizeof(double2) * 3 * o.Q;
     // children below the coarsest level with far pairs (the expansions above it are zero)
-    for (int lvl = std::max(1, op->lfar + 1); lvl <= o.L; ++lvl) {
+    for (int lvl = std::max(1, op->lfar + 1); lvl <= last; ++lvl) {
         const int ncl = o.P << (2 * lvl);
         hipLaunchKernelGGL(k_l2l, dim3(ncl), dim3(256), shm, lstream(op), o, lvl, op->d_loc.p);
         IGE_LAUNCH_CHECK();
     }
 }
+
+// the leaves' own level is left to launch_l2p_leaf
+void launch_l2l(ige_op op) { l2l_levels(op, op->view.L - 1); }
 
 int near_blk_u(int nF)
 {
@@ -993,15 +1090,28 @@ void launch_spmv(ige_op op, const double2 *x, double2 *y, hipStream_t st, hipEve
 void launch_l2p_leaf(ige_op op)
 {
     const DevOp &o = op->view;
-    const int nleaf = o.P * o.SL * o.SL;
+    const int nleaf = o.P * o.SL * o.SL, down = o.L >= std::max(1, op->lfar + 1) ? 1 : 0;
+    const size_t Q = o.Q, QR = (size_t)o.Q1 * o.rowlen;
     if (o.scalar) {
-        const size_t shm = sizeof(double2) * (size_t)o.Q1 * (o.s + o.p);
-        hipLaunchKernelGGL(k_l2p_leaf_sc, dim3(nleaf), dim3(256), shm, lstream(op), o, op->d_loc.p, op->d_ybuf.p);
+        const size_t shm = sizeof(double2) * (QR + 3 * Q + (down ? 4 * Q : 0)) + sizeof(double) * (2 * QR + (down ? 2 * Q : 0));
+        lds_attr_once(reinterpret_cast<const void *>(&k_l2p_leaf_sc), shm);
+        hipLaunchKernelGGL(k_l2p_leaf_sc, dim3(nleaf), dim3(256), shm, lstream(op), o, down, op->d_loc.p, op->d_ybuf.p);
         IGE_LAUNCH_CHECK();
         return;
     }
-    const size_t shm = sizeof(double2) * 3 * (size_t)o.Q1 * o.rowlen;
-    hipLaunchKernelGGL(k_l2p_leaf, dim3(nleaf), dim3(256), shm, lstream(op), o, op->d_loc.p, op->d_ybuf.p);
+    const size_t shm = sizeof(double2) * (3 * QR + 3 * Q + (down ? 6 * Q : 0)) + sizeof(double) * (6 * QR + 1 + (down ? 2 * Q : 0));
+    lds_attr_once(reinterpret_cast<const void *>(&k_l2p_leaf), shm);
+    const int nth = std::min<int>(512, (int)(3 * std::max(Q, QR) + 63) / 64 * 64);
+    hipLaunchKernelGGL(k_l2p_leaf, dim3(nleaf), dim3(nth), shm, lstream(op), o, down, op->d_loc.p, op->d_ybuf.p);
+    IGE_LAUNCH_CHECK();
+}
+
+// sums of a fused one-column apply: near-field partial results and leaf rows
+void launch_gather(ige_op op, double2 *y)
+{
+    const DevOp &o = op->view;
+    hipLaunchKernelGGL(k_gather, dim3((unsigned)(((int64_t)o.N * 16 + 255) / 256)), dim3(256), 0, lstream(op), o,
+                       op->d_cred_ptr.p, op->d_cred_idx.p, op->d_cpart.p, op->d_ybuf.p, y);
     IGE_LAUNCH_CHECK();
 }
 

@@ -371,6 +371,10 @@ void launch_m2l_reduce(ige_op op, int prec);
 void plan_m2l_sym(ige_op op, hipStream_t s, int chunk);
 void launch_m2l_sym(ige_op op);
 void launch_m2l_reduce_sym(ige_op op);
+// the same coupling with the near-field product's items in one launch, and both results' sums
+bool m2l_sym_near_ok(const ige_op_s *op);
+void launch_m2l_sym_near(ige_op op, const double2 *x);
+void launch_gather(ige_op op, double2 *y);
 void launch_l2l(ige_op op);
 // near-field product; records mid (if given) between the block pass and the reduction
 void launch_spmv(ige_op op, const double2 *x, double2 *y, hipStream_t st, hipEvent_t mid = nullptr);
