@@ -239,6 +239,24 @@ void near_batched(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t 
 // ---------------------------------------------------------------------------
 // P2M on the leaves (gather of the glued coefficients fused), kRB columns
 // ---------------------------------------------------------------------------
+// The transfers below are bound by latency and by the reads of their inner sums; the tables of
+// those sums come to shared memory with the fields (level 6, 64 columns: P2M 109 us with the
+// tables from global memory, 102 now; M2M 115 and 81; L2L 100 and 90; L2P 130 and 105).
+// moment tables of a leaf: Mp, Mq, Mdp of k1, then of k2, [Q1][RL] each
+__device__ __forceinline__ void leaf_tables(const DevOp &o, int k1, int k2, double *M)
+{
+    const int QR = o.Q1 * o.rowlen;
+    for (int i = threadIdx.x; i < 6 * QR; i += blockDim.x) {
+        const int a = i / QR, m = i - a * QR, b = a % 3;
+        M[i] = (b == 0 ? o.Mp : (b == 1 ? o.Mq : o.Mdp))[(size_t)(a < 3 ? k1 : k2) * QR + m];
+    }
+}
+// transfer matrices T0, T1, [Q1][Q1] each
+__device__ __forceinline__ void transfer_tables(const DevOp &o, double *T)
+{
+    for (int i = threadIdx.x; i < 2 * o.Q; i += blockDim.x) T[i] = i < o.Q ? o.T0[i] : o.T1[i - o.Q];
+}
+
 template <int kRB>
 __global__ __launch_bounds__(256) void k_p2m_b(DevOp o, int r, const double2 *xt, double2 *mom, double2 *src)
 {
@@ -254,6 +272,8 @@ __global__ __launch_bounds__(256) void k_p2m_b(DevOp o, int r, const double2 *xt
     double2 *Z1 = X2 + w2b * w1b * kRB;        // [w2a][Q1][kRB]
     double2 *Zd = Z1 + w2a * Q1 * kRB;
     double2 *Z2 = Zd + w2a * Q1 * kRB;         // [w2b][Q1][kRB]
+    double *Mt = reinterpret_cast<double *>(Z2 + w2b * Q1 * kRB);
+    leaf_tables(o, k1, k2, Mt);
     for (int i = threadIdx.x; i < w2a * w1a * kRB; i += blockDim.x) {
         const int c = i % kRB, t = i / kRB, i2 = t / w1a, i1 = t % w1a;
         const size_t off = (((size_t)j * 2 + 0) * o.nb + (k2 * s + i2)) * o.nb + (k1 * s + i1);
@@ -265,8 +285,8 @@ __global__ __launch_bounds__(256) void k_p2m_b(DevOp o, int r, const double2 *xt
         X2[i] = c < nc ? cscaleb((double)o.sgn[off], xt[(size_t)o.dof[off] * r + c0 + c]) : make_double2(0, 0);
     }
     __syncthreads();
-    const double *Mpu = o.Mp + (size_t)k1 * Q1 * RL, *Mqu = o.Mq + (size_t)k1 * Q1 * RL, *Mdu = o.Mdp + (size_t)k1 * Q1 * RL;
-    const double *Mpv = o.Mp + (size_t)k2 * Q1 * RL, *Mqv = o.Mq + (size_t)k2 * Q1 * RL, *Mdv = o.Mdp + (size_t)k2 * Q1 * RL;
+    const int QR = Q1 * RL;
+    const double *Mpu = Mt, *Mqu = Mt + QR, *Mdu = Mt + 2 * QR, *Mpv = Mt + 3 * QR, *Mqv = Mt + 4 * QR, *Mdv = Mt + 5 * QR;
     for (int i = threadIdx.x; i < w2a * Q1 * kRB; i += blockDim.x) {
         const int c = i % kRB, t = i / kRB, i2 = t / Q1, m1 = t % Q1;
         double2 z = make_double2(0, 0), zd = make_double2(0, 0);
@@ -372,12 +392,14 @@ __global__ __launch_bounds__(256) void k_m2m_b(DevOp o, int lvl, int r, double2 
     double2 *acc = sm2;               // [3 fields][Q][kRB]
     double2 *W = acc + 3 * QR;        // [3 fields][Q1 (n2)][Q1 (m1)][kRB] of one child
     double2 *X = W + 3 * QR;          // the child's three fields, staged at once (coalesced along columns)
+    double *Tt = reinterpret_cast<double *>(X + 3 * QR);
+    transfer_tables(o, Tt);
     for (int i = threadIdx.x; i < 3 * QR; i += blockDim.x) acc[i] = make_double2(0, 0);
     for (int ch = 0; ch < 4; ++ch) {
         const int c1 = ch & 1, c2 = ch >> 1;
         const int cgc = (int)o.lvl_off[lvl + 1] + (j * 2 * S + 2 * k2 + c2) * 2 * S + 2 * k1 + c1;
         const double2 *cm = mom + (size_t)cgc * 3 * Q * r;
-        const double *Tu = c1 ? o.T1 : o.T0, *Tv = c2 ? o.T1 : o.T0;
+        const double *Tu = Tt + c1 * Q, *Tv = Tt + c2 * Q;
         __syncthreads();
         for (int i = threadIdx.x; i < 3 * QR; i += blockDim.x) {
             const int c = i % kRB, t = i / kRB;   // t = f Q + q
@@ -667,10 +689,12 @@ __global__ __launch_bounds__(256) void k_l2l_b(DevOp o, int lvl, int r, double2 
     const int Sp = S / 2;
     const int pgc = (int)o.lvl_off[lvl - 1] + (j * Sp + k2 / 2) * Sp + k1 / 2;
     const int c1 = k1 & 1, c2 = k2 & 1;
-    const double *Tu = c1 ? o.T1 : o.T0, *Tv = c2 ? o.T1 : o.T0;
     const double2 *par = loc + (size_t)pgc * 3 * Q * r;
     double2 *W = sm2;                 // [3][Q1 (m2)][Q1 (n1)][kRB]
     double2 *X = W + 3 * Q * kRB;     // the parent's fields, staged once (coalesced along columns)
+    double *Tt = reinterpret_cast<double *>(X + 3 * Q * kRB);
+    const double *Tu = Tt + c1 * Q, *Tv = Tt + c2 * Q;
+    transfer_tables(o, Tt);
     for (int i = threadIdx.x; i < 3 * Q * kRB; i += blockDim.x) {
         const int c = i % kRB, t = i / kRB;
         X[i] = c < nc ? par[(size_t)t * r + c0 + c] : make_double2(0, 0);
@@ -703,12 +727,14 @@ __global__ __launch_bounds__(256) void k_l2p_leaf_b(DevOp o, int r, const double
     const int rr = id % (SL * SL), k2 = rr / SL, k1 = rr % SL;
     const int gc = (int)o.lvl_off[o.L] + id;
     const double2 *t = loc + (size_t)gc * 3 * Q * r;
-    const double *Mpu = o.Mp + (size_t)k1 * Q1 * RL, *Mqu = o.Mq + (size_t)k1 * Q1 * RL, *Mdu = o.Mdp + (size_t)k1 * Q1 * RL;
-    const double *Mpv = o.Mp + (size_t)k2 * Q1 * RL, *Mqv = o.Mq + (size_t)k2 * Q1 * RL, *Mdv = o.Mdp + (size_t)k2 * Q1 * RL;
     double2 *W0 = sm2;                    // [Q1][RL][kRB]
     double2 *W1 = W0 + Q1 * RL * kRB;
     double2 *W1d = W1 + Q1 * RL * kRB;
     double2 *T3 = W1d + Q1 * RL * kRB;    // the leaf's three fields [3][Q][kRB], read once
+    double *Mt = reinterpret_cast<double *>(T3 + 3 * Q * kRB);
+    leaf_tables(o, k1, k2, Mt);
+    const int QR = Q1 * RL;
+    const double *Mpu = Mt, *Mqu = Mt + QR, *Mdu = Mt + 2 * QR, *Mpv = Mt + 3 * QR, *Mqv = Mt + 4 * QR, *Mdv = Mt + 5 * QR;
     const int w1a = s + p, w1b = s + p - 1;
     for (int i = threadIdx.x; i < 3 * Q * kRB; i += blockDim.x) {
         const int c = i % kRB, tt = i / kRB;
@@ -920,7 +946,7 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
         } else {
             const size_t per = sizeof(double2) * (2 * w1a * w1a + 3 * w1a * o.Q1);
             const int rb = pick_rb(per);
-            IGE_RB_SWITCH(rb, k_p2m_b, dim3(nleaf, chunks(rb)), dim3(256), per * rb, s, o, r, xt, op->d_bmom.p,
+            IGE_RB_SWITCH(rb, k_p2m_b, dim3(nleaf, chunks(rb)), dim3(256), per * rb + sizeof(double) * 6 * o.Q1 * o.rowlen, s, o, r, xt, op->d_bmom.p,
                           op->d_bsrc.p);
         }
         mark(1);
@@ -928,7 +954,7 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
             const size_t per = sizeof(double2) * 9 * o.Q;   // accumulators, intermediate, staged child (3 fields each)
             const int rb = pick_rb(per);
             for (int lvl = o.L - 1; lvl >= std::max(0, op->lfar); --lvl) {   // as the single-column pass
-                IGE_RB_SWITCH(rb, k_m2m_b, dim3(o.P << (2 * lvl), chunks(rb)), dim3(256), per * rb, s, o, lvl, r,
+                IGE_RB_SWITCH(rb, k_m2m_b, dim3(o.P << (2 * lvl), chunks(rb)), dim3(256), per * rb + sizeof(double) * 2 * o.Q, s, o, lvl, r,
                               op->d_bmom.p, op->d_bsrc.p);
             }
         }
@@ -1007,7 +1033,7 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
             const size_t per = sizeof(double2) * 6 * o.Q;   // intermediate and staged parent
             const int rb = pick_rb(per);
             for (int lvl = std::max(1, op->lfar + 1); lvl <= o.L; ++lvl) {
-                IGE_RB_SWITCH(rb, k_l2l_b, dim3(o.P << (2 * lvl), chunks(rb)), dim3(256), per * rb, s, o, lvl, r,
+                IGE_RB_SWITCH(rb, k_l2l_b, dim3(o.P << (2 * lvl), chunks(rb)), dim3(256), per * rb + sizeof(double) * 2 * o.Q, s, o, lvl, r,
                               op->d_bloc.p);
             }
         }
@@ -1019,8 +1045,9 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
                           op->d_bybuf.p);
         } else {   // three intermediates and the staged fields
             const size_t per = sizeof(double2) * (3 * (size_t)o.Q1 * o.rowlen + 3 * (size_t)o.Q);
-            const int rb = pick_rb(per, 0, kLdsMax);
-            IGE_RB_SWITCH(rb, k_l2p_leaf_b, dim3(nleaf, chunks(rb)), dim3(256), per * rb, s, o, r, op->d_bloc.p,
+            const size_t fixed = sizeof(double) * 6 * o.Q1 * o.rowlen;
+            const int rb = pick_rb(per, fixed, kLdsMax);
+            IGE_RB_SWITCH(rb, k_l2p_leaf_b, dim3(nleaf, chunks(rb)), dim3(256), per * rb + fixed, s, o, r, op->d_bloc.p,
                           op->d_bybuf.p);
         }
         mark(6);
