@@ -374,7 +374,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)op->NC * Q * (9 * 8 + 11 * 16 * R);             // node data, moments, fields
     b += (size_t)op->T.far.size() * 4 * Q * 16 / 4 * R;          // coupling partials (chunks of partners)
     b += nfp * ((Q + 16 * kSymTiles - 1) / (16 * kSymTiles)) * 2 * 4 * Q * 16;   // one column: partials per unordered pair
-    b += (size_t)op->nsing * 24 + (size_t)D.N * 80 * R;
+    b += (size_t)op->nsing * 32 + (size_t)D.N * 80 * R;
     b += std::max((size_t)E * nl * 16, std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols)));   // right-hand side element moments
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
     b += (size_t)5 * 18 * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * 8;   // and rule
@@ -522,6 +522,29 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
                 }
                 for (size_t i = 1; i < sptr.size(); ++i) sptr[i] += sptr[i - 1];
                 op->d_sing_ptr.upload(sptr, s);
+                // pairs to compute: within one leaf (a block's pairs are ordered by test, then trial
+                // element) the first of each two that differ in the order of their elements
+                std::vector<int2> swk;
+                swk.reserve(sing.size());
+                for (size_t k0 = 0, k1; k0 < sing.size(); k0 = k1) {
+                    const int32_t blk = sing[k0].blk;
+                    for (k1 = k0; k1 < sing.size() && sing[k1].blk == blk; ++k1) {}
+                    const bool same = A.pair[2 * (size_t)blk] == A.pair[2 * (size_t)blk + 1];
+                    for (size_t k = k0; k < k1; ++k) {
+                        const int32_t e = sing[k].e, f = sing[k].f;
+                        if (!same || e == f) {
+                            swk.push_back(make_int2((int)k, -1));
+                        } else if (e < f) {
+                            const auto m = std::lower_bound(sing.begin() + k0, sing.begin() + k1, std::make_pair(f, e),
+                                                            [](const ige::SingularPair &a, const std::pair<int32_t, int32_t> &b) {
+                                                                return std::make_pair(a.e, a.f) < b;
+                                                            });
+                            IGE_REQUIRE(m != sing.begin() + k1 && m->e == f && m->f == e, "singular pair without its transpose");
+                            swk.push_back(make_int2((int)k, (int)(m - sing.begin())));
+                        }
+                    }
+                }
+                op->d_sing_work.upload(swk, s);
             }
             op->d_sblk.alloc(ige::near_singular_scratch(op));
             v.sing = op->d_sing.p; v.sing_ptr = op->d_sing_ptr.p; v.sblk = op->d_sblk.p;
@@ -906,7 +929,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_nb3.bytes() + op->d_xnb.bytes() + op->d_nbpart.bytes() + op->d_nbwork.bytes();
         b += op->d_nbpartner.bytes() + op->d_nbslot.bytes() + op->d_nborder.bytes() + op->d_nbred_ptr.bytes();
         b += op->d_nbred_idx.bytes() + op->d_morder.bytes();
-        b += op->d_Mp.bytes() * 3 + op->d_inc.bytes() + op->d_sing.bytes() + op->d_work.bytes();
+        b += op->d_Mp.bytes() * 3 + op->d_inc.bytes() + op->d_sing.bytes() + op->d_sing_work.bytes() + op->d_work.bytes();
         b += op->d_work1.bytes() + op->d_wrk_of_tgt1.bytes() + op->d_wrk_of_tgt.bytes();
         b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes() + op->d_part.bytes();
         b += op->d_swork.bytes() + op->d_spartner.bytes() + op->d_sred_ptr.bytes() + op->d_sred_idx.bytes() + op->d_spart.bytes();

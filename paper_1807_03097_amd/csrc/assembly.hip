@@ -351,14 +351,16 @@ __global__ __launch_bounds__(256) void k_singular_rule(DevOp o, double *rule)
 // and the two tangents; the products Psi_l^c are formed as they are read, so a row is half
 // as long and twice the waves fit.  Control points and spline coefficients of the two elements
 // are kept in shared memory, the points come from the rule's table.
+// The form and the rules are symmetric: of two pairs that differ in the order of their elements
+// (both are listed where they lie in one leaf) one is computed, the other its transpose.
 // GD: degree in both directions of all patches of the surface (1 or 2; 0: any, out of line)
 // Bound by FP64 issue: two instructions of 64 cycles per point and 400 vector FP64 operations
 // per batch (two of the longest at a time on a SIMD).  Before, a point's rule came from five
 // integer divisions, every coefficient and control point from global memory, eleven FP64
 // divisions, and its rows (48 values per side) left room for six waves per CU: sphere level 5,
-// p = 2, 5 Gauss points (160 million points): 45.5 ms, 19.2 now.
+// p = 2, 5 Gauss points (160 million points): 45.5 ms, 19.2 then, 13.1 with one of each two pairs.
 template <int P, bool SC, int GD>
-__global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPair *list, const double *rule)
+__global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPair *list, const int2 *work, const double *rule)
 {
     // points per batch: 32 (16 for p = 4, whose 40 local functions would not fit);
     // SC: the scalar operator's (p+1)^2 local functions
@@ -372,7 +374,8 @@ __global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPai
     __shared__ double sX[NB][3];
     __shared__ double sExt[2][2][NE];   // spline coefficients by side and direction: degree p, degree p - 1
     __shared__ double sCp[2][NC];       // control points of the element's span, by side
-    const SingularPair sp = list[blockIdx.x];
+    const int2 wk = work[blockIdx.x];   // the pair and the one with the elements exchanged (-1: none listed)
+    const SingularPair sp = list[wk.x];
     const int lane = threadIdx.x, half = lane >> 5, qi = lane & 31;
     int ja, a1, a2, jb, b1, b2;
     elem_of(o, sp.e, ja, a1, a2);
@@ -531,7 +534,7 @@ __global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPai
     }
     // lane holds B[16 u + lane/16 + 4 j][16 v + lane % 16]; the element-pair block goes
     // to its own slot, added to the near-field block by k_near_regular in list order
-    double2 *dst = o.sblk + (size_t)blockIdx.x * NL * NL;
+    double2 *dst = o.sblk + (size_t)wk.x * NL * NL, *tr = o.sblk + (size_t)max(wk.y, 0) * NL * NL;
 #pragma unroll
     for (int u = 0; u < LT; ++u)
 #pragma unroll
@@ -539,7 +542,10 @@ __global__ __launch_bounds__(64) void k_near_singular(DevOp o, const SingularPai
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const int l = 16 * u + (lane >> 4) + 4 * j, lb = 16 * v + (lane & 15);
-                if (l < NL && lb < NL) dst[l * NL + lb] = make_double2(br[u][v][j], bi[u][v][j]);
+                if (l >= NL || lb >= NL) continue;
+                const double2 b = make_double2(br[u][v][j], bi[u][v][j]);
+                dst[l * NL + lb] = b;
+                if (wk.y >= 0) tr[lb * NL + l] = b;
             }
 }
 
@@ -628,11 +634,11 @@ template <int P, bool SC>
 void launch_near_singular_p(ige_op op, int gd, const double *rule)
 {
     const DevOp &o = op->view;
-    const dim3 grid((unsigned)op->nsing), blk(64);
+    const dim3 grid((unsigned)op->d_sing_work.n), blk(64);
     hipStream_t s = lstream(op);
-    if (gd == 1) hipLaunchKernelGGL((k_near_singular<P, SC, 1>), grid, blk, 0, s, o, op->d_sing.p, rule);
-    else if (gd == 2) hipLaunchKernelGGL((k_near_singular<P, SC, 2>), grid, blk, 0, s, o, op->d_sing.p, rule);
-    else hipLaunchKernelGGL((k_near_singular<P, SC, 0>), grid, blk, 0, s, o, op->d_sing.p, rule);
+    if (gd == 1) hipLaunchKernelGGL((k_near_singular<P, SC, 1>), grid, blk, 0, s, o, op->d_sing.p, op->d_sing_work.p, rule);
+    else if (gd == 2) hipLaunchKernelGGL((k_near_singular<P, SC, 2>), grid, blk, 0, s, o, op->d_sing.p, op->d_sing_work.p, rule);
+    else hipLaunchKernelGGL((k_near_singular<P, SC, 0>), grid, blk, 0, s, o, op->d_sing.p, op->d_sing_work.p, rule);
     IGE_HIP(hipGetLastError());
 }
 }  // namespace

@@ -206,6 +206,7 @@ struct ige_op_s {
     ige::DBuf<double2> d_sctab;
     ige::DBuf<int32_t> d_inc;
     ige::DBuf<ige::SingularPair> d_sing;
+    ige::DBuf<int2> d_sing_work;         // pairs to compute, each with its transpose's place or -1
     ige::DBuf<double2> d_sblk;           // singular element-pair blocks (assembly only)
     ige::DBuf<int32_t> d_sing_ptr;
     ige::DBuf<ige::M2LWork> d_work;
