@@ -375,7 +375,7 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
     b += (size_t)op->T.far.size() * 4 * Q * 16 / 4 * R;          // coupling partials (chunks of partners)
     b += nfp * ((Q + 16 * kSymTiles - 1) / (16 * kSymTiles)) * 2 * 4 * Q * 16;   // one column: partials per unordered pair
     b += (size_t)op->nsing * 32 + (size_t)D.N * 80 * R;
-    b += std::max((size_t)E * nl * 16, std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols)));   // right-hand side element moments
+    b += std::max((size_t)E * nl * 16, (size_t)16 << 20) + ((size_t)32 << 20) + std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols));   // right-hand side element moments, potential
     b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
     b += (size_t)5 * 18 * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * 8;   // and rule
     b += ((size_t)restart + 1 + 8) * D.N * 16 * R;               // Krylov basis and work vectors
@@ -823,7 +823,8 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // (the upward pass stops there) but the matrix-core coupling stages them
             IGE_HIP(hipMemsetAsync(op->d_src.p, 0, op->d_src.bytes(), s));
             op->d_loc.alloc((size_t)op->NC * 3 * v.Q);
-            op->d_rhs.alloc(ige::rhs_scratch_values(v, 1));
+            op->rhs_n = ige::rhs_base_values(op);
+            op->d_rhs.alloc(op->rhs_n + ige::pot_base_values(op));
             op->d_ybuf.alloc((size_t)D.P * v.SL * v.SL * 2 * F.rowlen * F.rowlen);
             op->d_part.alloc(std::max<size_t>(1, op->work1.size()) * 4 * v.Q);
             // one FP64 column: the coupling over unordered pairs; IGE_M2L_SYM=1 takes
@@ -933,7 +934,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_work1.bytes() + op->d_wrk_of_tgt1.bytes() + op->d_wrk_of_tgt.bytes();
         b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes() + op->d_part.bytes();
         b += op->d_swork.bytes() + op->d_spartner.bytes() + op->d_sred_ptr.bytes() + op->d_sred_idx.bytes() + op->d_spart.bytes();
-        b += op->d_rhs.bytes() + op->d_pot.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
+        b += op->d_rhs.bytes() + op->d_rhs_more.bytes() + op->d_pot.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
         b += op->d_cnr.bytes() + op->d_cnc.bytes() + op->d_cld.bytes() + op->d_cidx.bytes() + op->d_corder.bytes() + op->d_cred_idx.bytes();
         b += op->d_cocc_ptr.bytes() + op->d_cocc.bytes() + op->d_cnp_ptr.bytes() + op->d_cnp_leaf.bytes();
         b += op->d_cnp_code.bytes() + op->d_csym.bytes() + op->d_cvoff.bytes() + op->d_clst.bytes();
@@ -1340,8 +1341,9 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
 
 namespace {
 // right-hand sides of r columns, up to kRhsCols per launch.  The scratch of the element
-// moments holds one column from the assembly on and grows to the columns of a launch (at most
-// 256 MiB, or one column), except while the caller captures the stream, where it serves as it is
+// moments holds at least one column from the assembly on; where it does not hold those of a launch a
+// second one does (at most 256 MiB), except while the caller captures the stream: the first
+// then serves as it is and stays where it is
 void rhs_columns(ige_op op, int r, int kind, const double *a, const double2 *pol, ige_c64 *f, int ptr_kind)
 {
     set_device(op->ctx);
@@ -1350,14 +1352,20 @@ void rhs_columns(ige_op op, int r, int kind, const double *a, const double2 *pol
     const size_t one = ige::rhs_scratch_values(op->view, 1);
     const int fit = (int)std::max<size_t>(1, ((size_t)256 << 20) / (sizeof(double2) * one));
     int nc = std::min({r, ige::kRhsCols, fit});
-    if (op->d_rhs.n < one * nc) {
+    double2 *scr = op->d_rhs.p;
+    size_t nscr = op->rhs_n;
+    if (nscr < one * nc) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         IGE_HIP(hipStreamIsCapturing(s, &cap));
         if (cap == hipStreamCaptureStatusNone) {
-            IGE_HIP(hipStreamSynchronize(s));   // a launch that uses the old scratch may be in flight
-            op->d_rhs.alloc(one * nc);
+            if (op->d_rhs_more.n < one * nc) {
+                IGE_HIP(hipStreamSynchronize(s));   // a launch that uses the old one may be in flight
+                op->d_rhs_more.alloc(one * nc);
+            }
+            scr = op->d_rhs_more.p;
+            nscr = op->d_rhs_more.n;
         } else {
-            nc = (int)(op->d_rhs.n / one);
+            nc = (int)(nscr / one);
         }
     }
     if (ptr_kind == IGE_HOST && op->d_by.n < (size_t)N * nc) op->d_by.alloc((size_t)N * nc);
@@ -1365,7 +1373,7 @@ void rhs_columns(ige_op op, int r, int kind, const double *a, const double2 *pol
         const int k = std::min(nc, r - c);
         double2 *fc = reinterpret_cast<double2 *>(f) + (size_t)c * N;
         double2 *dst = ptr_kind == IGE_HOST ? op->d_by.p : fc;
-        ige::launch_rhs(op, kind, k, a + 3 * c, pol ? pol + 3 * c : nullptr, dst);
+        ige::launch_rhs(op, kind, k, a + 3 * c, pol ? pol + 3 * c : nullptr, dst, scr, nscr);
         if (ptr_kind == IGE_HOST) {
             IGE_HIP(hipMemcpyAsync(fc, dst, sizeof(double2) * N * k, hipMemcpyDeviceToHost, s));
             IGE_HIP(hipStreamSynchronize(s));
@@ -1823,11 +1831,15 @@ int ige_potential(ige_op op, int r, const ige_c64 *w, int ptr_kind, int npts, co
         const size_t nout = (size_t)3 * npts, nsrc = ige::potential_source_doubles(op);
         const size_t npart = parts > 1 ? nout * parts : 0, nw = ptr_kind == IGE_HOST ? (size_t)r * N : 0;
         const size_t need = 2 * (npart + nout + nw) + nsrc + nout;
-        if (op->d_pot.n < need) {
-            IGE_HIP(hipStreamSynchronize(s));
-            op->d_pot.alloc(need);
+        double *wsp = reinterpret_cast<double *>(op->d_rhs.p + op->rhs_n);   // where that holds it
+        if (2 * (op->d_rhs.n - op->rhs_n) < need) {
+            if (op->d_pot.n < need) {
+                IGE_HIP(hipStreamSynchronize(s));
+                op->d_pot.alloc(need);
+            }
+            wsp = op->d_pot.p;
         }
-        double2 *dpart = reinterpret_cast<double2 *>(op->d_pot.p), *dout = dpart + npart, *dw = dout + nout;
+        double2 *dpart = reinterpret_cast<double2 *>(wsp), *dout = dpart + npart, *dw = dout + nout;
         double *dsrc = reinterpret_cast<double *>(dw + nw), *dpts = dsrc + nsrc;
         if (npts) IGE_HIP(hipMemcpyAsync(dpts, points, sizeof(double) * nout, hipMemcpyHostToDevice, s));
         const double2 *W = reinterpret_cast<const double2 *>(w);

@@ -125,10 +125,19 @@ __global__ __launch_bounds__(256) void k_rhs_sum(DevOp o, int nc, const double2 
 
 size_t rhs_scratch_values(const DevOp &o, int nc) { return (size_t)o.P * o.n * o.n * o.nl * nc; }
 
-void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f)
+// What the operator keeps from its assembly on: element moments of one column or of as many as a
+// launch takes within 16 MiB, and a potential's workspace within 32 MiB
+size_t rhs_base_values(ige_op op)
+{
+    const size_t one = rhs_scratch_values(op->view, 1), most = ((size_t)16 << 20) / sizeof(double2);
+    return std::max(one, std::min(most, kRhsCols * one));
+}
+size_t pot_base_values(ige_op op) { return std::min(((size_t)32 << 20) / sizeof(double2), potential_source_doubles(op) / 2 + 65536); }
+
+void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f, double2 *scr, size_t nscr)
 {
     const DevOp &o = op->view;
-    IGE_REQUIRE(nc >= 1 && nc <= kRhsCols && op->d_rhs.n >= rhs_scratch_values(o, nc), "right-hand side scratch too small");
+    IGE_REQUIRE(nc >= 1 && nc <= kRhsCols && nscr >= rhs_scratch_values(o, nc), "right-hand side scratch too small");
     RhsCols cols{};
     for (int c = 0; c < nc; ++c)
         for (int d = 0; d < 3; ++d) {
@@ -142,10 +151,10 @@ void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol
     const dim3 grid((unsigned)((E + ne - 1) / ne));
     const size_t shm = sizeof(double2) * 16 * o.G2;
     hipStream_t s = lstream(op);
-    if (o.scalar) hipLaunchKernelGGL(k_rhs_elem<true>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, op->d_rhs.p);
-    else hipLaunchKernelGGL(k_rhs_elem<false>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, op->d_rhs.p);
+    if (o.scalar) hipLaunchKernelGGL(k_rhs_elem<true>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, scr);
+    else hipLaunchKernelGGL(k_rhs_elem<false>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, scr);
     IGE_HIP(hipGetLastError());
-    hipLaunchKernelGGL(k_rhs_sum, dim3((unsigned)(((int64_t)o.N * nc + 255) / 256)), dim3(256), 0, s, o, nc, op->d_rhs.p, f);
+    hipLaunchKernelGGL(k_rhs_sum, dim3((unsigned)(((int64_t)o.N * nc + 255) / 256)), dim3(256), 0, s, o, nc, scr, f);
     IGE_HIP(hipGetLastError());
 }
 

@@ -267,7 +267,10 @@ struct ige_op_s {
     ige::DBuf<double2> d_ybuf;   // [leaves][2][rowlen][rowlen] L2P results per leaf
     ige::DBuf<double2> d_x, d_y; // staging for host pointers
     ige::DBuf<double> d_pot;     // workspace of the potential: sources, points, results, parts
-    ige::DBuf<double2> d_rhs;    // element moments of the right-hand sides [E][nl][columns]
+    // element moments of the right-hand sides [E][nl][columns], then a potential's workspace: from
+    // the assembly on and never replaced (captured launches refer to it); moments of more columns
+    size_t rhs_n = 0;
+    ige::DBuf<double2> d_rhs, d_rhs_more;
     // batched-apply workspaces (r columns, column index innermost)
     int bcap = 0;
     ige::DBuf<double2> d_bnpart;       // near-field partial results [nslots][rb]
@@ -403,7 +406,9 @@ void lds_attr_once(const void *kern, size_t shm);
 // element moments in d_rhs
 constexpr int kRhsCols = 16;
 size_t rhs_scratch_values(const DevOp &o, int nc);
-void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f);
+void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f, double2 *scr, size_t nscr);
+size_t rhs_base_values(ige_op op);
+size_t pot_base_values(ige_op op);
 // GMRES vector kernels (V: [k][r][n], vectors [r][n]; gate/run/flag: per-column int masks)
 struct GsPlan {
     int nchk = 0, nblk = 0;             // entry chunks of the dot and blocks of the update kernel
