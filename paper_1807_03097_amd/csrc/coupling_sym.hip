@@ -392,6 +392,9 @@ void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
     const double near_us = (double)op->cmp.nval * 16.0 / 4.7e6, far_us = steps * 340.0 / (1024.0 * 2400.0);
     std::vector<int32_t> spart;
     op->swork.clear();
+    // each pair is visited from the cluster of smaller index alone
+    const auto upper = std::count_if(T.far.begin(), T.far.end(), [](const auto &f) { return f[2] > f[1]; });
+    IGE_REQUIRE(2 * (size_t)upper == T.far.size(), "far pairs are not symmetric");
     int rt = 1;
     for (const auto &f : T.far) rt = std::max(rt, ((F.ql[f[0]] + 1) * (F.ql[f[0]] + 1) + 15) / 16);   // node tiles of a cluster
     rt = 2 * ((std::min(rt, kSymTiles) + 1) / 2);
