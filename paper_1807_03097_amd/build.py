@@ -23,7 +23,7 @@ FLAGS = [
 # accumulation registers and copy them there and back around every loop (a loop of eight
 # 16x16x4 FP64 products: 47 TFLOP/s with the copies, 78 without).
 MFMA_VGPR = ["-mllvm", "-amdgpu-mfma-vgpr-form=1"]
-FILE_FLAGS = {"assembly.hip": MFMA_VGPR, "coupling_sym.hip": MFMA_VGPR, "coupling_gen.hip": MFMA_VGPR, "near_cols.hip": MFMA_VGPR}
+FILE_FLAGS = {"assembly.hip": MFMA_VGPR, "coupling_sym.hip": MFMA_VGPR, "coupling_gen.hip": MFMA_VGPR, "near_cols.hip": MFMA_VGPR, "fields.hip": MFMA_VGPR}
 
 
 # host-code sanitizer variants (the device code is compiled as usual): used by the CPU

@@ -16,6 +16,7 @@ namespace {
 
 using dm::cadd;
 using dm::cscale;
+typedef double dx4 __attribute__((ext_vector_type(4)));
 
 // the columns of one launch: direction or source point, and the polarisation (EFIE)
 struct RhsCols {
@@ -33,7 +34,7 @@ struct RhsCols {
 // Bound by the sines and cosines (one per element point and column) and by the
 // products; one thread per unknown and column evaluated each of them for all of its
 // (up to nine, p = 2) elements again and read Psi across unknowns: 64 waves on 24,576
-// elements (p = 2, 5 x 5 points) 24.2 ms before, 0.69 ms now.
+// elements (p = 2, 5 x 5 points) 24.2 ms then, 0.67 ms in this form alone.
 template <bool SC>
 __global__ __launch_bounds__(256) void k_rhs_elem(DevOp o, int64_t E, int rw, int nc, int kind, RhsCols cols, double2 *loc)
 {
@@ -94,6 +95,72 @@ __global__ __launch_bounds__(256) void k_rhs_elem(DevOp o, int64_t E, int rw, in
     }
 }
 
+// The same for more than eight columns and up to 16 local functions, on the FP64 matrix instruction: a
+// wave takes one element.  Per step of four Gauss points lane (hi, n) evaluates point 4 t + hi of column
+// n, which is operand B as it stands; the stored operand of the 16 local functions at the four
+// points is operand A, one product per component of the tested field and for the real and the
+// imaginary parts.
+// Bound by the sines and cosines (seven per lane at 5 x 5 points), FP64 issue and the 11 KB of
+// operands per element, which are read in whole lines (from the row layout, 16 rows of 200 bytes
+// at a time, 16 columns took 135 us).  24,576 elements of 12 functions, with the sum: 16 columns 171 us
+// in the form above, 102 here; 12 columns 154 and 98; 64 columns 674 and 393.
+template <bool SC>
+__global__ __launch_bounds__(256) void k_rhs_mx(DevOp o, int64_t E, int nc, int kind, RhsCols cols, double2 *loc)
+{
+    constexpr int ND = SC ? 1 : 3;
+    const int G2 = o.G2, NL = o.nl, lane = threadIdx.x & 63, n = lane & 15, hi = lane >> 4;
+    const int64_t e = (int64_t)blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    if (e >= E) return;   // the whole wave
+    const int c = min(n, nc - 1), T = 4 * ((G2 + 15) / 16);
+    const double a0 = cols.a[c][0], a1 = cols.a[c][1], a2 = cols.a[c][2];
+    const double *X = o.eX + e * 3 * G2, *F = o.ePsiF + (e * 4 + (SC ? 3 : 0)) * T * 64 + lane;
+    dx4 re[ND], im[ND];
+#pragma unroll
+    for (int d = 0; d < ND; ++d) re[d] = im[d] = dx4{0.0, 0.0, 0.0, 0.0};
+    for (int t = 0; 4 * t < G2; ++t) {
+        const int q = 4 * t + hi, qc = min(q, G2 - 1);
+        double A[ND];
+#pragma unroll
+        for (int d = 0; d < ND; ++d) A[d] = F[(d * T + t) * 64];
+        const double x0 = X[qc], x1 = X[G2 + qc], x2 = X[2 * G2 + qc];
+        double2 g;
+        double sn, cs;
+        if (!SC || kind == 0) {
+            sincos(o.kappa * (a0 * x0 + a1 * x1 + a2 * x2), &sn, &cs);
+            g = make_double2(cs, sn);
+        } else {
+            const double d0 = x0 - a0, d1 = x1 - a1, d2 = x2 - a2;
+            const double r = sqrt(d0 * d0 + d1 * d1 + d2 * d2);
+            sincos(o.kappa * r, &sn, &cs);
+            const double f = 0.07957747154594767 / r;   // 1 / (4 pi r)
+            g = make_double2(cs * f, sn * f);
+        }
+        if (q >= G2) g = make_double2(0.0, 0.0);
+#pragma unroll
+        for (int d = 0; d < ND; ++d) {
+            re[d] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[d], g.x, re[d], 0, 0, 0);
+            im[d] = __builtin_amdgcn_mfma_f64_16x16x4f64(A[d], g.y, im[d], 0, 0, 0);
+        }
+    }
+    if (n >= nc) return;
+    // lane: column n, functions hi + 4 j
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int l = hi + 4 * j;
+        if (l >= NL) continue;
+        double2 v;
+        if constexpr (SC) {
+            v = make_double2(re[0][j], im[0][j]);
+        } else {
+            v = make_double2(0.0, 0.0);
+#pragma unroll
+            for (int d = 0; d < 3; ++d) v = cadd(v, dm::cmul(cols.pol[c][d], make_double2(re[d][j], im[d][j])));
+            v = make_double2(-v.x, -v.y);
+        }
+        loc[((size_t)e * NL + l) * nc + n] = v;
+    }
+}
+
 // f[c][i] = sum of the element moments of unknown i (incarnations, then elements row by
 // row), with the gluing sign; columns innermost over the threads
 __global__ __launch_bounds__(256) void k_rhs_sum(DevOp o, int nc, const double2 *loc, double2 *f)
@@ -151,7 +218,14 @@ void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol
     const dim3 grid((unsigned)((E + ne - 1) / ne));
     const size_t shm = sizeof(double2) * 16 * o.G2;
     hipStream_t s = lstream(op);
-    if (o.scalar) hipLaunchKernelGGL(k_rhs_elem<true>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, scr);
+    // The matrix form always works on 16 columns and 16 functions: from nine columns on, where the other
+    // pads to 16 as well (8 columns: 87 us there, 91 here; 12: 154 and 98); 24 functions in two
+    // tiles leave two waves per SIMD (16 columns: 53 and 58)
+    const bool mx = nc > 8 && o.nl <= 16;
+    const dim3 gm((unsigned)((E + 3) / 4));
+    if (mx && o.scalar) hipLaunchKernelGGL(k_rhs_mx<true>, gm, dim3(256), 0, s, o, E, nc, kind, cols, scr);
+    else if (mx) hipLaunchKernelGGL(k_rhs_mx<false>, gm, dim3(256), 0, s, o, E, nc, kind, cols, scr);
+    else if (o.scalar) hipLaunchKernelGGL(k_rhs_elem<true>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, scr);
     else hipLaunchKernelGGL(k_rhs_elem<false>, grid, dim3(256), shm, s, o, E, rw, nc, kind, cols, scr);
     IGE_HIP(hipGetLastError());
     hipLaunchKernelGGL(k_rhs_sum, dim3((unsigned)(((int64_t)o.N * nc + 255) / 256)), dim3(256), 0, s, o, nc, scr, f);

@@ -39,6 +39,28 @@ def test_rhs_columns(kind, p, level, r):
 
 
 @pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("p,level,g,r", [(1, 1, 1, 9), (1, 2, 2, 11), (2, 1, 3, 13), (2, 2, 4, 16), (2, 1, 8, 8), (3, 1, 5, 15),
+                                         (2, 3, 6, 10), (4, 1, 5, 12)])
+def test_rhs_ragged_columns(kind, p, level, g, r):
+    # 8 to 16 columns, quadrature orders that fill a step of four points exactly, by one point and
+    # less; at most 64 points per element: 1e-13 as above
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B, workloads as W
+    pats = W.cube_sphere()
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    sc = kind == "scalar"
+    op = B.Operator(geom, p, level, 3.0, 4, 1.0, g, 3, 1, kind=B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE)
+    o = O.Oracle(pats, p, level, 3.0, g=g, gs=3, scalar=sc)
+    dirs, pols = W.random_plane_waves(r, 7 + r)
+    F = op.rhs_scalar(B.IGE_RHS_PLANE, dirs) if sc else op.rhs_plane_wave(dirs, pols)
+    for c in range(r):
+        ref = o.rhs_scalar("plane", dirs[c]) if sc else o.rhs_plane_wave(dirs[c], pols[c])
+        assert _rel(F[c], ref) < 1e-13
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
 @pytest.mark.parametrize("p,level,npts", [(1, 1, 1), (2, 3, 3), (2, 2, 4), (3, 2, 5), (1, 4, 257)])
 def test_potential_points(kind, p, level, npts):
     # 1e-13: as above, the sum of E x 25 terms; the kernel value itself is good to 1.2 ulp of
