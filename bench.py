@@ -105,19 +105,19 @@ def log(*a):
 
 def load_traffic(r, kernel):
     """HBM bytes per launch of the near-field product from the committed counter
-    summary, valid only while the source file of that kernel is the one the counters
+    summary, valid only while the source files of that kernel are those the counters
     were taken on."""
     import hashlib
-    files = {"k_near_cmp": ("k_near_cmp_sphere_l5_p2_traffic.json", "near_once.hip"),
-             "k_near_blk": ("k_near_blk_sphere_l5_p2_traffic.json", "kernels.hip")}
+    files = {"k_near_cmp": ("k_near_cmp_sphere_l5_p2_traffic.json", ("near_once.hip", "near_item.hpp")),
+             "k_near_blk": ("k_near_blk_sphere_l5_p2_traffic.json", ("kernels.hip",))}
     if r != 1 or kernel not in files:
         return None
     path = os.path.join(ROOT, "profiles", files[kernel][0])
-    src = os.path.join(ROOT, "paper_1807_03097_amd", "csrc", files[kernel][1])
+    src = [os.path.join(ROOT, "paper_1807_03097_amd", "csrc", f) for f in files[kernel][1]]
     if not os.path.exists(path):
         return None
     ref = json.load(open(path))
-    h = hashlib.sha256(open(src, "rb").read()).hexdigest()
+    h = hashlib.sha256(b"".join(open(f, "rb").read() for f in src)).hexdigest()
     return ref["traffic_bytes"] if ref.get("source_sha256", ref.get("kernels_hip_sha256")) == h else None
 
 
@@ -616,7 +616,7 @@ def main():
         flops = entries * (14.0 + 32.0 * r)
         t_ms = stage_ms["m2l_kernel"]
         achieved = flops / (t_ms * 1e-3) / 1e12
-        return {"kernel": "k_m2l", "bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
+        return {"kernel": "k_m2l" if args.prec else "k_m2l_sym", "bound": "alu", "achieved": achieved, "peak": FP64_VECTOR_PEAK_TFLOPS,
                 "unit": "TFLOP/s", "frac": achieved / FP64_VECTOR_PEAK_TFLOPS, "traffic": None,
                 "node_pairs": int(entries), "avg_ms": t_ms}
 
