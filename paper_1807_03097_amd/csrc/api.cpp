@@ -1052,7 +1052,7 @@ void ensure_batched(ige_op op, int r)
     op->d_bsrc.alloc((size_t)op->NC * 4 * Q * r);
     IGE_HIP(hipMemsetAsync(op->d_bsrc.p, 0, op->d_bsrc.bytes(), op->ctx->stream));   // as d_src
     op->d_bloc.alloc((size_t)op->NC * 3 * Q * r);
-    op->d_bpart.alloc(std::max<size_t>(1, op->work.size()) * 4 * Q * r);
+    op->d_bpart.alloc(std::max<size_t>({1, op->work.size(), op->mwork.size()}) * 4 * Q * r);   // partials of either list
     op->d_bybuf.alloc((size_t)v.P * v.SL * v.SL * 2 * v.rowlen * v.rowlen * r);
     op->d_bxt.alloc((size_t)v.N * r);
     op->d_bnpart.alloc(std::max<size_t>(1, (size_t)v.nblk * v.nF * (1 + v.nch)) * 4);

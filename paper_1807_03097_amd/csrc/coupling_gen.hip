@@ -13,7 +13,7 @@ namespace {
 
 typedef double dx4 __attribute__((ext_vector_type(4)));
 
-// One workgroup per work item (cluster t, up to 8 partners) and column chunk; wave w takes the
+// One workgroup per work item (cluster t, up to 8 or 32 partners) and column chunk; wave w takes the
 // rows 16 w .. 16 w + 15 of t.  In a step a wave evaluates 16 rows x 4 nodes of G, one value per
 // lane, which is the A operand as it stands; a tile of the B operand holds 8 complex columns as
 // [Re V | Im V] against Re G and [-Im V | Re V] against Im G, so the accumulators are [Re U | Im U].
@@ -199,9 +199,11 @@ void m2l_generate(ige_op op, int r, const double2 *src, hipStream_t s)
     // 8): the workgroups' waves then load every SIMD alike
     const int nrow = (Q + 15) / 16, ks = nrow == 2 || nrow == 6 ? 2 : 1;
     const bool lng = m2l_gen_long(op, r);
+    const size_t items = lng ? op->mwork.size() : op->work.size();
+    IGE_REQUIRE(op->d_bpart.n >= items * 4 * (size_t)o.Q * r, "coupling partials too small");
     const auto *work = lng ? op->d_mwork.p : op->d_work.p;
     const int32_t *partner = lng ? op->d_mpartner.p : op->d_partner.p;
-    const dim3 grid((unsigned)(lng ? op->mwork.size() : op->work.size()), (unsigned)((r + rc - 1) / rc)), blk(64 * nrow * ks);
+    const dim3 grid((unsigned)items, (unsigned)((r + rc - 1) / rc)), blk(64 * nrow * ks);
 #define IGE_MG(NT, KC, KS) \
     hipLaunchKernelGGL((k_m2l_gen<NT, KC, KS>), grid, blk, 0, s, o, r, rc, nf, work, partner, src, op->d_bpart.p)
 #define IGE_MGK(NT) \
