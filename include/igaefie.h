@@ -176,11 +176,12 @@ typedef struct {
     int32_t q_level[11];    /* interpolation degree of each level 0..leaf_level (0 beyond) */
     double level_diam[11];  /* largest bounding-ball diameter of the clusters of each level
                                0..leaf_level (0 beyond) */
-    int32_t m2l_unordered;  /* 1: the one-column FP64 coupling evaluates the kernel once per
-                               unordered far pair and serves both clusters (the kernel is
-                               symmetric), as asked by IGE_M2L_SYM=1 at creation with one
-                               degree (<= 8) on every level; 0: once per ordered pair
-                               (default) */
+    int32_t m2l_unordered;  /* 1: the partners per work item of the one-column FP64 coupling were
+                               asked for (IGE_M2L_SYM=1 at creation, one degree <= 8 on every
+                               level); 0: they follow the library's rule (default).  Either way
+                               that coupling, where it is not streamed from stored blocks,
+                               evaluates the kernel once per unordered far pair and serves both
+                               clusters (the kernel is symmetric) */
 } ige_op_info_t;
 int ige_op_info(ige_op op, ige_op_info_t *out);
 

@@ -1,0 +1,85 @@
+"""The one-column FP64 coupling over unordered far pairs against forms that share no kernel with
+it: stored blocks, several columns (ordered pairs), and the oracle.  Meshes with enough far pairs
+for whole clusters per work item, so that degrees 8 to 15 take six and eight row tiles, the single
+row over (81 nodes) and several row chunks, in the launch shared with the near field and by itself."""
+import numpy as np
+import pytest
+
+from paper_1807_03097_amd import workloads as W
+
+pytestmark = pytest.mark.gpu
+
+
+def _rel(a, b):
+    return float(np.linalg.norm(a - b) / np.linalg.norm(b))
+
+
+MESHES = {"sphere": (3, 5520),   # two or four partners per item
+          "torus": (2, 1920)}    # one partner per item
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("surface", sorted(MESHES))
+@pytest.mark.parametrize("q", [2, 4, 6, 7, 8, 9, 10, 11])
+def test_one_column_equals_other_forms(q, surface, kind):
+    # the same kernel values (within 1.2 ulp of the phase) and sums of a few thousand terms in
+    # another order: under 1e-13 of the norm; 1e-12 against the oracle
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B
+    level, npairs = MESHES[surface]
+    pats = W.cube_sphere() if surface == "sphere" else W.torus()
+    sc = kind == "scalar"
+    kd = B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    op = B.Operator(geom, 1, level, 3.0, q, 1.6, 4, 4, 1, kind=kd)
+    st = B.Operator(geom, 1, level, 3.0, q, 1.6, 4, 4, 1, kind=kd, store_coupling=1)
+    assert op.info.far_pairs == npairs and npairs // 2 >= 256
+    x = W.random_coeffs(op.N, q)
+    y = op.apply(x)
+    op.set_overlap(False)   # the coupling and the near field in launches of their own
+    assert _rel(op.apply(x), y) < 1e-13
+    assert _rel(st.apply(x), y) < 1e-13
+    for c in op.apply(np.stack([x, x])):
+        assert _rel(c, y) < 1e-13
+    assert _rel(y, O.Oracle(pats, 1, level, 3.0, g=4, gs=4, scalar=sc).fmm_apply(x, q, 1.6, 1)) < 1e-12
+    ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("degrees", [(4, 5, 15), (4, 15, 12), (3, 10, 8), (2, 3, 11), (12, 8, 1)])
+def test_one_column_degree_per_level(degrees, kind):
+    # far pairs on the levels 1 and 2, node counts from 4 to 256 in one launch
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B
+    pats = W.cube_sphere()
+    sc = kind == "scalar"
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    op = B.Operator(geom, 1, 3, 3.0, 4, 1.6, 4, 4, 1, kind=B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE, q_level=degrees)
+    assert set(op.partition()["far"][:, 0]) == {1, 2}
+    x = W.random_coeffs(op.N, 5)
+    y = op.apply(x)
+    op.set_overlap(False)
+    assert _rel(op.apply(x), y) < 1e-13
+    for c in op.apply(np.stack([x, x, x])):
+        assert _rel(c, y) < 1e-13
+    assert _rel(y, O.Oracle(pats, 1, 3, 3.0, g=4, gs=4, scalar=sc).fmm_apply(x, list(degrees), 1.6, 1)) < 1e-12
+    ctx.close()
+
+
+def test_info_names_asked_items_only(monkeypatch):
+    # m2l_unordered says whether the items were asked for; the coupling is over unordered pairs
+    # either way, and both operators match the stored blocks
+    from paper_1807_03097_amd import binding as B
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, W.cube_sphere())
+    op = B.Operator(geom, 1, 3, 3.0, 6, 1.6, 4, 4, 1)
+    st = B.Operator(geom, 1, 3, 3.0, 6, 1.6, 4, 4, 1, store_coupling=1)
+    monkeypatch.setenv("IGE_M2L_SYM", "1")
+    asked = B.Operator(geom, 1, 3, 3.0, 6, 1.6, 4, 4, 1)
+    assert (op.info.m2l_unordered, asked.info.m2l_unordered) == (0, 1)
+    x = W.random_coeffs(op.N, 1)
+    y = st.apply(x)
+    assert _rel(op.apply(x), y) < 1e-13 and _rel(asked.apply(x), y) < 1e-13
+    ctx.close()
