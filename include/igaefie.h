@@ -216,7 +216,8 @@ int ige_apply(ige_op op, int r, const ige_c64 *x, ige_c64 *y, int ptr_kind);
  * products, M2L) in the given precision:
  *   IGE_F64   FP64 (as ige_apply; several columns on the FP64 matrix cores, with kernel
  *             values evaluated per apply; with 8 or more columns the autotuner may choose
- *             kernel matrices stored in FP64 instead, both orientations);
+ *             kernel matrices stored in FP64 instead, both orientations, or
+ *             IGE_M2L_F64=stored at creation asks for them);
  *   IGE_F32   FP32 kernel values: evaluated and accumulated in FP32 when generated
  *             on the fly, an FP32 copy of the stored blocks with FP64 accumulation when
  *             stored; relative error about kappa * diam * 2^-23 on the far field;

@@ -691,9 +691,12 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
                 op->m2l_generate_one = false;
                 if (const char *e = std::getenv("IGE_M2L_LDS_KB")) op->m2l_lds = (size_t)std::max(0, std::min(150, std::atoi(e))) * 1024;
                 if (const char *e = std::getenv("IGE_M2L_ONE")) op->m2l_generate_one = std::string(e) == "generate";
-                // many FP64 columns: stored blocks on the FP64 matrix cores (default) or
-                // evaluated per apply (IGE_M2L_F64=generate)
-                if (const char *e = std::getenv("IGE_M2L_F64")) op->f64mx_off = std::string(e) == "generate";
+                // many FP64 columns: evaluated per apply (default; IGE_M2L_F64=generate: the autotuner
+                // does not try stored blocks either) or from stored blocks (IGE_M2L_F64=stored)
+                if (const char *e = std::getenv("IGE_M2L_F64")) {
+                    op->f64mx_off = std::string(e) == "generate";
+                    op->f64mx_stored = std::string(e) == "stored";
+                }
                 // several FP64 columns: near field over ordered leaf pairs (default) or every
                 // block once for both of its products (IGE_NEAR_F64=blocks)
                 if (const char *e = std::getenv("IGE_NEAR_F64")) op->near_blocks = std::string(e) == "blocks";
@@ -1274,7 +1277,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
             switch (id) {
                 case ige::kTuneM2lDb: return 1;
                 case ige::kTuneM2lOrder: return 0;
-                case ige::kTuneM2lF64: return 0;
+                case ige::kTuneM2lF64: return op->f64mx_stored ? 1 : 0;
                 case ige::kTuneM2lNcol: return -1;   // the smallest chunk holding all columns
                 case ige::kTuneNearBxNt: return r > 32 ? 4 : (r > 16 ? 2 : 1);
                 default: return -1;                   // the largest that fits
@@ -1282,7 +1285,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
         };
         // coordinate descent over the knobs that the (r, prec) apply uses
         const bool mx = r > 1 && prec >= IGE_BF16 && op->mxl.empty(), near_bx = r > 1 && prec == IGE_BF16X3_ALL;
-        // FP64 coupling from stored blocks against the kernel evaluated per apply (default);
+        // FP64 coupling from stored blocks against the kernel evaluated per apply (one of them the default);
         // the columns per workgroup of the generated FP32 coupling
         const bool f64mx = prec == IGE_F64 && ige::m2l_f64mx_ok(op, r);
         const bool gen = r > 1 && prec == IGE_F32 && !op->stored && !op->work.empty();
@@ -1299,7 +1302,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
                                             {near_bx, ige::kTuneNearBxNt, 0, {1, 2, 4}},
                                             {false, ige::kTuneUnused, 0, {}},
                                             {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
-                                            {f64mx, ige::kTuneM2lF64, IGE_F64, {1}}};
+                                            {f64mx, ige::kTuneM2lF64, IGE_F64, {op->f64mx_stored ? 0 : 1}}};
         // each candidate timed in two rounds (minimum kept); a candidate replaces the
         // default only when it is more than 2 % faster (the timings vary by about that)
         std::vector<int> chosen(ige::kTuneKnobs, -1);

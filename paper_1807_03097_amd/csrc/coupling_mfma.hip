@@ -1111,11 +1111,11 @@ bool m2l_f64mx_ok(ige_op op, int r)
     return op->gd_fit == 1;
 }
 
-// The stored blocks only where the autotuner found them faster: evaluating the values as the
+// The stored blocks only where asked for (IGE_M2L_F64=stored) or found faster by the autotuner: evaluating the values as the
 // matrix operand needs no padding of Re and Im rows to 32 nodes, no blocks in memory and no
 // streaming of them (level 6, 64 columns, degree 8: 9.5 ms against 10.7 with 4.1 GB of blocks;
 // torus level 4, 23 columns, degree 6: 1.32 against 2.66 ms)
-bool m2l_f64mx_use(ige_op op, int r) { return tune_get(op, kTuneM2lF64, r, IGE_F64, 0) != 0 && m2l_f64mx_ok(op, r); }
+bool m2l_f64mx_use(ige_op op, int r) { return tune_get(op, kTuneM2lF64, r, IGE_F64, op->f64mx_stored ? 1 : 0) != 0 && m2l_f64mx_ok(op, r); }
 
 void m2l_f64mx(ige_op op, int r, const double2 *src, hipStream_t s, hipEvent_t mid)
 {

@@ -237,7 +237,8 @@ struct ige_op_s {
     ige::DBuf<double2> d_ndpart;
     bool near_blocks = false;           // IGE_NEAR_F64=blocks: the unordered-block kernel instead
     int gd_fit = -1;                    // FP64 blocks fit in device memory (-1: not yet decided)
-    bool f64mx_off = false;             // FP64 coupling of many columns generated per apply (IGE_M2L_F64=generate)
+    bool f64mx_off = false;             // FP64 coupling of many columns always evaluated per apply (IGE_M2L_F64=generate)
+    bool f64mx_stored = false;          // from stored blocks where they fit, unless tuned otherwise (IGE_M2L_F64=stored)
     ige::DBuf<int32_t> d_morder;         // work items by decreasing partner count (per level with mxl)
     // a degree per level: the matrix-core coupling level by level (levels with far pairs)
     struct MxLevel {

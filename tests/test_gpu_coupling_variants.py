@@ -83,3 +83,36 @@ def test_info_names_asked_items_only(monkeypatch):
     y = st.apply(x)
     assert _rel(op.apply(x), y) < 1e-13 and _rel(asked.apply(x), y) < 1e-13
     ctx.close()
+
+
+@pytest.mark.parametrize("kind", ["efie", "scalar"])
+@pytest.mark.parametrize("q", [4, 8, (4, 6, 10), (4, 10, 3)])
+def test_stored_fp64_blocks_equal_evaluated(monkeypatch, q, kind):
+    # 8, 9 and 70 columns: one chunk, a ragged one, several; the same values and sums of a few
+    # thousand terms in another order: under 1e-13 of the norm
+    from oracle import oracle as O
+    from paper_1807_03097_amd import binding as B
+    pats = W.cube_sphere()
+    sc = kind == "scalar"
+    kw = dict(kind=B.IGE_OP_SCALAR if sc else B.IGE_OP_EFIE, q_level=q if isinstance(q, tuple) else None)
+    q0 = q[0] if isinstance(q, tuple) else q
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, pats)
+    op = B.Operator(geom, 1, 3, 3.0, q0, 1.6, 4, 4, 1, **kw)
+    monkeypatch.setenv("IGE_M2L_F64", "stored")
+    st = B.Operator(geom, 1, 3, 3.0, q0, 1.6, 4, 4, 1, **kw)
+    far = st.partition()["far"]
+    deg = [d if isinstance(q, int) else q[l] for l, d in zip(far[:, 0], [q0] * len(far))]
+    qp = [32 * (-(-(d + 1) ** 2 // 32)) for d in deg]
+    blocks = sum(2 * n * n * 8 for n in qp)   # per ordered pair [Qp][2 Qp] doubles
+    held = {o: int(B.ige_op_info(o.h).device_bytes) for o in (op, st)}
+    X = np.stack([W.random_coeffs(op.N, 40 + c) for c in range(70)])
+    for r in (8, 9, 70):
+        Y, Z = op.apply(X[:r].copy()), st.apply(X[:r].copy())
+        for c in range(r):
+            assert _rel(Z[c], Y[c]) < 1e-13, (r, c)
+    more = {o: int(B.ige_op_info(o.h).device_bytes) - held[o] for o in (op, st)}
+    assert more[st] - more[op] >= blocks   # the second operator did store them
+    yo = O.Oracle(pats, 1, 3, 3.0, g=4, gs=4, scalar=sc).fmm_apply(X[69], list(q) if isinstance(q, tuple) else q, 1.6, 1)
+    assert _rel(Z[69], yo) < 1e-12
+    ctx.close()
