@@ -1303,6 +1303,7 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
                                             {false, ige::kTuneUnused, 0, {}},
                                             {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
                                             {f64mx, ige::kTuneM2lF64, IGE_F64, {op->f64mx_stored ? 0 : 1}}};
+        const bool had_blocks = op->d_Gd.p != nullptr;
         // each candidate timed in two rounds (minimum kept); a candidate replaces the
         // default only when it is more than 2 % faster (the timings vary by about that)
         std::vector<int> chosen(ige::kTuneKnobs, -1);
@@ -1335,6 +1336,12 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
         IGE_HIP(hipStreamSynchronize(s));
+        // FP64 blocks made here for a candidate that lost: given back
+        if (!had_blocks && op->d_Gd.p && !ige::m2l_f64mx_use(op, r)) {
+            op->d_Gd.release();
+            op->d_vd.release();
+            op->d_bmpart64.release();
+        }
         for (int i = 0; i < std::min(nchoice, (int)ige::kTuneKnobs); ++i) choice[i] = chosen[i];
     });
     return rc == IGE_OK ? tried : rc;

@@ -116,3 +116,25 @@ def test_stored_fp64_blocks_equal_evaluated(monkeypatch, q, kind):
     yo = O.Oracle(pats, 1, 3, 3.0, g=4, gs=4, scalar=sc).fmm_apply(X[69], list(q) if isinstance(q, tuple) else q, 1.6, 1)
     assert _rel(Z[69], yo) < 1e-12
     ctx.close()
+
+
+def test_autotuner_gives_back_rejected_blocks():
+    # the memory of the stored blocks is held after the call only if they were chosen
+    from paper_1807_03097_amd import binding as B
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, W.torus())
+    op = B.Operator(geom, 1, 3, 3.0, 6, 1.6, 4, 4, 1)
+    X = np.stack([W.random_coeffs(op.N, c) for c in range(9)])
+    Y = op.apply(X)
+    held = int(B.ige_op_info(op.h).device_bytes)
+    chosen = op.autotune(9)["m2l_f64_matrix_cores"]
+    more = int(B.ige_op_info(op.h).device_bytes) - held
+    blocks = int(op.info.far_pairs) * 64 * 2 * 64 * 8   # 49 nodes: [64][128] doubles per ordered pair
+    print(f"stored blocks chosen {chosen}: {more} bytes more, blocks {blocks}", flush=True)
+    assert more >= blocks if chosen == 1 else more == 0
+    Z = op.apply(X)
+    for c in range(9):
+        assert _rel(Z[c], Y[c]) < 1e-13
+    # asked for again, they are made again
+    assert op.autotune(9)["m2l_f64_matrix_cores"] in (0, 1)
+    ctx.close()
