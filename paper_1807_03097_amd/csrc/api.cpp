@@ -316,6 +316,15 @@ void plan_compact(ige_op op, const ige::NearBlocks &A)
     ige::build_near_compact(op->cmp, op->D, op->T, A, nrows);
 }
 
+// partners per item of the coupling of several columns, and of the one-column FP32 coupling
+int item_partners(const char *name, int def)
+{
+    const char *e = std::getenv(name);
+    return e ? std::max(1, std::min(64, std::atoi(e))) : def;
+}
+int m2l_chunk() { return item_partners("IGE_M2L_CHUNK", 8); }
+int m2l_chunk1() { return item_partners("IGE_M2L_CHUNK1", 12); }
+
 // host part: unknowns, trees, near pattern, singular pairs, far tables; the assembly leaves the lists
 // of distinct entries (compact) until its quadrature is under way
 void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige::SingularPair> &sing, bool compact)
@@ -350,8 +359,10 @@ void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige
 
 }  // extern "C"
 
-// device bytes an assembled operator and a single-column GMRES with the given
-// restart will hold (estimate from the host plan)
+// device bytes an assembled operator and a GMRES of r columns with the given restart will
+// hold at most (estimate from the host plan): what stays, and the largest of what the assembly,
+// the right-hand sides and the solve need one after the other.  FP64 coupling blocks that an
+// autotuner may store are not counted (it runs outside a server)
 size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const ige_solve_opts *opts)
 {
     const ige::Discretisation &D = op->D;
@@ -369,26 +380,40 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
         b += (size_t)C.nval * 16 + (size_t)C.npart * 16 + C.idx.size() * 4 + C.red_idx.size() * 4 +
              C.red_ptr.size() * 8 + C.occ.size() * 4 + C.wsub.size() * 40;
     }
-    b += (size_t)nblk * nF * 3 * 16 * R;                         // partial results (2 row chunks)
-    b += (size_t)E * (3 + 4 * nl) * G2 * 8 + (size_t)E * psi_fragment_doubles(nl, G2) * 8 + (size_t)E * 96;
+    // partial results (2 row chunks) of several columns, or of one where the once-per-entry form does not run
+    if (R > 1 || op->cmp.maxn > near_cmp_max()) b += (size_t)nblk * nF * 3 * 16 * R;
+    const size_t frag = (size_t)E * psi_fragment_doubles(nl, G2) * 8;
+    b += (size_t)E * (3 + 4 * nl) * G2 * 8 + (nl <= kRhsMxFns ? frag : 0) + (size_t)E * 96;
     b += (size_t)op->NC * Q * (9 * 8 + 11 * 16 * R);             // node data, moments, fields
-    b += (size_t)op->T.far.size() * 4 * Q * 16 / 4 * R;          // coupling partials (chunks of partners)
-    b += nfp * ((Q + 16 * kSymTiles - 1) / (16 * kSymTiles)) * 2 * 4 * Q * 16;   // one column: partials per unordered pair
-    b += (size_t)op->nsing * 32 + (size_t)D.N * 80 * R;
-    b += std::max((size_t)E * nl * 16, (size_t)16 << 20) + ((size_t)32 << 20) + std::min<size_t>((size_t)256 << 20, (size_t)E * nl * 16 * std::min<size_t>(R, kRhsCols));   // right-hand side element moments, potential
-    b += (size_t)op->nsing * nl * nl * 16 + (size_t)nblk * s * s * 4;   // singular pair blocks (assembly)
-    b += (size_t)5 * 18 * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * op->prm.gauss_singular * 8;   // and rule
-    b += ((size_t)restart + 1 + 8) * D.N * 16 * R;               // Krylov basis and work vectors
+    b += (size_t)op->nsing * 24 + (size_t)D.N * 80 * R;
+    const size_t mom = (size_t)E * nl;                           // element moments of one right-hand side
+    b += ige::rhs_base_values(mom) * 16;
+    const size_t gs = op->prm.gauss_singular;
+    const size_t assembly = (size_t)op->nsing * (nl * nl * 16 + 8) + (size_t)nblk * s * s * 4 +   // singular pair blocks
+                            5 * 18 * gs * gs * gs * gs * 8 +                                      // and their rule
+                            (nl <= kRhsMxFns ? 0 : frag);
+    size_t items1 = 0, items = 0, mitems = 0;                    // coupling: items of one column in FP32, of several, of many
+    for (size_t i = 0, k; i < op->T.far.size(); i = k) {
+        for (k = i; k < op->T.far.size() && op->T.far[k][0] == op->T.far[i][0] && op->T.far[k][1] == op->T.far[i][1]; ++k) {}
+        items1 += (k - i + m2l_chunk1() - 1) / m2l_chunk1();
+        items += (k - i + m2l_chunk() - 1) / m2l_chunk();
+        mitems += (k - i + 31) / 32;
+    }
+    if (R > 1) b += std::max(items, mitems) * 4 * Q * 16 * R;
+    const size_t spart = std::max(sym_rule(op).parts, items1) * 4 * Q * 16;   // and partial results of either precision
+    const size_t rhs = std::min<size_t>((size_t)256 << 20, mom * 16 * std::min<size_t>(R, kRhsCols));
+    size_t solve = ((size_t)restart + 1 + 8) * D.N * 16 * R;     // Krylov basis and work vectors
     const ige::GsPlan gp = ige::gs_plan(D.N, (int)R, restart);
-    b += ige::gs_part_count(gp, (int)R, restart) * 16;           // Gram-Schmidt scratch
+    solve += ige::gs_part_count(gp, (int)R, restart) * 16;       // Gram-Schmidt scratch
     // copies made on first use by the many-column kernels
     if (opts && opts->refine) {
         const int ip = opts->inner_prec;
-        if (opts->inner_tol >= 1e-5) b += ((size_t)restart + 1) * D.N * 8 * R;   // FP32 inner basis
-        if (ip == IGE_F32) b += (size_t)op->T.far.size() * Q * Q * 8;           // FP32 coupling values
-        if (ip >= IGE_BF16) b += nfp * 2 * (ip == IGE_BF16 ? 1 : 2) * Qp * 2 * Qp * 2;
-        if (ip == IGE_BF16X3_ALL) b += (size_t)nblk * 2 * 2 * Qn * 2 * Qn * 2 + (size_t)nblk * nF * 8 * R;
+        if (opts->inner_tol >= 1e-5) solve += ((size_t)restart + 1) * D.N * 8 * R;   // FP32 inner basis
+        if (ip == IGE_F32) solve += (size_t)op->T.far.size() * Q * Q * 8;           // FP32 coupling values
+        if (ip >= IGE_BF16) solve += nfp * 2 * (ip == IGE_BF16 ? 1 : 2) * Qp * 2 * Qp * 2;
+        if (ip == IGE_BF16X3_ALL) solve += (size_t)nblk * 2 * 2 * Qn * 2 * Qn * 2 + (size_t)nblk * nF * 8 * R;
     }
+    b += std::max(assembly, spart + std::max(rhs, solve));
     return b;
 }
 
@@ -502,7 +527,6 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             ige::plan_near_bf16(op, A.pair, A.leafdof, A.nF);
             op->d_bval.alloc(std::max<int64_t>(1, op->nnz));
             IGE_HIP(hipMemsetAsync(op->d_bval.p, 0, sizeof(double2) * op->nnz, s));
-            op->d_npart.alloc(std::max<int64_t>(1, A.nslots()));
             v.bpair = op->d_bpair.p; v.bval = op->d_bval.p; v.leafdof = op->d_leafdof.p; v.leafsgn = op->d_leafsgn.p;
             v.red_ptr = op->d_red_ptr.p; v.red_idx = op->d_red_idx.p;
             op->d_sing.upload(sing, s);
@@ -560,6 +584,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
                 bool on = C.nsub() > 0 && C.maxn <= ige::near_cmp_max();
                 if (const char *e = std::getenv("IGE_NEAR_COMPACT")) on = on && std::atoi(e) != 0;
                 op->cmp_on = on;
+                if (!on) op->d_npart.alloc(std::max<int64_t>(1, A.nslots()));
                 if (on) {
                     std::vector<int4> wk(C.wsub.size());
                     for (size_t w = 0; w < wk.size(); ++w) wk[w] = make_int4(C.wsub[w], C.wr0[w], C.wr1[w], 0);
@@ -617,8 +642,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             ige::launch_node_geometry(op);
             // M2L work items: partners of each target in chunks
             // partners per M2L work item (tuning knob IGE_M2L_CHUNK, default 8)
-            int CH = 8;
-            if (const char *e = std::getenv("IGE_M2L_CHUNK")) CH = std::max(1, std::min(64, std::atoi(e)));
+            const int CH = m2l_chunk();
             op->overlap = true;
             if (const char *e = std::getenv("IGE_OVERLAP")) op->overlap = std::atoi(e) != 0;
             if (const char *e = std::getenv("IGE_NEAR_FIRST")) op->near_first = std::atoi(e) != 0;
@@ -630,8 +654,7 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // items leave more of the device to the near-field product beside them (C2:
             // 0.1818-0.1854 ms per apply against 0.1863-0.1885 with 8; alone the coupling
             // kernel takes 98 against 91 us)
-            int CH1 = 12;
-            if (const char *e = std::getenv("IGE_M2L_CHUNK1")) CH1 = std::max(1, std::min(64, std::atoi(e)));
+            const int CH1 = m2l_chunk1();
             std::vector<int32_t> partner;
             for (const auto &f : T.far) partner.push_back((int32_t)(op->lvl_off[f[0]] + f[2]));
             // targets with chunks of up to ch partners, and per target its range of items
@@ -826,22 +849,9 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // (the upward pass stops there) but the matrix-core coupling stages them
             IGE_HIP(hipMemsetAsync(op->d_src.p, 0, op->d_src.bytes(), s));
             op->d_loc.alloc((size_t)op->NC * 3 * v.Q);
-            op->rhs_n = ige::rhs_base_values(op);
-            op->d_rhs.alloc(op->rhs_n + ige::pot_base_values(op));
             op->d_ybuf.alloc((size_t)D.P * v.SL * v.SL * 2 * F.rowlen * F.rowlen);
-            op->d_part.alloc(std::max<size_t>(1, op->work1.size()) * 4 * v.Q);
-            // one FP64 column: the coupling over unordered pairs; IGE_M2L_SYM=1 takes
-            // IGE_M2L_SYM_CHUNK (default 4) partners per item instead of the rule's
-            if (!T.far.empty()) {
-                int chunk = 0;
-                op->m2l_sym = false;
-                if (const char *e = std::getenv("IGE_M2L_SYM")) op->m2l_sym = std::atoi(e) != 0 && !F.varq && v.Q <= 81;
-                if (op->m2l_sym) {
-                    chunk = 4;
-                    if (const char *e = std::getenv("IGE_M2L_SYM_CHUNK")) chunk = std::max(1, std::min(64, std::atoi(e)));
-                }
-                ige::plan_m2l_sym(op, s, chunk);
-            }
+            // one FP64 column: the coupling over unordered pairs
+            if (!T.far.empty()) ige::plan_m2l_sym(op, s);
             if (op->stored) ige::store_coupling(op);
             IGE_HIP(hipStreamCreate(&op->aux));
             // fork/join between two streams of one device: no system-scope fence (the
@@ -852,8 +862,17 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             int err = 0;
             IGE_HIP(hipMemcpy(&err, op->d_err.p, sizeof(int), hipMemcpyDeviceToHost));
             IGE_REQUIRE(err == 0, "near-field assembly produced entries outside the leaf function slots");
+            // what the assembly alone needed goes before what only products need comes
             op->d_sblk.release();
+            op->d_sing_work.release();
             v.sblk = nullptr;
+            if (v.nl > ige::kRhsMxFns) {
+                op->d_ePsiF.release();
+                v.ePsiF = nullptr;
+            }
+            // partials of one column, FP64 or FP32 (stored blocks have their own)
+            if (!op->stored || op->m2l_generate_one) op->d_spart.alloc(std::max(op->nspart, op->work1.size() * 4 * v.Q));
+            op->d_rhs.alloc(ige::rhs_base_values(ige::rhs_scratch_values(v, 1)));
         } catch (...) {
             delete op;
             throw;
@@ -935,7 +954,7 @@ int ige_op_info(ige_op op, ige_op_info_t *out)
         b += op->d_nbred_idx.bytes() + op->d_morder.bytes();
         b += op->d_Mp.bytes() * 3 + op->d_inc.bytes() + op->d_sing.bytes() + op->d_sing_work.bytes() + op->d_work.bytes();
         b += op->d_work1.bytes() + op->d_wrk_of_tgt1.bytes() + op->d_wrk_of_tgt.bytes();
-        b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes() + op->d_part.bytes();
+        b += op->d_partner.bytes() + op->d_mom.bytes() + op->d_src.bytes() + op->d_loc.bytes();
         b += op->d_swork.bytes() + op->d_spartner.bytes() + op->d_sred_ptr.bytes() + op->d_sred_idx.bytes() + op->d_spart.bytes();
         b += op->d_rhs.bytes() + op->d_rhs_more.bytes() + op->d_pot.bytes() + op->d_x.bytes() + op->d_y.bytes() + op->d_V.bytes() + op->d_w.bytes() + op->d_r.bytes();
         b += op->d_cnr.bytes() + op->d_cnc.bytes() + op->d_cld.bytes() + op->d_cidx.bytes() + op->d_corder.bytes() + op->d_cred_idx.bytes();
@@ -1363,7 +1382,7 @@ void rhs_columns(ige_op op, int r, int kind, const double *a, const double2 *pol
     const int fit = (int)std::max<size_t>(1, ((size_t)256 << 20) / (sizeof(double2) * one));
     int nc = std::min({r, ige::kRhsCols, fit});
     double2 *scr = op->d_rhs.p;
-    size_t nscr = op->rhs_n;
+    size_t nscr = op->d_rhs.n;
     if (nscr < one * nc) {
         hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
         IGE_HIP(hipStreamIsCapturing(s, &cap));
@@ -1841,15 +1860,11 @@ int ige_potential(ige_op op, int r, const ige_c64 *w, int ptr_kind, int npts, co
         const size_t nout = (size_t)3 * npts, nsrc = ige::potential_source_doubles(op);
         const size_t npart = parts > 1 ? nout * parts : 0, nw = ptr_kind == IGE_HOST ? (size_t)r * N : 0;
         const size_t need = 2 * (npart + nout + nw) + nsrc + nout;
-        double *wsp = reinterpret_cast<double *>(op->d_rhs.p + op->rhs_n);   // where that holds it
-        if (2 * (op->d_rhs.n - op->rhs_n) < need) {
-            if (op->d_pot.n < need) {
-                IGE_HIP(hipStreamSynchronize(s));
-                op->d_pot.alloc(need);
-            }
-            wsp = op->d_pot.p;
+        if (op->d_pot.n < need) {
+            IGE_HIP(hipStreamSynchronize(s));
+            op->d_pot.alloc(need);
         }
-        double2 *dpart = reinterpret_cast<double2 *>(wsp), *dout = dpart + npart, *dw = dout + nout;
+        double2 *dpart = reinterpret_cast<double2 *>(op->d_pot.p), *dout = dpart + npart, *dw = dout + nout;
         double *dsrc = reinterpret_cast<double *>(dw + nw), *dpts = dsrc + nsrc;
         if (npts) IGE_HIP(hipMemcpyAsync(dpts, points, sizeof(double) * nout, hipMemcpyHostToDevice, s));
         const double2 *W = reinterpret_cast<const double2 *>(w);

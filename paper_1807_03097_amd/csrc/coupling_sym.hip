@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <cstdlib>
+#include <string>
 
 #include "device_math.hpp"
 #include "near_item.hpp"
@@ -373,10 +375,18 @@ __global__ __launch_bounds__(1024) void k_m2l_reduce_sym(DevOp o, int S, const i
 
 }  // namespace
 
-void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
+SymRule sym_rule(const ige_op_s *op)
 {
     const auto &T = op->T;
     const auto &F = op->F;
+    SymRule R;
+    // IGE_M2L_SYM=1 takes IGE_M2L_SYM_CHUNK (default 4) partners per item instead of the rule's
+    if (const char *e = std::getenv("IGE_M2L_SYM"))
+        R.asked = std::atoi(e) != 0 && !F.varq && (F.q + 1) * (F.q + 1) <= 81 && !T.far.empty();
+    if (R.asked) {
+        R.chunk = 4;
+        if (const char *e = std::getenv("IGE_M2L_SYM_CHUNK")) R.chunk = std::max(1, std::min(64, std::atoi(e)));
+    }
     // Partners per item when not asked for.  Two: the shorter items hide the kernel's own
     // latencies and end together (level 4 solve, 829 iterations, 107 ms against 113 with three and
     // 118 with four).  Four beside a near-field product that takes at least half as long: fewer
@@ -385,29 +395,48 @@ void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
     // against 663; level 6, degrees up to 14: 725 against 719).  The times compared are near bytes
     // at 4.7 TB/s and steps of 16 rows x 4 columns at 340 cycles on 1,024 SIMDs.
     double steps = 0.0;
+    int64_t items = 0;
+    int rt = 1;
     for (const auto &f : T.far) {
         const int Q = (F.ql[f[0]] + 1) * (F.ql[f[0]] + 1);
         steps += 0.5 * ((Q + 12) / 16) * ((Q + 3) / 4);
+        rt = std::max(rt, (Q + 15) / 16);   // node tiles of a cluster
     }
-    const double near_us = (double)op->cmp.nval * 16.0 / 4.7e6, far_us = steps * 340.0 / (1024.0 * 2400.0);
-    std::vector<int32_t> spart;
-    op->swork.clear();
-    // each pair is visited from the cluster of smaller index alone
-    const auto upper = std::count_if(T.far.begin(), T.far.end(), [](const auto &f) { return f[2] > f[1]; });
-    IGE_REQUIRE(2 * (size_t)upper == T.far.size(), "far pairs are not symmetric");
-    int rt = 1;
-    for (const auto &f : T.far) rt = std::max(rt, ((F.ql[f[0]] + 1) * (F.ql[f[0]] + 1) + 15) / 16);   // node tiles of a cluster
+    R.near_us = (double)op->cmp.nval * 16.0 / 4.7e6;
+    R.far_us = steps * 340.0 / (1024.0 * 2400.0);
     rt = 2 * ((std::min(rt, kSymTiles) + 1) / 2);
     // Few pairs: one partner per item where that makes no more than four items per CU, and with less
     // than one per CU 64 rows per item.  A wave is then bound by its own latencies (level 4, 60
     // pairs of 81 nodes: 39 us with two partners and all rows, 14 now; torus level 3, 72 pairs of 225
     // nodes, 128 rows per item: 70 and 47).
-    int64_t items = 0;
     for (const auto &f : T.far) items += ((F.ql[f[0]] + 1) * (F.ql[f[0]] + 1) + 16 * rt - 1) / (16 * rt);
-    op->near_us = near_us;
-    op->far_us = far_us;
-    if (chunk <= 0) chunk = items / 2 < 1024 ? 1 : (near_us > 0.5 * far_us ? 4 : 2);
+    if (R.chunk <= 0) R.chunk = items / 2 < 1024 ? 1 : (R.near_us > 0.5 * R.far_us ? 4 : 2);
     if (items / 2 < 256) rt = std::min(rt, 4);
+    R.rows = 16 * rt;
+    // partial results: one per item and one per pair, for each chunk of rows
+    for (size_t i = 0, k; i < T.far.size(); i = k) {   // sorted by level, cluster, partner
+        const int lvl = T.far[i][0], tg = T.far[i][1], Q = (F.ql[lvl] + 1) * (F.ql[lvl] + 1);
+        size_t up = 0;
+        for (k = i; k < T.far.size() && T.far[k][0] == lvl && T.far[k][1] == tg; ++k) up += T.far[k][2] > tg;
+        R.parts += (up + (up + R.chunk - 1) / R.chunk) * ((Q + R.rows - 1) / R.rows);
+    }
+    return R;
+}
+
+void plan_m2l_sym(ige_op op, hipStream_t s)
+{
+    const auto &T = op->T;
+    const auto &F = op->F;
+    const SymRule rule = sym_rule(op);
+    const int chunk = rule.chunk, rt = rule.rows / 16;
+    std::vector<int32_t> spart;
+    op->swork.clear();
+    // each pair is visited from the cluster of smaller index alone
+    const auto upper = std::count_if(T.far.begin(), T.far.end(), [](const auto &f) { return f[2] > f[1]; });
+    IGE_REQUIRE(2 * (size_t)upper == T.far.size(), "far pairs are not symmetric");
+    op->m2l_sym = rule.asked;
+    op->near_us = rule.near_us;
+    op->far_us = rule.far_us;
     op->sym_rt = rt / 2;
     size_t i = 0;
     while (i < T.far.size()) {   // sorted by level, cluster, partner
@@ -440,7 +469,8 @@ void plan_m2l_sym(ige_op op, hipStream_t s, int chunk)
     op->d_spartner.upload(spart, s);
     op->d_sred_ptr.upload(sptr, s);
     op->d_sred_idx.upload(sidx, s);
-    op->d_spart.alloc(((size_t)nw + spart.size()) * 4 * op->view.Q);
+    IGE_REQUIRE((size_t)nw + spart.size() == rule.parts, "coupling partials miscounted");
+    op->nspart = rule.parts * 4 * op->view.Q;   // d_spart, allocated at the end of the assembly
 }
 
 void launch_m2l_sym(ige_op op)

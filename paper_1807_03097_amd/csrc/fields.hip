@@ -192,14 +192,13 @@ __global__ __launch_bounds__(256) void k_rhs_sum(DevOp o, int nc, const double2 
 
 size_t rhs_scratch_values(const DevOp &o, int nc) { return (size_t)o.P * o.n * o.n * o.nl * nc; }
 
-// What the operator keeps from its assembly on: element moments of one column or of as many as a
-// launch takes within 16 MiB, and a potential's workspace within 32 MiB
-size_t rhs_base_values(ige_op op)
+// What the operator keeps from its assembly on, so that a captured launch finds it: element moments of
+// one column, or of as many as a launch takes within 1 MiB
+size_t rhs_base_values(size_t one)
 {
-    const size_t one = rhs_scratch_values(op->view, 1), most = ((size_t)16 << 20) / sizeof(double2);
+    const size_t most = ((size_t)1 << 20) / sizeof(double2);
     return std::max(one, std::min(most, kRhsCols * one));
 }
-size_t pot_base_values(ige_op op) { return std::min(((size_t)32 << 20) / sizeof(double2), potential_source_doubles(op) / 2 + 65536); }
 
 void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f, double2 *scr, size_t nscr)
 {
@@ -221,7 +220,7 @@ void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol
     // The matrix form always works on 16 columns and 16 functions: from nine columns on, where the other
     // pads to 16 as well (8 columns: 87 us there, 91 here; 12: 154 and 98); 24 functions in two
     // tiles leave two waves per SIMD (16 columns: 53 and 58)
-    const bool mx = nc > 8 && o.nl <= 16;
+    const bool mx = nc > 8 && o.nl <= kRhsMxFns;
     const dim3 gm((unsigned)((E + 3) / 4));
     if (mx && o.scalar) hipLaunchKernelGGL(k_rhs_mx<true>, gm, dim3(256), 0, s, o, E, nc, kind, cols, scr);
     else if (mx) hipLaunchKernelGGL(k_rhs_mx<false>, gm, dim3(256), 0, s, o, E, nc, kind, cols, scr);

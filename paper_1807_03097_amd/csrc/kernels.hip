@@ -1000,7 +1000,7 @@ void launch_m2l(ige_op op, int prec)
     }
     lds_attr_once(reinterpret_cast<const void *>(&k_m2l), shm);
     hipLaunchKernelGGL(k_m2l, dim3(grid), dim3(kM2LThreads), shm, lstream(op), o, nwork, op->d_work1.p, op->d_partner.p,
-                       op->d_src.p, op->d_part.p);
+                       op->d_src.p, op->d_spart.p);
     IGE_LAUNCH_CHECK();
 }
 
@@ -1014,7 +1014,7 @@ void launch_m2l_reduce(ige_op op, int prec)
     if (prec == IGE_F64)
         launch_m2l_reduce_sym(op);
     else
-        hipLaunchKernelGGL(k_m2l_reduce, dim3(op->NC), dim3(128), 0, lstream(op), o, op->d_wrk_of_tgt1.p, op->d_part.p,
+        hipLaunchKernelGGL(k_m2l_reduce, dim3(op->NC), dim3(128), 0, lstream(op), o, op->d_wrk_of_tgt1.p, op->d_spart.p,
                            op->d_loc.p);
     IGE_LAUNCH_CHECK();
     if (!o.varq) return;

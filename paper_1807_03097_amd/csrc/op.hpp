@@ -148,7 +148,8 @@ struct ige_op_s {
     std::vector<ige::SymWork> swork;      // row cluster with a chunk of partners of larger index
     ige::DBuf<ige::SymWork> d_swork;
     ige::DBuf<int32_t> d_spartner, d_sred_ptr, d_sred_idx;   // partners; per cluster its slots
-    ige::DBuf<double2> d_spart;           // [items + partners][4][Q] partial couplings
+    ige::DBuf<double2> d_spart;           // [items + partners][4][Q] partial couplings; FP32: [items of work1][4][Q]
+    size_t nspart = 0;
     // many columns: the near-field product on the second stream beside the far field
     // (0: in line after it, 1: from the start, 2: after M2M)
     int batch_overlap = 1;
@@ -190,7 +191,7 @@ struct ige_op_s {
     ige::DBuf<int8_t> d_leafsgn;
     ige::DBuf<int64_t> d_red_ptr;
     ige::DBuf<double2> d_bval;
-    ige::DBuf<double2> d_npart;        // near-field partial results [nslots]
+    ige::DBuf<double2> d_npart;        // near-field partial results [nslots] (without the once-per-entry form)
     // near field stored once per distinct entry (product of one column)
     ige::NearCompact cmp;
     bool cmp_on = false;
@@ -263,14 +264,12 @@ struct ige_op_s {
     // apply workspaces (one right-hand side at a time)
     ige::DBuf<double2> d_mom;    // [NC][3][Q]   s^1, s^2, d
     ige::DBuf<double2> d_src;    // [NC][4][Q]   v_x, v_y, v_z, d
-    ige::DBuf<double2> d_part;   // [one-column items][4][Q]
     ige::DBuf<double2> d_loc;    // [NC][3][Q]   t^1, t^2, t^d
     ige::DBuf<double2> d_ybuf;   // [leaves][2][rowlen][rowlen] L2P results per leaf
     ige::DBuf<double2> d_x, d_y; // staging for host pointers
     ige::DBuf<double> d_pot;     // workspace of the potential: sources, points, results, parts
-    // element moments of the right-hand sides [E][nl][columns], then a potential's workspace: from
-    // the assembly on and never replaced (captured launches refer to it); moments of more columns
-    size_t rhs_n = 0;
+    // element moments of the right-hand sides [E][nl][columns]: from the assembly on and never
+    // replaced (captured launches refer to it); moments of more columns, on first use
     ige::DBuf<double2> d_rhs, d_rhs_more;
     // batched-apply workspaces (r columns, column index innermost)
     int bcap = 0;
@@ -371,9 +370,16 @@ void near_bf16(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
 bool near_cols_use(const ige_op_s *op, int r);
 void near_cols(ige_op op, int r, const double2 *xt, double2 *yt, hipStream_t s);
 void launch_m2l_reduce(ige_op op, int prec);
-// one FP64 column: work lists of the unordered-pair coupling (chunk partners per item,
-// 0: by rule), its launch and its reduction
-void plan_m2l_sym(ige_op op, hipStream_t s, int chunk);
+// one FP64 column: item sizes of the unordered-pair coupling and its partial results, from the
+// host plan; its work lists, its launch and its reduction
+struct SymRule {
+    int chunk = 0, rows = 0;                 // partners and rows per item
+    bool asked = false;                      // item size from the environment
+    size_t parts = 0;                        // partial results
+    double near_us = 0.0, far_us = 0.0;
+};
+SymRule sym_rule(const ige_op_s *op);
+void plan_m2l_sym(ige_op op, hipStream_t s);
 void launch_m2l_sym(ige_op op);
 void launch_m2l_reduce_sym(ige_op op);
 // the same coupling with the near-field product's items in one launch, and both results' sums
@@ -406,10 +412,10 @@ void lds_attr_once(const void *kern, size_t shm);
 // a [nc][3] with polarisations pol [nc][3] (EFIE); kind 1: point sources at a, scalar only);
 // element moments in d_rhs
 constexpr int kRhsCols = 16;
+constexpr int kRhsMxFns = 16;   // most local functions of the matrix-core form, which reads ePsiF
 size_t rhs_scratch_values(const DevOp &o, int nc);
 void launch_rhs(ige_op op, int kind, int nc, const double *a, const double2 *pol, double2 *f, double2 *scr, size_t nscr);
-size_t rhs_base_values(ige_op op);
-size_t pot_base_values(ige_op op);
+size_t rhs_base_values(size_t one);   // one: values of one column
 // GMRES vector kernels (V: [k][r][n], vectors [r][n]; gate/run/flag: per-column int masks)
 struct GsPlan {
     int nchk = 0, nblk = 0;             // entry chunks of the dot and blocks of the update kernel

@@ -201,6 +201,7 @@ struct ige_srv_s {
             std::vector<ige_c64> f((size_t)N * nw), x((size_t)N * nw, ige_c64{0.0, 0.0});
             int rr = ige_rhs_plane_wave(op, nw, dir.data(), pol.data(), f.data(), IGE_HOST);
             if (rr != IGE_OK) throw ige::Status{rr, ige_last_error()};
+            op->d_rhs_more.release();   // the solve's memory comes after it (planned_device_bytes)
             std::vector<ige_solve_stats> st((size_t)nw);
             rr = ige_solve(op, nw, f.data(), x.data(), IGE_HOST, &lead->opts, st.data());
             if (rr != IGE_OK && rr != IGE_ENOTCONV) throw ige::Status{rr, ige_last_error()};
