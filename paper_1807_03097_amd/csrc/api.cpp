@@ -359,6 +359,15 @@ void plan(ige_op op, const ige_geom_s *geom, ige::NearBlocks &A, std::vector<ige
 
 }  // extern "C"
 
+bool ige::krylov_goes_on(int r, const char *run, const int *iters, const int *cap, const double *est, const double *prev,
+                         const double *tol)
+{
+    for (int c = 0; c < r; ++c)
+        if (run[c] && iters[c] + 1 < cap[c] && !(est[c] * (prev[c] > 0.0 ? std::min(1.0, est[c] / prev[c]) : 1.0) <= tol[c]))
+            return true;
+    return false;
+}
+
 // device bytes an assembled operator and a GMRES of r columns with the given restart will
 // hold at most (estimate from the host plan): what stays, and the largest of what the assembly,
 // the right-hand sides and the solve need one after the other.  FP64 coupling blocks that an
@@ -1581,6 +1590,7 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
             else apply_dev(op, r, V + (size_t)j * r * N, V + (size_t)(j + 1) * r * N, prec, &ag);
         };
         bool applied = false;
+        std::vector<double> prev(r, 0.0);   // residual estimates one step back
         for (int jj = 0; jj < m; ++jj) {
             if (!applied) apply_basis(jj);
             applied = false;
@@ -1596,12 +1606,16 @@ void gmres_batched(ige_op op, int r, const double2 *B, double2 *X, const std::ve
             ige::launch_gs_fin(s, gp, N, r, np1, np2, op->d_grun.p, op->d_gflag.p, k, h1, h2, hs, y, v, u, v32, op->h_hpack.p);
             IGE_HIP(hipEventRecord(op->ev_gs, s));
             if (b32 && !one) std::swap(cur, nxt);
-            // the next step's operator starts while the host reads this column
-            if (k < m) {
+            // the next step's operator starts while the host reads this column, where that step is
+            // expected: a product that nothing uses costs more than the host's turn, in a solve of
+            // few iterations of many columns above all
+            if (k < m && ige::krylov_goes_on(r, run.data(), out.iters.data(), it_cap.data(), out.relres_est.data(), prev.data(),
+                                             tol.data())) {
                 apply_basis(k);
                 applied = true;
             }
             IGE_HIP(hipEventSynchronize(op->ev_gs));
+            prev = out.relres_est;
             const double2 *hp = op->h_hpack.p;
             int nrun = 0;
             bool changed = false;

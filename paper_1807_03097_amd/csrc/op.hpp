@@ -442,6 +442,11 @@ void launch_gs_add(hipStream_t s, const GsPlan &g, int64_t n, int r, const float
 void launch_gs_fin(hipStream_t s, const GsPlan &g, int64_t n, int r, const double *npart1, const double *npart2,
                    const int *run, const int *flag, int k, const double2 *h1, const double2 *h2, int hs, const double2 *y,
                    double2 *v, double2 *u, float2 *v32, double2 *out);
+// whether a step follows the one under way, as far as can be told before its column is read: some
+// running column has iterations left and would not reach its tolerance by the factor of its last
+// step (est: residual estimate before this step, prev: before the last one, 0 if there was none)
+bool krylov_goes_on(int r, const char *run, const int *iters, const int *cap, const double *est, const double *prev,
+                    const double *tol);
 void launch_axpby(ige_op op, int64_t n, double2 a, const double2 *x, double2 b, double2 *y);
 void launch_norm2_b(ige_op op, int r, const double2 *x, double *out);
 void launch_scale_cols(ige_op op, int r, const double *s, const double2 *x, double2 *y);
