@@ -28,7 +28,7 @@ __device__ inline float2 cmac(float2 acc, float2 a, float2 b)
     return make_float2(fmaf(a.x, b.x, fmaf(-a.y, b.y, acc.x)), fmaf(a.x, b.y, fmaf(a.y, b.x, acc.y)));
 }
 
-// FP64 (near-field quadrature, potential): 1/r by the hardware reciprocal square root and two Newton steps
+// FP64 (element pairs that share a corner): 1/r by the hardware reciprocal square root and two Newton steps
 // y <- y (3/2 - r^2 y^2 / 2); sin and cos of kappa r by Cody-Waite reduction
 // t = kappa r - k pi/2 (pi/2 split into three doubles, products exact through
 // fused multiply-add) and the Taylor polynomials of sin (to t^17) and cos (to t^18)
@@ -88,10 +88,9 @@ __device__ inline double2 helmholtz_r2(double kappa, double r2)
 // gives e^{ix} / (4 pi) = (C c - S s, S c + C s).  1/r from the hardware reciprocal
 // square root y0 and one third-order step y = y0 (1 + e/2 + 3e^2/8), e = 1 - r^2 y0^2
 // (the next term, 5e^3/16, is below 1e-21 for the hardware estimate's |e| < 1e-7).
-// Valid for |kappa r| < 5e7 (k fits an int).  Measured against long-double sine and
-// cosine over x in [0, 2000] and [1e-6, 1e6]: within 1.12 ulp(x) of e^{ix}.
-// The second form also returns 1/r and kappa r; it takes k and its table index from the
-// mantissa of x 128/pi + 1.5 2^52 and so holds for kappa r up to 1e13.
+// k and its table index come from the mantissa of x 128/pi + 1.5 2^52: valid for kappa r up
+// to 1e13.  Measured against long-double sine and cosine over x in [0, 2000] and [1e-6, 1e6]:
+// within 1.12 ulp(x) of e^{ix}.  The first form also returns 1/r and kappa r.
 __device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double2 *tab, double &ir, double &kr)
 {
     constexpr double kInvStep = 40.74366543152521;   // 128/pi
@@ -137,23 +136,8 @@ __device__ inline double2 helmholtz_tab_end(double ir, double c, double s, doubl
 }
 __device__ inline double2 helmholtz_r2_tab(double kappa, double r2, const double2 *tab)
 {
-    constexpr double kInvStep = 40.74366543152521;   // 128/pi
-    constexpr double kStep = 0.02454369260617026;    // pi/128 rounded to double
-    const double y0 = __builtin_amdgcn_rsq(r2);
-    const double e = fma(-(r2 * y0), y0, 1.0);
-    const double y = fma(e * y0, fma(e, 0.375, 0.5), y0);
-    const double x = kappa * (r2 * y);
-    const double k = rint(x * kInvStep);
-    const double t = fma(-k, kStep, x);
-    const double2 cs = tab[(int)k & 255];
-    const double z = t * t;
-    const double ps = fma(z, 1.0 / 120.0, -1.0 / 6.0);   // 1/5!, -1/3!
-    const double s = fma(t * z, ps, t);
-    double pc = -1.0 / 720.0;                         // -1/6!
-    pc = fma(pc, z, 1.0 / 24.0);                      //  1/4!
-    pc = fma(pc, z, -0.5);                            // -1/2!
-    const double c = fma(z, pc, 1.0);
-    return make_double2(fma(cs.x, c, -cs.y * s) * y, fma(cs.y, c, cs.x * s) * y);
+    double ir, kr;
+    return helmholtz_r2_tab(kappa, r2, tab, ir, kr);
 }
 
 // FP32 counterpart (relative error about kappa r 2^-23 from the rounding of r):
