@@ -1324,13 +1324,12 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice)
             std::vector<int> cand;
         };
         const bool mxon = mx && !op->mwork.empty();
-        const Knob knobs[ige::kTuneKnobs] = {{mxon, ige::kTuneM2lOrder, split, {1}},
-                                            {mxon, ige::kTuneM2lDb, split, {1, 0}},
-                                            {mxon, ige::kTuneM2lNcol, split, {64, 128, 256}},
-                                            {near_bx, ige::kTuneNearBxNt, 0, {1, 2, 4}},
-                                            {false, ige::kTuneUnused, 0, {}},
-                                            {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
-                                            {f64mx, ige::kTuneM2lF64, IGE_F64, {op->f64mx_stored ? 0 : 1}}};
+        const Knob knobs[] = {{mxon, ige::kTuneM2lOrder, split, {1}},
+                              {mxon, ige::kTuneM2lDb, split, {1, 0}},
+                              {mxon, ige::kTuneM2lNcol, split, {64, 128, 256}},
+                              {near_bx, ige::kTuneNearBxNt, 0, {1, 2, 4}},
+                              {gen, ige::kTuneM2lRb, prec, {1, 2, 4}},
+                              {f64mx, ige::kTuneM2lF64, IGE_F64, {op->f64mx_stored ? 0 : 1}}};
         const bool had_blocks = op->d_Gd.p != nullptr;
         // each candidate timed in two rounds (minimum kept); a candidate replaces the
         // default only when it is more than 2 % faster (the timings vary by about that)

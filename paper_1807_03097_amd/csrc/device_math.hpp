@@ -12,13 +12,13 @@ __device__ inline double2 cadd(double2 a, double2 b) { return make_double2(a.x +
 __device__ inline double2 cscale(double s, double2 a) { return make_double2(s * a.x, s * a.y); }
 __device__ inline float2 cmul(float2 a, float2 b) { return make_float2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x); }
 __device__ inline float2 cadd(float2 a, float2 b) { return make_float2(a.x + b.x, a.y + b.y); }
-// acc + a b as four fused multiply-adds (no separate product and sum)
 // surface element |d_uF x d_vF|
 __device__ inline double surf_elem(const double Fu[3], const double Fv[3])
 {
     const double nx = Fu[1] * Fv[2] - Fu[2] * Fv[1], ny = Fu[2] * Fv[0] - Fu[0] * Fv[2], nz = Fu[0] * Fv[1] - Fu[1] * Fv[0];
     return sqrt(fma(nx, nx, fma(ny, ny, nz * nz)));
 }
+// acc + a b as four fused multiply-adds (no separate product and sum)
 __device__ inline double2 cmac(double2 acc, double2 a, double2 b)
 {
     return make_double2(fma(a.x, b.x, fma(-a.y, b.y, acc.x)), fma(a.x, b.y, fma(a.y, b.x, acc.y)));
@@ -178,13 +178,7 @@ __device__ inline float2 helmholtz_r2(float kappa, float r2)
     return make_float2(cs * f, sn * f);
 }
 
-template <typename T> struct cplx_of;
-template <> struct cplx_of<double> { using type = double2; };
-template <> struct cplx_of<float> { using type = float2; };
-
-__device__ inline double2 to_c(double2 a, double) { return a; }
-__device__ inline float2 to_c(double2 a, float) { return make_float2((float)a.x, (float)a.y); }
-__device__ inline double2 to_d(double2 a) { return a; }
+__device__ inline float2 to_f(double2 a) { return make_float2((float)a.x, (float)a.y); }
 __device__ inline double2 to_d(float2 a) { return make_double2(a.x, a.y); }
 
 // v of the lane N places on inside the 16-lane row (rotation)

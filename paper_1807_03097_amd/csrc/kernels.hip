@@ -421,7 +421,7 @@ __global__ __launch_bounds__(kM2LThreads) void k_m2l(DevOp o, int nwork, const M
         const double *Xs = o.nodeX + (size_t)sc * 3 * Qs;
         const double2 *Vs = src + (size_t)sc * 4 * Qs;
         for (int i = tid; i < 3 * Q; i += kM2LThreads) sX[(i % Q) * 4 + i / Q] = (T)Xs[(i / Q) * Qs + i % Q];
-        for (int i = tid; i < 4 * Q; i += kM2LThreads) sV[(i % Q) * 4 + i / Q] = dm::to_c(Vs[(i / Q) * Qs + i % Q], T(0));
+        for (int i = tid; i < 4 * Q; i += kM2LThreads) sV[(i % Q) * 4 + i / Q] = dm::to_f(Vs[(i / Q) * Qs + i % Q]);
         __syncthreads();
         if (active) {
             for (int ms = mb; ms < me; ++ms) {

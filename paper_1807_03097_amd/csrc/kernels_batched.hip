@@ -446,7 +446,7 @@ __global__ __launch_bounds__(256) void k_m2m_b(DevOp o, int lvl, int r, double2 
 }
 
 // ---------------------------------------------------------------------------
-// M2L, kRB columns: one kernel value per node pair serves 4 kRB products, and
+// M2L with FP32 values, kRB columns (FP64: coupling_gen.hip): one kernel value per node pair serves 4 kRB products, and
 // every source value read from LDS serves kNTB target nodes of the thread.
 // Threads: kNTB target nodes x a part of the source nodes; parts summed in LDS,
 // one field at a time.
@@ -454,11 +454,12 @@ __global__ __launch_bounds__(256) void k_m2m_b(DevOp o, int lvl, int r, double2 
 constexpr int kM2LThreadsB = 256;
 constexpr int kNTB = 3;
 
-template <typename T, int kRB>
+template <int kRB>
 __global__ __launch_bounds__(kM2LThreadsB) void k_m2l_b(DevOp o, int r, const M2LWork *work, const int32_t *partner,
                                                          const double2 *src, double2 *part)
 {
-    using C = typename dm::cplx_of<T>::type;
+    using T = float;
+    using C = float2;
     extern __shared__ double smd[];
     const M2LWork wk = work[blockIdx.x];
     const int c0 = blockIdx.y * kRB, nc = min(kRB, r - c0);
@@ -478,9 +479,6 @@ __global__ __launch_bounds__(kM2LThreadsB) void k_m2l_b(DevOp o, int r, const M2
     T *sX = reinterpret_cast<T *>(smd);                        // [Q][4]: x, y, z, unused
     C *sV = reinterpret_cast<C *>(smd + (4 * Q * (int)sizeof(T) + 15) / 16 * 2);   // [Q][4][kRB], after sX
     double2 *red = reinterpret_cast<double2 *>(smd);           // [S][Q][kRB] (one field at a time)
-    __shared__ double2 sTab[256];                               // (cos, sin)(j pi/128), FP64 only
-    if constexpr (sizeof(T) == 8)
-        for (int i = tid; i < 256; i += kM2LThreadsB) sTab[i] = o.sctab[i];   // first use after a barrier
     const T kap = (T)o.kappa;
     const double *Xt = o.nodeX + (size_t)wk.tgt * 3 * Qs;
     T xt[kNTB][3];
@@ -510,7 +508,7 @@ __global__ __launch_bounds__(kM2LThreadsB) void k_m2l_b(DevOp o, int r, const M2
         for (int i = tid; i < 3 * Q; i += kM2LThreadsB) sX[(i % Q) * 4 + i / Q] = (T)Xs[(i / Q) * Qs + i % Q];
         for (int i = tid; i < 4 * Q * kRB; i += kM2LThreadsB) {
             const int c = i % kRB, fm = i / kRB, f = fm / Q, m = fm % Q;
-            sV[((size_t)m * 4 + f) * kRB + c] = c < nc ? dm::to_c(Vs[((size_t)f * Qs + m) * r + c0 + c], T(0)) : C{0, 0};
+            sV[((size_t)m * 4 + f) * kRB + c] = c < nc ? dm::to_f(Vs[((size_t)f * Qs + m) * r + c0 + c]) : C{0, 0};
         }
         __syncthreads();
         if (active) {
@@ -520,8 +518,7 @@ __global__ __launch_bounds__(kM2LThreadsB) void k_m2l_b(DevOp o, int r, const M2
 #pragma unroll
                 for (int t = 0; t < kNTB; ++t) {
                     const T d0 = xt[t][0] - x0, d1 = xt[t][1] - x1, d2 = xt[t][2] - x2;
-                    if constexpr (sizeof(T) == 8) G[t] = dm::helmholtz_r2_tab(kap, fma(d0, d0, fma(d1, d1, d2 * d2)), sTab);
-                    else G[t] = dm::helmholtz_r2(kap, fma(d0, d0, fma(d1, d1, d2 * d2)));
+                    G[t] = dm::helmholtz_r2(kap, fma(d0, d0, fma(d1, d1, d2 * d2)));
                 }
 #pragma unroll
                 for (int f = 0; f < 4; ++f) {
@@ -1004,12 +1001,10 @@ void apply_batched(ige_op op, int r, const double2 *x, double2 *y, double2 *xt, 
                 const int rb = std::min(rbmax, tune_get(op, kTuneM2lRb, r, prec, rbmax));
                 const dim3 grid(op->work.size(), chunks(rb)), blk(kM2LThreadsB);
                 const size_t shm = fixed + per * rb;
-                {
-                    switch (rb) {
-                        case 4: hipLaunchKernelGGL((k_m2l_b<float, 4>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                        case 2: hipLaunchKernelGGL((k_m2l_b<float, 2>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                        default: hipLaunchKernelGGL((k_m2l_b<float, 1>), grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
-                    }
+                switch (rb) {
+                    case 4: hipLaunchKernelGGL(k_m2l_b<4>, grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
+                    case 2: hipLaunchKernelGGL(k_m2l_b<2>, grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
+                    default: hipLaunchKernelGGL(k_m2l_b<1>, grid, blk, shm, s, o, r, op->d_work.p, op->d_partner.p, op->d_bsrc.p, op->d_bpart.p); break;
                 }
                 IGE_HIP(hipGetLastError());
             }
