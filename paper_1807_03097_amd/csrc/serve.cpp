@@ -348,20 +348,22 @@ namespace {
 void fill_stats(const SrvReq &r, ige_srv_stats *st)
 {
     if (!st) return;
+    // what the worker writes while it runs the request: from its end on
+    const bool done = r.state == 2;
     st->state = r.state;
-    st->rc = r.rc;
-    st->iters = r.iters;
-    st->relres = r.relres;
+    st->rc = done ? r.rc : 0;
+    st->iters = done ? r.iters : 0;
+    st->relres = done ? r.relres : 0.0;
     st->n_dof = r.n_dof;
     st->footprint = r.footprint;
     st->t_submit = r.t_submit;
     st->t_start = r.t_start;
     st->t_done = r.t_done;
-    st->assemble_s = r.assemble_s;
-    st->solve_s = r.solve_s;
+    st->assemble_s = done ? r.assemble_s : 0.0;
+    st->solve_s = done ? r.solve_s : 0.0;
     st->n_waves = r.nw;
-    st->merged = r.merged;
-    st->reused = r.reused ? 1 : 0;
+    st->merged = done ? r.merged : 1;
+    st->reused = done && r.reused ? 1 : 0;
 }
 
 template <typename F>
