@@ -862,14 +862,17 @@ ige_op ige::assemble_on(ige_ctx ctx, const ige_geom_s *geom, const ige_params &p
             // one FP64 column: the coupling over unordered pairs
             if (!T.far.empty()) ige::plan_m2l_sym(op, s);
             if (op->stored) ige::store_coupling(op);
-            IGE_HIP(hipStreamCreate(&op->aux));
+            // not synchronised with the legacy stream: it takes part in captures, and work on the
+            // legacy stream (of any thread) is not allowed while a blocking stream does.  All its
+            // work is forked from the context's stream and joined to it
+            IGE_HIP(hipStreamCreateWithFlags(&op->aux, hipStreamNonBlocking));
             // fork/join between two streams of one device: no system-scope fence (the
             // kernels' own releases and acquires order the device memory; 5 us per apply)
             IGE_HIP(hipEventCreateWithFlags(&op->ev_fork, hipEventDisableTiming | hipEventDisableSystemFence));
             IGE_HIP(hipEventCreateWithFlags(&op->ev_join, hipEventDisableTiming | hipEventDisableSystemFence));
+            int err = 0;   // copied on this stream: on the legacy one it would wait for every worker's
+            IGE_HIP(hipMemcpyAsync(&err, op->d_err.p, sizeof(int), hipMemcpyDeviceToHost, s));
             IGE_HIP(hipStreamSynchronize(s));
-            int err = 0;
-            IGE_HIP(hipMemcpy(&err, op->d_err.p, sizeof(int), hipMemcpyDeviceToHost));
             IGE_REQUIRE(err == 0, "near-field assembly produced entries outside the leaf function slots");
             // what the assembly alone needed goes before what only products need comes
             op->d_sblk.release();
@@ -1005,8 +1008,9 @@ int ige_op_near_blocks(ige_op op, ige_c64 *out, int64_t n)
         IGE_REQUIRE(op->assembled, "operator was planned, not assembled");
         IGE_REQUIRE(n == op->nnz, "n must equal near_nnz");
         set_device(op->ctx);
-        IGE_HIP(hipStreamSynchronize(op->ctx->stream));
-        if (n > 0) IGE_HIP(hipMemcpy(out, op->d_bval.p, sizeof(double2) * (size_t)n, hipMemcpyDeviceToHost));
+        hipStream_t s = op->ctx->stream;
+        if (n > 0) IGE_HIP(hipMemcpyAsync(out, op->d_bval.p, sizeof(double2) * (size_t)n, hipMemcpyDeviceToHost, s));
+        IGE_HIP(hipStreamSynchronize(s));
     });
 }
 
