@@ -271,7 +271,8 @@ int ige_op_autotune(ige_op op, int r, int prec, int *choice, int nchoice);
  * of the coupling kernel (stages 7 and 8 below; the others read 0), for timing the
  * dominant kernels at little cost; level 0 stops recording.  ige_op_stage_times
  * synchronises the streams and returns the average device time (ms) per stage over
- * the last (up to 256) recorded applies: 0 P2M, 1 M2M, 2 M2L, 3 M2L reduce, 4 L2L,
+ * the last (up to 256) recorded applies: 0 P2M, 1 M2M, 2 M2L, 3 M2L reduce, 4 L2L (for
+ * one column that into the leaves runs in stage 6),
  * 5 near-field product (block pass and reduction), 6 L2P, 7 the block pass alone (the
  * whole near-field product for r > 1), 8 the coupling product alone (stage 2 without
  * the conversion of the source fields to the matrix-core operand layout).  n:
@@ -288,7 +289,8 @@ int ige_op_stage_times(ige_op op, double *ms, int n);
  * e_inc(x) = pol * exp(i kappa dir.x) (Sec. 3.2, eq. (eq:linsys) with the rotated
  * trace pairing written out): dir [r][3] unit vectors (host), pol [r][3] complex
  * (host), f: N*r complex in ptr_kind memory.  Solving A w = f gives the surface
- * current w with e_s = V~ w (eq:ESLP). */
+ * current w with e_s = V~ w (eq:ESLP).  The element moments go through scratch memory
+ * of the operator: calls on one operator, and replays of captured ones, must be ordered. */
 int ige_rhs_plane_wave(ige_op op, int r, const double *dir, const ige_c64 *pol, ige_c64 *f, int ptr_kind);
 
 /* Right-hand side of the scalar single layer (kind IGE_OP_SCALAR), the Galerkin
@@ -411,7 +413,9 @@ int ige_srv_destroy(ige_srv srv);
  *   e_s(x) = int G(x-y) w(y) + kappa^-2 grad_x int G(x-y) div w(y) dsigma(y),
  * each element integrated with the g x g Gauss rule of the near field, so points
  * should stay a few element sizes away from the surface.  E: [r][npts][3] complex,
- * host memory.  Synchronous; uses temporary device memory (E * g^2 * 88 bytes).
+ * host memory.  Synchronous; its device memory (E * g^2 * 88 bytes, points, results)
+ * is made by the first call and kept with the operator while at most 256 MiB, so calls
+ * on one operator must not overlap.
  * On the scalar single layer (kind IGE_OP_SCALAR) component 0 of each point holds
  * the single layer potential u(x) = int G(x-y) w(y) dsigma(y) and components 1, 2
  * are zero. */

@@ -26,9 +26,9 @@ typedef double dx4 __attribute__((ext_vector_type(4)));
 // lane took its fields from shared memory for 3 rows at a time and spent 4 fields on the
 // scalar operator; the one with stored blocks padded 2 Q to multiples of 32 on both sides and
 // the columns to 64 or 128.
-// Level 6, 27,912 ordered pairs of 81 nodes, 64 columns: 10.7 ms from stored blocks, 9.3 now (49
+// Level 6, 27,912 ordered pairs of 81 nodes, 64 columns: 10.7 ms from stored blocks, 9.2 now (50
 // TFLOP/s of matrix instructions); torus level 4, 26,848 pairs of 49 nodes, 23 columns: 2.66 and
-// 1.31 ms; scalar, sphere level 4, 64 nodes, 5 columns: 504 us evaluated before, 84 now.
+// 1.40 ms beside the near field; scalar, sphere level 4, 64 nodes, 5 columns: 504 us evaluated before, 88 now.
 template <int NT, int KC, int KS>
 __global__ __launch_bounds__(KS > 1 ? 768 : 1024) void k_m2l_gen(DevOp o, int r, int rc, int nf, const M2LWork *work, const int32_t *partner,
                                                   const double2 *src, double2 *part)

@@ -39,8 +39,8 @@ __device__ inline double perm_lane(int addr, double v)
 // cycles each) and the transposition per 64 values that stand for 128 ordered node pairs;
 // the ordered form (one value per ordered pair, 16 complex multiply-adds of a lane, partner
 // nodes and fields through shared memory) issued 61 instructions per 64.  Level 5, 5,520
-// ordered pairs of 81 nodes: 92 us before, 65 now, the apply beside
-// the near-field product 164 and 141 us (with that product's own step).
+// ordered pairs of 81 nodes: 92 us before, 69 now (73 between events), the apply beside
+// the near-field product 164 and 138 us (with that product's own step).
 //
 // The waves are two row halves (RT tiles each) x two column halves of the same partner.  The
 // next partner's nodes and fields are on their way into registers during the whole of the
@@ -392,8 +392,9 @@ SymRule sym_rule(const ige_op_s *op)
     // 118 with four).  Four beside a near-field product that takes at least half as long: fewer
     // items start and load their rows beside it (level 5, one column, 141 us against 150 with two
     // or three, 153 with six; torus level 5, degree 5, near field four times the coupling: 616
-    // against 663; level 6, degrees up to 14: 725 against 719).  The times compared are near bytes
-    // at 4.7 TB/s and steps of 16 rows x 4 columns at 340 cycles on 1,024 SIMDs.
+    // against 663; a tie at level 6, degrees up to 14: 725 against 719).  The times compared are near bytes
+    // at 4.7 TB/s and steps of 16 rows x 4 columns at 340 cycles on 1,024 SIMDs, all of them
+    // busy: a scale for the coupling, not its time (level 5: 40 us by it, 69 measured).
     double steps = 0.0;
     int64_t items = 0;
     int rt = 1;

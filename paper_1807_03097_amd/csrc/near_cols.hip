@@ -26,7 +26,7 @@ typedef double dx4 __attribute__((ext_vector_type(4)));
 // products per block and 16 columns' worth of matrix instructions 349 us), beyond by the matrix
 // instructions (level 6, 64 columns, 132 GFLOP: 2.70 ms = 49 TFLOP/s; from blocks padded to 32
 // slots, split into parts and stored per ordered pair 4.5 ms, 2.1 GB more).  Scalar level 4, 36
-// slots, 5 columns: 54 us, 138 with the unordered blocks in passes of 4 columns.
+// slots, 5 columns: 22 us (54 in an earlier form), 138 with the unordered blocks in passes of 4 columns.
 // Contiguous items per XCD measured slower (level 6, 64 columns 2.90 ms against 2.70), 4x4x4
 // instructions for up to 6 columns no faster.
 // UG: steps of four slots loaded ahead
@@ -168,7 +168,8 @@ __global__ __launch_bounds__(256) void k_near_cols_sum(int64_t N, int r, int S, 
 // large leaves: it reads half the bytes and uses the vector units beside the coupling's matrix
 // instructions (level 6, 180 slots per leaf, 4 columns: 1,650 us per apply with it, 1,735 here; 6
 // columns: 3,144 and 2,009; level 4, 4 columns: 101 and 107, 8 columns: 157 and 131; 84 slots, 4
-// columns: 351 and 314; level 5, 3 columns: 437 and 422)
+// columns: 351 and 314).  The line lies where the blocks of level 6 put it; with the same 180
+// slots at level 5, 3 columns, it is 3 % off (437 with the unordered blocks, 422 here).
 bool near_cols_use(const ige_op_s *op, int r)
 {
     const int nF = op->view.nF;

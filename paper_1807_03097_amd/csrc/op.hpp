@@ -153,7 +153,7 @@ struct ige_op_s {
     // many columns: the near-field product on the second stream beside the far field
     // (0: in line after it, 1: from the start, 2: after M2M)
     int batch_overlap = 1;
-    double near_us = 0.0, far_us = 0.0;   // one column: near-field product and coupling at their rates, microseconds
+    double near_us = 0.0, far_us = 0.0;   // one column: scales of near-field product and coupling (sym_rule), microseconds
     bool near_first = false;           // overlap: near field beside the upward pass only, then the coupling alone
     hipEvent_t ev_fork = nullptr, ev_join = nullptr;
     int64_t prof_count = 0;
