@@ -370,8 +370,9 @@ bool ige::krylov_goes_on(int r, const char *run, const int *iters, const int *ca
 
 // device bytes an assembled operator and a GMRES of r columns with the given restart will
 // hold at most (estimate from the host plan): what stays, and the largest of what the assembly,
-// the right-hand sides and the solve need one after the other.  FP64 coupling blocks that an
-// autotuner may store are not counted (it runs outside a server)
+// the right-hand sides and the solve need one after the other.  FP64 coupling blocks are counted
+// where IGE_M2L_F64=stored asks for them, not where an autotuner may store them (it runs
+// outside a server)
 size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const ige_solve_opts *opts)
 {
     const ige::Discretisation &D = op->D;
@@ -409,6 +410,13 @@ size_t ige::planned_device_bytes(const ige_op_s *op, int restart, int r, const i
         mitems += (k - i + 31) / 32;
     }
     if (R > 1) b += std::max(items, mitems) * 4 * Q * 16 * R;
+    const char *f64 = std::getenv("IGE_M2L_F64");
+    if (R >= 8 && f64 && std::string(f64) == "stored") {
+        size_t qf = 0;                                           // padded nodes on the levels with far pairs
+        for (const auto &f : op->T.far) qf = std::max(qf, 32 * (((size_t)(op->F.ql[f[0]] + 1) * (op->F.ql[f[0]] + 1) + 31) / 32));
+        if (qf <= 128)                                           // blocks, operands of at most 128 columns a chunk, partials
+            b += nfp * 2 * qf * 2 * qf * 8 + (size_t)op->NC * ((R + 31) / 32) * 128 * 2 * qf * 8 + mitems * 4 * Q * 16 * R;
+    }
     const size_t spart = std::max(sym_rule(op).parts, items1) * 4 * Q * 16;   // and partial results of either precision
     const size_t rhs = std::min<size_t>((size_t)256 << 20, mom * 16 * std::min<size_t>(R, kRhsCols));
     size_t solve = ((size_t)restart + 1 + 8) * D.N * 16 * R;     // Krylov basis and work vectors

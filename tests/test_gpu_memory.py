@@ -36,6 +36,34 @@ def test_small_objects_fit_small_budgets(surface, p, level, q, eta, depth, waves
     ctx.close()
 
 
+@pytest.mark.parametrize("surface,p,level,q,depth,q_level", [
+    ("sphere", 2, 5, 8, 3, None),            # 2,760 pairs of 96 padded nodes
+    ("torus", 1, 3, 7, -1, None),            # leaves of one element
+    ("sphere", 2, 5, 8, 3, [8, 8, 5]),       # level by level
+])
+def test_stored_fp64_coupling_is_admitted(monkeypatch, surface, p, level, q, depth, q_level):
+    # stored blocks, their operands and partials are part of what a request of 8 waves is admitted for
+    from paper_1807_03097_amd import binding as B
+    monkeypatch.setenv("IGE_M2L_F64", "stored")
+    ctx = B.Context(0)
+    geom = B.Geometry(ctx, W.cube_sphere() if surface == "sphere" else W.torus())
+    plan = B.Operator(geom, p, level, 2.0, q, 1.6, 5, 5, depth, plan_only=True)
+    dirs, pols = W.random_plane_waves(8, 3)
+    srv = B.Server(ctx, 1, 16 << 30, max_merge=1)
+    t = srv.submit(geom, p, level, 2.0, dirs, pols, q=q, eta=1.6, leaf_depth=depth, tol=1e-6, restart=5, maxit=3,
+                   q_level=q_level)
+    fp = srv.wait(t)["footprint"]
+    srv.close()
+    op = B.Operator(geom, p, level, 2.0, q, 1.6, 5, 5, depth, q_level=q_level)
+    before = int(B.ige_op_info(op.h).device_bytes)
+    op.solve(op.rhs_plane_wave(dirs, pols), tol=1e-6, restart=5, maxit=3)
+    held = int(B.ige_op_info(op.h).device_bytes)
+    pairs = len(plan.partition()["far"]) // 2
+    print(f"{pairs} pairs, footprint {fp / MIB:.1f} MiB, assembled {before / MIB:.1f}, after a solve {held / MIB:.1f}", flush=True)
+    assert held <= fp
+    ctx.close()
+
+
 def test_potential_workspace_on_first_use():
     # sources of 24 x 25 points and a few points and results: well under 1 MiB
     from paper_1807_03097_amd import binding as B
